@@ -443,43 +443,135 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
   }
 }
 
-// Three standard normals for one spin update: counter (atom id, step lo,
-// step hi, replica<<2|sub), key (seed lo, seed hi); u = (x + 1/2) 2^-32 and
-// Box-Muller on (u0, u1) and (u2, u3).
-__device__ __forceinline__ void gauss3(uint64_t seed, uint32_t id, int64_t step,
-                                       uint32_t replica, int sub, double g[3]) {
-  uint32_t c[4] = {id, (uint32_t)((uint64_t)step & 0xffffffffu),
-                   (uint32_t)((uint64_t)step >> 32), (replica << 2) | (uint32_t)(sub & 3)};
-  philox4x32_10(c, (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32));
-  const double s = 1.0 / 4294967296.0;
-  const double twopi = 6.283185307179586;
-  double u0 = ((double)c[0] + 0.5) * s, u1 = ((double)c[1] + 0.5) * s;
-  double u2 = ((double)c[2] + 0.5) * s, u3 = ((double)c[3] + 0.5) * s;
-  double ra = sqrt(-2.0 * log(u0)), rb = sqrt(-2.0 * log(u2));
-  double sn, cs;
-  sincos(twopi * u1, &sn, &cs);
-  g[0] = ra * cs;
-  g[1] = ra * sn;
-  g[2] = rb * cos(twopi * u3);
+// a*b + c with the coefficient c in scalar registers: the Horner steps of the
+// normals below then take one vector instruction each and no vector register
+// for the coefficient.
+__device__ __forceinline__ double fma_sc(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
 }
 
+// Box-Muller's functions on the uniforms of the Philox words, 0 < u < 1,
+// without the argument checks and large-argument reductions of the library's
+// log, sqrt and sincos (those took about 540 instructions per FP64 draw, most
+// of the instructions of a spin update, these with Philox about 250; the
+// update is bound by the latency of its instruction stream when a class is a
+// few wavefronts per SIMD or less).
+//
+// -2 ln u: u = 2^k (1 + f) with sqrt(1/2) <= 1 + f < sqrt(2), s = f/(2 + f)
+// and ln(1 + f) = 2 atanh(s) = f - s (f - R), R = 2 (s^2/3 + s^4/5 + ...)
+// (2s = f - s f, so the rounding of s enters scaled by f). The series is cut
+// at s^20 (2e-17 relative).
+__device__ __forceinline__ double neg2_log(double u) {
+  double m = __builtin_amdgcn_frexp_mant(u);  // [1/2, 1)
+  int k = __builtin_amdgcn_frexp_exp(u);
+  const bool low = m < 0.70710678118654752440;
+  m = low ? 2.0 * m : m;
+  k = low ? k - 1 : k;
+  const double f = m - 1.0, b = m + 1.0;
+  double y = __builtin_amdgcn_rcp(b);
+  y = fma(y, fma(-b, y, 1.0), y);
+  y = fma(y, fma(-b, y, 1.0), y);
+  const double s = f * y, z = s * s;
+  double R = fma_sc(z, 2.0 / 19.0, 2.0 / 17.0);
+  R = fma_sc(R, z, 2.0 / 15.0);
+  R = fma_sc(R, z, 2.0 / 13.0);
+  R = fma_sc(R, z, 2.0 / 11.0);
+  R = fma_sc(R, z, 2.0 / 9.0);
+  R = fma_sc(R, z, 2.0 / 7.0);
+  R = fma_sc(R, z, 2.0 / 5.0);
+  R = fma_sc(R, z, 2.0 / 3.0);
+  R *= z;
+  const double kd = (double)k;
+  // k ln 2 in two parts, the first exact in the product
+  const double t = f - fma(kd, -1.90821492927058770002e-10, s * (f - R));
+  return -2.0 * fma(kd, 6.93147180369123816490e-01, t);
+}
+
+// sqrt(x) of a normal x > 0: the hardware estimate of 1/sqrt(x), one coupled
+// Newton step and a last step on the residual x - g^2.
+__device__ __forceinline__ double sqrt_pos(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  return fma(fma(-g, g, x), h, g);
+}
+
+// sin(2 pi z), |z| <= 1/4, by its Taylor series (2 pi z)^(2k+1)/(2k+1)! to
+// k = 10 (1e-18 at |z| = 1/4). cos(2 pi u) = sin(2 pi (|u - 1/2| - 1/4)) on
+// [0, 1] then needs no quadrant selection, and the argument reduction is exact
+// (multiples of 2^-33), where 2 pi u rounded to a double moved the angle by up
+// to 4e-16.
+__device__ __forceinline__ double sin_2pi(double z) {
+  const double w = z * z;
+  double p = fma_sc(w, 1.1309237482517961e-3, -1.2031585942120627e-2);
+  p = fma_sc(p, w, 1.0422916220813984e-1);
+  p = fma_sc(p, w, -7.1812230177850052e-1);
+  p = fma_sc(p, w, 3.8199525848482821);
+  p = fma_sc(p, w, -1.5094642576822990e1);
+  p = fma_sc(p, w, 4.2058693944897654e1);
+  p = fma_sc(p, w, -7.6705859753061385e1);
+  p = fma_sc(p, w, 8.1605249276075055e1);
+  p = fma_sc(p, w, -4.1341702240399760e1);
+  p = fma_sc(p, w, 6.2831853071795865);
+  return z * p;
+}
+
+// The same in FP32: series to s^8 (5e-9), a residual step on the hardware
+// square root estimate, and the sine to (2 pi z)^13 (7e-10 at |z| = 1/4).
+__device__ __forceinline__ float neg2_log(float u) {
+  float m = __builtin_amdgcn_frexp_mantf(u);
+  int k = __builtin_amdgcn_frexp_expf(u);
+  const bool low = m < 0.70710678f;
+  m = low ? 2.0f * m : m;
+  k = low ? k - 1 : k;
+  const float f = m - 1.0f;
+  const float s = f * __builtin_amdgcn_rcpf(m + 1.0f), z = s * s;
+  const float R = z * fmaf(z, fmaf(z, fmaf(z, 2.0f / 9.0f, 2.0f / 7.0f), 2.0f / 5.0f), 2.0f / 3.0f);
+  const float kd = (float)k;
+  const float t = f - fmaf(kd, 2.12194440e-4f, s * (f - R));
+  return -2.0f * fmaf(kd, 6.93359375e-1f, t);
+}
+__device__ __forceinline__ float sqrt_pos(float x) {
+  const float y = __builtin_amdgcn_rsqf(fmaxf(x, 1e-30f));  // u may round to 1: x = 0
+  const float g = x * y;
+  return fmaf(fmaf(-g, g, x), 0.5f * y, g);
+}
+__device__ __forceinline__ float sin_2pi(float z) {
+  const float w = z * z;
+  float p = fmaf(w, 3.8199526f, -15.0946426f);
+  p = fmaf(p, w, 42.0586939f);
+  p = fmaf(p, w, -76.7058598f);
+  p = fmaf(p, w, 81.6052493f);
+  p = fmaf(p, w, -41.3417022f);
+  p = fmaf(p, w, 6.28318531f);
+  return z * p;
+}
+
+// Three standard normals for one spin update: counter (atom id, step lo,
+// step hi, replica<<2|sub), key (seed lo, seed hi); u = (x + 1/2) 2^-32 (the
+// FP32 form: of the leading 24 bits, in FP32) and Box-Muller on (u0, u1) and
+// (u2, u3).
+template <typename real>
 __device__ __forceinline__ void gauss3(uint64_t seed, uint32_t id, int64_t step,
-                                       uint32_t replica, int sub, float g[3]) {
+                                       uint32_t replica, int sub, real g[3]) {
   uint32_t c[4] = {id, (uint32_t)((uint64_t)step & 0xffffffffu),
                    (uint32_t)((uint64_t)step >> 32), (replica << 2) | (uint32_t)(sub & 3)};
   philox4x32_10(c, (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32));
-  const float s = 2.3283064365386963e-10f;
-  const float twopi = 6.2831853071795865f;
-  float u0 = ((float)(c[0] >> 8) + 0.5f) * (s * 256.0f);
-  float u1 = ((float)(c[1] >> 8) + 0.5f) * (s * 256.0f);
-  float u2 = ((float)(c[2] >> 8) + 0.5f) * (s * 256.0f);
-  float u3 = ((float)(c[3] >> 8) + 0.5f) * (s * 256.0f);
-  float ra = sqrtf(-2.0f * logf(u0)), rb = sqrtf(-2.0f * logf(u2));
-  float sn, cs;
-  sincosf(twopi * u1, &sn, &cs);
-  g[0] = ra * cs;
-  g[1] = ra * sn;
-  g[2] = rb * cosf(twopi * u3);
+  real u[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    u[q] = sizeof(real) == 8 ? ((real)c[q] + (real)0.5) * (real)(1.0 / 4294967296.0)
+                             : ((real)(c[q] >> 8) + (real)0.5) * (real)(1.0 / 16777216.0);
+  const real half = (real)0.5, quarter = (real)0.25;
+  const real ra = sqrt_pos(neg2_log(u[0])), rb = sqrt_pos(neg2_log(u[2]));
+  g[0] = ra * sin_2pi(fabs(u[1] - half) - quarter);
+  // sin(2 pi u) = cos(2 pi |u - 1/4|)
+  g[1] = ra * sin_2pi(fabs(fabs(u[1] - quarter) - half) - quarter);
+  g[2] = rb * sin_2pi(fabs(u[3] - half) - quarter);
 }
 
 // -------------------------------------------------------------------------
