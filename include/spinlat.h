@@ -292,9 +292,11 @@ int sl_get_stats(sl_system *sys, sl_stats *out);
 int sl_synchronize(sl_system *sys);
 
 /* Launch shape of the per-step kernels. Changes speed only: the results
- * differ at most by summation-order roundoff. lanes = 1, 2, 4 or 8
- * consecutive wavefront lanes cooperate on one atom (0 = default: 2 for
- * the spin phase, 1 for forces).
+ * differ at most by summation-order roundoff. lanes = 1, 2, 4 or 8 lanes
+ * cooperate on one atom. 0 = default: in the spin phase chosen per class from
+ * its size, in the force launch from the number of atoms (a value set there is
+ * the least number taken; a system too small to fill the device takes more);
+ * sl_get_tuning reports the defaults as 2 and 1.
  * Runs of consecutive colour classes of at most small_class atoms each are
  * applied by one single-workgroup launch (0 = default 128, -1 = never). */
 typedef struct {
@@ -305,8 +307,9 @@ typedef struct {
                          the spline form of a learned one): J(r_ij) of every
                          spin-segment entry is evaluated once per drift and
                          read by the spin phases; 0 = default (on for the
-                         FP32 form, off for FP64, as measured on MI355X),
-                         1 on, -1 off */
+                         FP32 form; for FP64 on where it pays: with the spin
+                         bath, with seven or more classes, in large systems
+                         and on frozen lattices, reported as -1), 1 on, -1 off */
     int overlap;      /* split force (analytic potentials, 1 or 2 force
                          lanes): the spin-independent pair terms of a step's
                          closing force run on a second stream of the library

@@ -14,12 +14,16 @@ namespace sl {
 // before the previous one decides; if a rebuild is due the replica stops
 // and the host rebuilds it before the next launch. Replicas are
 // independent, so no two workgroups ever wait on each other.
-template <typename real, int LANES, int MLP>
+template <typename real, int WAVES, int MLP>
 __global__ __launch_bounds__(kBatchBlock) void k_batch_run(RepDesc<real> *D) {
   __shared__ double redm[kBatchBlock / 64][3];
   __shared__ double bcast[3];
   RepDesc<real> &d = D[blockIdx.x];
-  const int t = threadIdx.x, l = t & (LANES - 1), per = kBatchBlock / LANES;
+  constexpr int kTeams = kBatchBlock / 64 / WAVES;
+  __shared__ SpinTeam<real, WAVES> steam[WAVES > 1 ? kTeams : 1];
+  __shared__ ForceTeam<real, WAVES> fteam[WAVES > 1 ? kTeams : 1];
+  const int t = threadIdx.x, tm = wave_id() / WAVES, w = wave_id() % WAVES, per = 64 * kTeams;
+  const int a = 64 * tm + (t & 63);  // atom of a pass
   int pos = d.pos;
   int64_t step = d.step;
   const int64_t target = d.target;
@@ -48,9 +52,10 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch_run(RepDesc<real> *D) {
         else if (q > K - 1) sb[0] = subf + 1;
         const int b0 = d.off[c], b1 = d.off[c + 1];
         for (int base = b0; base < b1; base += per) {
-          const int i = base + t / LANES;
-          spin_update<real, true, true, LANES, (MLP & 7)>(V, d.P, i, i < b1, l, nrep, st, sb, d.h, d.amp,
-                                                     d.seed, d.replica, d.rs2);
+          const int i = base + a;
+          spin_update<real, true, true, WAVES, (MLP & 7)>(V, d.P, i, i < b1, w, steam + tm, nrep, st, sb,
+                                                          d.h, d.amp, d.seed, d.replica, d.rs2);
+          if (WAVES > 1) __syncthreads();
         }
         __syncthreads();
       }
@@ -74,10 +79,11 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch_run(RepDesc<real> *D) {
     const bool next = step + 1 < target;
     double bdm = 0.0, bvm = 0.0, bwm = kInf;
     for (int base = 0; base < W.n; base += per) {
-      const int i = base + t / LANES;
+      const int i = base + a;
       double e[8], dm = 0.0, vm = 0.0, wm = kInf;
-      if (next) force_atom<real, kModeFinal | kModeNext, LANES, MLP>(W, d.P, F, i, i < W.n, l, e, dm, vm, wm);
-      else force_atom<real, kModeFinal, LANES, MLP>(W, d.P, F, i, i < W.n, l, e, dm, vm, wm);
+      if (next) force_atom<real, kModeFinal | kModeNext, WAVES, MLP>(W, d.P, F, i, i < W.n, w, fteam + tm, e, dm, vm, wm);
+      else force_atom<real, kModeFinal, WAVES, MLP>(W, d.P, F, i, i < W.n, w, fteam + tm, e, dm, vm, wm);
+      if (WAVES > 1) __syncthreads();
       bdm = fmax(bdm, dm);
       bvm = fmax(bvm, vm);
       bwm = fmin(bwm, wm);
@@ -88,15 +94,15 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch_run(RepDesc<real> *D) {
     if ((t & 63) == 0) { redm[t >> 6][0] = bdm; redm[t >> 6][1] = bvm; redm[t >> 6][2] = bwm; }
     __syncthreads();
     if (t == 0) {
-      double a = 0.0, b = 0.0, c = kInf;
-      for (int w = 0; w < kBatchBlock / 64; ++w) {
-        a = fmax(a, redm[w][0]);
-        b = fmax(b, redm[w][1]);
-        c = fmin(c, redm[w][2]);
+      double xd = 0.0, xv = 0.0, xw = kInf;
+      for (int q = 0; q < kBatchBlock / 64; ++q) {
+        xd = fmax(xd, redm[q][0]);
+        xv = fmax(xv, redm[q][1]);
+        xw = fmin(xw, redm[q][2]);
       }
-      bcast[0] = a;
-      bcast[1] = b;
-      bcast[2] = c;
+      bcast[0] = xd;
+      bcast[1] = xv;
+      bcast[2] = xw;
     }
     __syncthreads();
     pdm = cdm; pvm = cvm; pdt = cdt; pwm = cwm; prb = crb; havep = 1;
@@ -143,7 +149,7 @@ template void launch_batch_run<float>(RepDesc<float> *, int, int, int, hipStream
 // the whole device works on each phase instead of one workgroup per replica.
 // All replicas advance in lockstep inside a call; replica r is at step
 // d.step + kk with its current positions in buffer d.pos ^ (kk & 1).
-template <typename real, int LANES, int MLP>
+template <typename real, int WAVES, int MLP>
 __global__ __launch_bounds__(kBlock) void k_batch_spin(const RepDesc<real> *D, BatchPhase bp) {
   const RepDesc<real> &d = D[blockIdx.y];
   const int K = d.K;
@@ -159,29 +165,33 @@ __global__ __launch_bounds__(kBlock) void k_batch_spin(const RepDesc<real> *D, B
     s0 = subf + 1;
   }
   const int b0 = d.off[c], b1 = d.off[c + 1];
-  const int base = b0 + (int)blockIdx.x * (kBlock / LANES);
+  const int base = b0 + (int)blockIdx.x * team_atoms(WAVES);
   if (base >= b1) return;
-  const int i = base + (int)threadIdx.x / LANES, l = threadIdx.x & (LANES - 1);
+  __shared__ SpinTeam<real, WAVES> team[WAVES > 1 ? kBlock / 64 / WAVES : 1];
+  const int t = wave_id() / WAVES, w = wave_id() % WAVES;
+  const int i = base + 64 * t + (int)(threadIdx.x & 63);
   const int pos = d.pos ^ (bp.kk & 1);
   const int64_t step = d.step + bp.kk;
   const int64_t st[kMaxRep] = {step, step, step, step};
   const int sb[kMaxRep] = {s0, s1, 0, 0};
-  spin_update<real, true, true, LANES, MLP>(d.V[bp.half == 0 ? pos : 1 - pos], d.P, i, i < b1,
-                                             l, nrep, st, sb, d.h, d.amp, d.seed, d.replica,
-                                             d.rs2);
+  spin_update<real, true, true, WAVES, MLP>(d.V[bp.half == 0 ? pos : 1 - pos], d.P, i, i < b1,
+                                             w, team + t, nrep, st, sb, d.h, d.amp, d.seed,
+                                             d.replica, d.rs2);
 }
 
 // Force, kicks and drift of every replica at one boundary; each block stores
 // its replica's rebuild predictor terms, which k_batch_pred_reduce joins into
 // the replica's pinned slot (as k_pred_reduce does for one system).
-template <typename real, int MODE, int LANES, int MLP>
+template <typename real, int MODE, int WAVES, int MLP>
 __global__ __launch_bounds__(kBlock) void k_batch_force(const RepDesc<real> *D, BatchPhase bp) {
   __shared__ double redm[kBlock / 64][3];
   const RepDesc<real> &d = D[blockIdx.y];
   const int n = d.V[0].n;
-  const int per = kBlock / LANES;
+  constexpr int per = team_atoms(WAVES);
   const int nb = (n + per - 1) / per;
   if ((int)blockIdx.x >= nb) return;
+  __shared__ ForceTeam<real, WAVES> team[WAVES > 1 ? kBlock / 64 / WAVES : 1];
+  const int t = wave_id() / WAVES, w = wave_id() % WAVES;
   // buffer holding this boundary's positions; the drift goes to the other
   const int cur = bp.after ? 1 - (d.pos ^ (bp.kk & 1)) : d.pos;
   const int64_t boundary = d.step + bp.kk + bp.after;
@@ -192,9 +202,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_force(const RepDesc<real> *D, 
   F.ny = const_cast<double *>(d.V[1 - cur].ry);
   F.nz = const_cast<double *>(d.V[1 - cur].rz);
   F.host_out = d.ring + 8 * (int)(boundary & 3);
-  const int i = (int)blockIdx.x * per + (int)threadIdx.x / LANES, l = threadIdx.x & (LANES - 1);
+  const int i = (int)blockIdx.x * per + 64 * t + (int)(threadIdx.x & 63);
   double e[8], dm = 0.0, vm = 0.0, wm = kInf;
-  force_atom<real, MODE, LANES, MLP>(d.V[cur], d.P, F, i, i < n, l, e, dm, vm, wm);
+  force_atom<real, MODE, WAVES, MLP>(d.V[cur], d.P, F, i, i < n, w, team + t, e, dm, vm, wm);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const double a = wave_max(dm), b = wave_max(vm), c = wave_min(wm);
   if (lane == 0) { redm[wv][0] = a; redm[wv][1] = b; redm[wv][2] = c; }

@@ -19,12 +19,6 @@ constexpr double kMvv2e = 1.0364269652680506e-4;  // eV per amu A^2/ps^2
 
 constexpr double kInf = 1e300;     // "no watched pair" distance squared
 constexpr int kMaxRep = 4;        // consecutive updates one spin launch can do
-// Workgroup of the spin phase: one wavefront. A class of 108 000 atoms at one
-// lane per atom is 1688 wavefronts; in 256-thread groups the 422 groups
-// leave 166 CUs with two and 90 with one, in single-wave groups every CU gets
-// six or seven (2.6 % faster per step at 432 000 atoms).
-constexpr int kSpinBlock = 64;
-constexpr int kSpinChunk = 4;     // neighbours per lane gathered together (spin phase)
 // Neighbours per lane gathered together in the force gather. With
 // displacement-ordered rows 4 beats 8 (117 against 128 us per launch at
 // 432 000 atoms: fewer registers, more waves in flight) and 16 (195 us).
@@ -575,6 +569,11 @@ __device__ __forceinline__ void gauss3(uint64_t seed, uint32_t id, int64_t step,
 }
 
 // -------------------------------------------------------------------------
+// Wavefront of this thread in its workgroup, as a wave-uniform value.
+__device__ __forceinline__ int wave_id() {
+  return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+}
+
 // Wavefront (64 lanes) and block reductions.
 __device__ __forceinline__ double wave_sum(double x) {
 #pragma unroll

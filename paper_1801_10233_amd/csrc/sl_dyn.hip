@@ -10,43 +10,50 @@
                        // (3, 4 and 5 measured alike, 6, 7, 8 and 14 slower)
 #endif
 
+#include <climits>
+
+#ifndef SL_JC_SPLIT
+#define SL_JC_SPLIT 131072
+#endif
+
 namespace sl {
 
+constexpr int kJcSplitAtoms = SL_JC_SPLIT;  // below: the row's slots split over grid.y
+
 template <typename real, bool LANGEVIN, bool ANISO, int LANES, int MLP, bool DUAL>
-__global__ __launch_bounds__(kBlock) void k_spin_phase(SysView<real> S, PotConst P,
-                                                       SpinPhaseArgs A, SysView<real> S2) {
-  // LANES consecutive lanes share one atom: each gathers every LANES-th
-  // neighbour, the partial sums are combined with cross-lane shuffles and
-  // the first lane rotates and stores the spin.
-  const int t = xcd_tile(blockIdx.x, gridDim.x) * kSpinBlock + threadIdx.x;
-  const int l = t & (LANES - 1);
-  const int i = A.begin + t / LANES;
-  spin_update<real, LANGEVIN, ANISO, LANES, MLP, DUAL>(S, P, i, i < A.end, l, A.nrep, A.step,
-                                                       A.sub, A.h, A.amp, A.seed, A.replica,
-                                                       A.rs2, &S2, !DUAL && A.keep != 0);
+__global__ __launch_bounds__((64 * TeamShape<LANES, LANGEVIN>::waves)) void k_spin_phase(
+    SysView<real> S, PotConst P, SpinPhaseArgs A, SysView<real> S2) {
+  using T = TeamShape<LANES, LANGEVIN>;  // one workgroup per team
+  __shared__ SpinTeam<real, T::waves> team[1];
+  const int i = A.begin + xcd_tile(blockIdx.x, gridDim.x) * T::atoms + (int)(threadIdx.x & (T::atoms - 1));
+  spin_update<real, LANGEVIN, ANISO, LANES, MLP, DUAL>(S, P, i, i < A.end, wave_id(), team, A.nrep,
+                                                       A.step, A.sub, A.h, A.amp, A.seed,
+                                                       A.replica, A.rs2, &S2, !DUAL && A.keep != 0);
 }
 
 // A run of small classes (a few atoms each, e.g. the extra colours a repair
 // adds) in one workgroup: the items are applied in order with a workgroup
 // barrier between them, which keeps the class order of the sweep while
-// paying one launch for the whole run.
-template <typename real, bool LANGEVIN, bool ANISO, int LANES, int MLP>
+// paying one launch for the whole run. Teams of kTailLanes wavefronts whatever
+// the launch shape of the large classes.
+constexpr int kTailLanes = 4;
+template <typename real, bool LANGEVIN, bool ANISO, int MLP>
 __global__ __launch_bounds__(kTailBlock) void k_spin_tail(SysView<real> S, PotConst P,
                                                           TailArgs T) {
-  const int l = threadIdx.x & (LANES - 1);
-  const int per = kTailBlock / LANES;
+  constexpr int kTeams = kTailBlock / 64 / kTailLanes;
+  __shared__ SpinTeam<real, kTailLanes> team[kTeams];
+  const int t = wave_id() / kTailLanes, w = wave_id() % kTailLanes;
   for (int q = 0; q < T.nitems; ++q) {
     const TailItem &it = T.item[q];
-    for (int base = it.begin; base < it.end; base += per) {
-      const int i = base + (int)threadIdx.x / LANES;
-      spin_update<real, LANGEVIN, ANISO, LANES, MLP>(S, P, i, i < it.end, l, it.nrep, it.step,
-                                                     it.sub, T.h, T.amp, T.seed, T.replica, T.rs2);
+    for (int base = it.begin; base < it.end; base += 64 * kTeams) {
+      const int i = base + 64 * t + (int)(threadIdx.x & 63);
+      spin_update<real, LANGEVIN, ANISO, kTailLanes, MLP>(S, P, i, i < it.end, w, team + t, it.nrep,
+                                                          it.step, it.sub, T.h, T.amp, T.seed,
+                                                          T.replica, T.rs2);
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
-
-
 
 // Exchange coefficients at one set of positions (the optional pair
 // coefficient cache): J(r_ij) for every spin-segment entry, with the same
@@ -56,7 +63,7 @@ __global__ __launch_bounds__(kTailBlock) void k_spin_tail(SysView<real> S, PotCo
 // positions move, and only then).
 template <typename real, bool SPL>
 __global__ __launch_bounds__(kBlock) void k_jcache(SysView<real> S, PotConst P, real *out,
-                                                   double rs2, const int2 *tiles) {
+                                                   double rs2, const int2 *tiles, int slots) {
   // with a tile table, block b takes the atom range of entry b (one spatial
   // slab of every class per XCD, as in the force launch)
   int i, end;
@@ -69,12 +76,16 @@ __global__ __launch_bounds__(kBlock) void k_jcache(SysView<real> S, PotConst P, 
     end = S.n;
   }
   if (i >= end) return;
-  const int ns = S.nspin[i];
+  // grid.y splits the row into groups of `slots` slots: one group of all in a
+  // large system; in a small one (few wavefronts per SIMD) a group is one
+  // round, so that the row's rounds run side by side
+  const int kb = (int)blockIdx.y * slots;
+  const int ns = min(S.nspin[i], kb + slots);
   const double rix = S.rx[i], riy = S.ry[i], riz = S.rz[i];
   // slots in chunks of SL_JC_CHUNK with all loads of a chunk issued before
   // use (the row's own slots only: ns <= kcap)
   constexpr int CH = SL_JC_CHUNK;
-  for (int k0 = 0; k0 < ns; k0 += CH) {
+  for (int k0 = kb; k0 < ns; k0 += CH) {
     int jj[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
@@ -108,16 +119,19 @@ __global__ __launch_bounds__(kBlock) void k_jcache(SysView<real> S, PotConst P, 
 
 template <typename real>
 void launch_jcache(const SysView<real> &S, const PotConst &P, real *out, double rs2,
-                   const int2 *tiles, int ntiles, hipStream_t st) {
+                   const int2 *tiles, int ntiles, int max_slots, hipStream_t st) {
   if (S.n <= 0) return;
-  const dim3 grid(tiles ? ntiles : (S.n + kBlock - 1) / kBlock);
-  if (S.spl.t) hipLaunchKernelGGL((k_jcache<real, true>), grid, dim3(kBlock), 0, st, S, P, out, rs2, tiles);
-  else hipLaunchKernelGGL((k_jcache<real, false>), grid, dim3(kBlock), 0, st, S, P, out, rs2, tiles);
+  const int nx = tiles ? ntiles : (S.n + kBlock - 1) / kBlock;
+  const bool split = S.n < kJcSplitAtoms && max_slots > SL_JC_CHUNK;
+  const int slots = split ? SL_JC_CHUNK : INT_MAX / 2;
+  const dim3 grid(nx, split ? (max_slots + SL_JC_CHUNK - 1) / SL_JC_CHUNK : 1);
+  if (S.spl.t) hipLaunchKernelGGL((k_jcache<real, true>), grid, dim3(kBlock), 0, st, S, P, out, rs2, tiles, slots);
+  else hipLaunchKernelGGL((k_jcache<real, false>), grid, dim3(kBlock), 0, st, S, P, out, rs2, tiles, slots);
 }
 template void launch_jcache<double>(const SysView<double> &, const PotConst &, double *, double,
-                                    const int2 *, int, hipStream_t);
+                                    const int2 *, int, int, hipStream_t);
 template void launch_jcache<float>(const SysView<float> &, const PotConst &, float *, double,
-                                   const int2 *, int, hipStream_t);
+                                   const int2 *, int, int, hipStream_t);
 
 // Fixed-order sum of nb partial rows of 8 doubles (deterministic result).
 __global__ __launch_bounds__(256) void k_reduce8(const double *partial, int nb, double *out) {
@@ -143,16 +157,23 @@ __global__ __launch_bounds__(256) void k_reduce8(const double *partial, int nb, 
 // Host launchers. The learned-potential variants (table lookups instead of
 // the analytic J and V) exist in the FP32 form only; variant 4 is the
 // analytic potential with the spin-orbit pair terms.
+template <typename real, bool LG, bool AN, int LANES, int MLP, bool DUAL>
+static void spin_phase_run(const SysView<real> &S, const PotConst &P, const SpinPhaseArgs &A,
+                           const SysView<real> &S2, hipStream_t st) {
+  using T = TeamShape<LANES, LG>;
+  const int nb = (A.end - A.begin + T::atoms - 1) / T::atoms;
+  hipLaunchKernelGGL((k_spin_phase<real, LG, AN, LANES, MLP, DUAL>), dim3(nb), dim3(64 * T::waves), 0,
+                     st, S, P, A, S2);
+}
+
 template <typename real, int LANES, int MLP, bool DUAL>
 static void spin_phase_lanes3(const SysView<real> &S, const PotConst &P, const SpinPhaseArgs &A,
                               const SysView<real> &S2, hipStream_t st) {
-  const long threads = (long)(A.end - A.begin) * LANES;
-  const int nb = (int)((threads + kSpinBlock - 1) / kSpinBlock);
   const bool lg = P.langevin != 0, an = P.aniso_on != 0;
-  if (lg && an) hipLaunchKernelGGL((k_spin_phase<real, true, true, LANES, MLP, DUAL>), dim3(nb), dim3(kSpinBlock), 0, st, S, P, A, S2);
-  else if (lg) hipLaunchKernelGGL((k_spin_phase<real, true, false, LANES, MLP, DUAL>), dim3(nb), dim3(kSpinBlock), 0, st, S, P, A, S2);
-  else if (an) hipLaunchKernelGGL((k_spin_phase<real, false, true, LANES, MLP, DUAL>), dim3(nb), dim3(kSpinBlock), 0, st, S, P, A, S2);
-  else hipLaunchKernelGGL((k_spin_phase<real, false, false, LANES, MLP, DUAL>), dim3(nb), dim3(kSpinBlock), 0, st, S, P, A, S2);
+  if (lg && an) spin_phase_run<real, true, true, LANES, MLP, DUAL>(S, P, A, S2, st);
+  else if (lg) spin_phase_run<real, true, false, LANES, MLP, DUAL>(S, P, A, S2, st);
+  else if (an) spin_phase_run<real, false, true, LANES, MLP, DUAL>(S, P, A, S2, st);
+  else spin_phase_run<real, false, false, LANES, MLP, DUAL>(S, P, A, S2, st);
 }
 
 template <typename real, int LANES, int MLP>
@@ -184,36 +205,24 @@ void launch_spin_phase(const SysView<real> &S, const PotConst &P, const SpinPhas
   }
 }
 
-template <typename real, int LANES, int MLP>
-static void spin_tail_lanes2(const SysView<real> &S, const PotConst &P, const TailArgs &T,
-                             hipStream_t st) {
+template <typename real, int MLP>
+static void spin_tail_run(const SysView<real> &S, const PotConst &P, const TailArgs &T,
+                          hipStream_t st) {
   const bool lg = P.langevin != 0, an = P.aniso_on != 0;
-  if (lg && an) hipLaunchKernelGGL((k_spin_tail<real, true, true, LANES, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
-  else if (lg) hipLaunchKernelGGL((k_spin_tail<real, true, false, LANES, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
-  else if (an) hipLaunchKernelGGL((k_spin_tail<real, false, true, LANES, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
-  else hipLaunchKernelGGL((k_spin_tail<real, false, false, LANES, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
-}
-
-template <typename real, int LANES>
-static void spin_tail_lanes(const SysView<real> &S, const PotConst &P, const TailArgs &T,
-                            hipStream_t st) {
-  if (P.soc_on) spin_tail_lanes2<real, LANES, 4>(S, P, T, st);
-  else if (S.jc) spin_tail_lanes2<real, LANES, 3>(S, P, T, st);
-  else if (sizeof(real) == 4 && S.spl.t) spin_tail_lanes2<real, LANES, (sizeof(real) == 4 ? 2 : 0)>(S, P, T, st);
-  else if (sizeof(real) == 4 && S.tab) spin_tail_lanes2<real, LANES, (sizeof(real) == 4 ? 1 : 0)>(S, P, T, st);
-  else spin_tail_lanes2<real, LANES, 0>(S, P, T, st);
+  if (lg && an) hipLaunchKernelGGL((k_spin_tail<real, true, true, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
+  else if (lg) hipLaunchKernelGGL((k_spin_tail<real, true, false, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
+  else if (an) hipLaunchKernelGGL((k_spin_tail<real, false, true, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
+  else hipLaunchKernelGGL((k_spin_tail<real, false, false, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
 }
 
 template <typename real>
-void launch_spin_tail(const SysView<real> &S, const PotConst &P, const TailArgs &T, int lanes,
-                      hipStream_t st) {
+void launch_spin_tail(const SysView<real> &S, const PotConst &P, const TailArgs &T, hipStream_t st) {
   if (T.nitems <= 0) return;
-  switch (lanes) {
-    case 1: spin_tail_lanes<real, 1>(S, P, T, st); break;
-    case 2: spin_tail_lanes<real, 2>(S, P, T, st); break;
-    case 8: spin_tail_lanes<real, 8>(S, P, T, st); break;
-    default: spin_tail_lanes<real, 4>(S, P, T, st); break;
-  }
+  if (P.soc_on) spin_tail_run<real, 4>(S, P, T, st);
+  else if (S.jc) spin_tail_run<real, 3>(S, P, T, st);
+  else if (sizeof(real) == 4 && S.spl.t) spin_tail_run<real, (sizeof(real) == 4 ? 2 : 0)>(S, P, T, st);
+  else if (sizeof(real) == 4 && S.tab) spin_tail_run<real, (sizeof(real) == 4 ? 1 : 0)>(S, P, T, st);
+  else spin_tail_run<real, 0>(S, P, T, st);
 }
 
 
@@ -229,8 +238,8 @@ template void launch_spin_phase<float>(const SysView<float> &, const PotConst &,
                                        const SpinPhaseArgs &, int, hipStream_t,
                                        const SysView<float> *);
 template void launch_spin_tail<double>(const SysView<double> &, const PotConst &,
-                                       const TailArgs &, int, hipStream_t);
+                                       const TailArgs &, hipStream_t);
 template void launch_spin_tail<float>(const SysView<float> &, const PotConst &, const TailArgs &,
-                                      int, hipStream_t);
+                                      hipStream_t);
 
 }  // namespace sl

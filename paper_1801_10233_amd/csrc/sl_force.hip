@@ -26,10 +26,12 @@ template void launch_eam_density<double>(const SysView<double> &, const PotConst
 template void launch_eam_density<float>(const SysView<float> &, const PotConst &, hipStream_t);
 
 
-template <typename real, int MODE, int LANES, int MLP>
-__global__ __launch_bounds__(kBlock, kForceWaves) void k_force(SysView<real> S, PotConst P, ForceArgs A) {
-  __shared__ double red[kBlock / 64][8];
-  __shared__ double redm[kBlock / 64][3];
+template <typename real, int MODE, int WAVES, int MLP>
+__global__ __launch_bounds__(team_block(WAVES), kForceWaves) void k_force(SysView<real> S, PotConst P, ForceArgs A) {
+  constexpr int kWv = team_block(WAVES) / 64, kAtoms = team_atoms(WAVES);
+  __shared__ double red[kWv][8];
+  __shared__ double redm[kWv][3];
+  __shared__ ForceTeam<real, WAVES> team[WAVES > 1 ? kWv / WAVES : 1];
   // With a tile table (A.tiles) block b takes the atom range the host gave
   // it: XCD b % 8 holds the same spatial slab of every colour class, so its
   // L2 serves the neighbour gathers of all classes of that slab. Without
@@ -37,24 +39,23 @@ __global__ __launch_bounds__(kBlock, kForceWaves) void k_force(SysView<real> S, 
   // colour classes may hold a few atoms scattered over the whole box
   // (repairs), whose gathers miss the caches; starting them first hides
   // their latency behind the bulk instead of leaving them as the tail.
-  int tile, i, l;
+  const int t = wave_id() / WAVES, w = wave_id() % WAVES;
+  const int a = 64 * t + (int)(threadIdx.x & 63);  // atom of the block
+  int tile, i;
   bool valid;
   if (A.tiles) {
     const int2 rg = A.tiles[blockIdx.x];
     tile = blockIdx.x;
-    i = rg.x + (int)threadIdx.x / LANES;
-    l = threadIdx.x & (LANES - 1);
+    i = rg.x + a;
     valid = i < rg.y;
   } else {
     tile = gridDim.x - 1 - xcd_tile(blockIdx.x, gridDim.x);
-    const int t = tile * kBlock + threadIdx.x;
-    l = t & (LANES - 1);
-    i = t / LANES;
+    i = tile * kAtoms + a;
     valid = i < S.n;
   }
   double e[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   double dm = 0.0, vm = 0.0, wm = kInf;
-  force_atom<real, MODE, LANES, MLP>(S, P, A, i, valid, l, e, dm, vm, wm);
+  force_atom<real, MODE, WAVES, MLP>(S, P, A, i, valid, w, team + t, e, dm, vm, wm);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (MODE & kModeEnergy) {
 #pragma unroll
@@ -64,15 +65,15 @@ __global__ __launch_bounds__(kBlock, kForceWaves) void k_force(SysView<real> S, 
     }
   }
   if (MODE & (kModeFinal | kModeNext)) {
-    const double a = wave_max(dm), b = wave_max(vm), c = wave_min(wm);
-    if (lane == 0) { redm[wv][0] = a; redm[wv][1] = b; redm[wv][2] = c; }
+    const double xd = wave_max(dm), xv = wave_max(vm), xw = wave_min(wm);
+    if (lane == 0) { redm[wv][0] = xd; redm[wv][1] = xv; redm[wv][2] = xw; }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     if (MODE & kModeEnergy) {
       for (int c = 0; c < 8; ++c) {
         double x = 0.0;
-        for (int w = 0; w < kBlock / 64; ++w) x += red[w][c];
+        for (int q = 0; q < kWv; ++q) x += red[q][c];
         A.partial[(size_t)tile * 8 + c] = x;
       }
     }
@@ -81,15 +82,15 @@ __global__ __launch_bounds__(kBlock, kForceWaves) void k_force(SysView<real> S, 
     // counter, cost ~50 us per launch at 1688 blocks: they serialise across
     // the XCDs.)
     if (MODE & (kModeFinal | kModeNext)) {
-      double a = 0.0, b = 0.0, c = kInf;
-      for (int w = 0; w < kBlock / 64; ++w) {
-        a = fmax(a, redm[w][0]);
-        b = fmax(b, redm[w][1]);
-        c = fmin(c, redm[w][2]);
+      double xd = 0.0, xv = 0.0, xw = kInf;
+      for (int q = 0; q < kWv; ++q) {
+        xd = fmax(xd, redm[q][0]);
+        xv = fmax(xv, redm[q][1]);
+        xw = fmin(xw, redm[q][2]);
       }
-      A.pred[(size_t)tile * 3 + 0] = a;
-      A.pred[(size_t)tile * 3 + 1] = b;
-      A.pred[(size_t)tile * 3 + 2] = c;
+      A.pred[(size_t)tile * 3 + 0] = xd;
+      A.pred[(size_t)tile * 3 + 1] = xv;
+      A.pred[(size_t)tile * 3 + 2] = xw;
     }
   }
 }
@@ -133,14 +134,13 @@ void launch_pred_reduce(const double *pred, int nb, int *err, double *host_out, 
 }
 
 
-template <typename real, int LANES, int MLP>
+template <typename real, int WAVES, int MLP>
 static void force_lanes2(const SysView<real> &S, const PotConst &P, const ForceArgs &A,
                          hipStream_t st) {
-  const long threads = (long)S.n * LANES;
-  const int nb = A.tiles ? A.ntiles : (int)((threads + kBlock - 1) / kBlock);
+  const int nb = A.tiles ? A.ntiles : force_blocks(S.n, WAVES);
   switch (A.mode) {
 #define SL_FORCE_CASE(m) \
-  case m: hipLaunchKernelGGL((k_force<real, m, LANES, MLP>), dim3(nb), dim3(kBlock), 0, st, S, P, A); break;
+  case m: hipLaunchKernelGGL((k_force<real, m, WAVES, MLP>), dim3(nb), dim3(team_block(WAVES)), 0, st, S, P, A); break;
     SL_FORCE_CASE(1) SL_FORCE_CASE(2) SL_FORCE_CASE(3) SL_FORCE_CASE(4)
     SL_FORCE_CASE(5) SL_FORCE_CASE(6) SL_FORCE_CASE(7)
 #undef SL_FORCE_CASE
@@ -148,39 +148,39 @@ static void force_lanes2(const SysView<real> &S, const PotConst &P, const ForceA
   }
 }
 
-template <typename real, int LANES>
+template <typename real, int WAVES>
 static void force_lanes(const SysView<real> &S, const PotConst &P, const ForceArgs &A,
                         hipStream_t st) {
-  if (P.soc_on && P.eam_on) force_lanes2<real, LANES, 12>(S, P, A, st);
-  else if (P.eam_on) force_lanes2<real, LANES, 8>(S, P, A, st);
-  else if (P.soc_on) force_lanes2<real, LANES, 4>(S, P, A, st);
-  else if (sizeof(real) == 4 && S.spl.t) force_lanes2<real, LANES, (sizeof(real) == 4 ? 2 : 0)>(S, P, A, st);
-  else if (sizeof(real) == 4 && S.tab) force_lanes2<real, LANES, (sizeof(real) == 4 ? 1 : 0)>(S, P, A, st);
-  else force_lanes2<real, LANES, 0>(S, P, A, st);
+  if (P.soc_on && P.eam_on) force_lanes2<real, WAVES, 12>(S, P, A, st);
+  else if (P.eam_on) force_lanes2<real, WAVES, 8>(S, P, A, st);
+  else if (P.soc_on) force_lanes2<real, WAVES, 4>(S, P, A, st);
+  else if (sizeof(real) == 4 && S.spl.t) force_lanes2<real, WAVES, (sizeof(real) == 4 ? 2 : 0)>(S, P, A, st);
+  else if (sizeof(real) == 4 && S.tab) force_lanes2<real, WAVES, (sizeof(real) == 4 ? 1 : 0)>(S, P, A, st);
+  else force_lanes2<real, WAVES, 0>(S, P, A, st);
 }
 
 // Pair pass of the split force: the spin-independent terms of every atom
 // into A.fp (MODE is 0 or kModeEnergy: with it the pair energy is stored
 // too). No reductions, kicks or predictor: the spin pass does those.
-template <typename real, int MODE, int LANES, int MLP>
+template <typename real, int MODE, int WAVES, int MLP>
 __global__ __launch_bounds__(kBlock, kForceWaves) void k_pair(SysView<real> S, PotConst P, ForceArgs A) {
+  __shared__ ForceTeam<real, WAVES> team[WAVES > 1 ? kBlock / 64 / WAVES : 1];
   const int tile = gridDim.x - 1 - xcd_tile(blockIdx.x, gridDim.x);
-  const int t = tile * kBlock + threadIdx.x;
-  const int l = t & (LANES - 1);
-  const int i = t / LANES;
+  const int t = wave_id() / WAVES, w = wave_id() % WAVES;
+  const int i = tile * team_atoms(WAVES) + 64 * t + (int)(threadIdx.x & 63);
   double e[8];
   double dm = 0.0, vm = 0.0, wm = kInf;
-  force_atom<real, MODE, LANES, MLP | 16>(S, P, A, i, i < S.n, l, e, dm, vm, wm);
+  force_atom<real, MODE, WAVES, MLP | 16>(S, P, A, i, i < S.n, w, team + t, e, dm, vm, wm);
 }
 
-template <typename real, int LANES, int MLP>
+template <typename real, int WAVES, int MLP>
 static void pair_lanes2(const SysView<real> &S, const PotConst &P, const ForceArgs &A,
                         bool energy, hipStream_t st) {
-  const int nb = (int)(((long)S.n * LANES + kBlock - 1) / kBlock);
+  const int nb = force_blocks(S.n, WAVES);
   if (energy)
-    hipLaunchKernelGGL((k_pair<real, kModeEnergy, LANES, MLP>), dim3(nb), dim3(kBlock), 0, st, S, P, A);
+    hipLaunchKernelGGL((k_pair<real, kModeEnergy, WAVES, MLP>), dim3(nb), dim3(kBlock), 0, st, S, P, A);
   else
-    hipLaunchKernelGGL((k_pair<real, 0, LANES, MLP>), dim3(nb), dim3(kBlock), 0, st, S, P, A);
+    hipLaunchKernelGGL((k_pair<real, 0, WAVES, MLP>), dim3(nb), dim3(kBlock), 0, st, S, P, A);
 }
 
 template <typename real>
@@ -219,7 +219,8 @@ template void launch_force_spin<float>(const SysView<float> &, const PotConst &,
                                        int, hipStream_t);
 
 // Blocks needed by a force launch (rows of the partial-sum buffer).
-int force_blocks(int n, int lanes) { return (int)(((long)n * lanes + kBlock - 1) / kBlock); }
+int force_block_atoms(int waves) { return team_atoms(waves); }
+int force_blocks(int n, int waves) { return (n + team_atoms(waves) - 1) / team_atoms(waves); }
 
 template <typename real>
 void launch_force(const SysView<real> &S, const PotConst &P, const ForceArgs &A, int lanes,

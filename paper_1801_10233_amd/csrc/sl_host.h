@@ -72,7 +72,10 @@ struct sl_system {
   double skin = 0.3;
   int max_nbr = 80, max_spin = 32;
   int Kbase = 0;                        // palette of the last full colouring
-  int spin_lanes = 2, force_lanes = 1;  // lanes per atom (tuning only)
+  // lanes per atom (tuning only); while a field of the tuning is left at its
+  // default the launches take the shape of the rules below instead
+  int spin_lanes = 2, force_lanes = 1;
+  bool spin_auto = true, jc_auto = true;
   // Runs of consecutive classes of at most this many atoms share one
   // single-workgroup launch (-1: never). Meant for the few-atom classes a
   // colour repair adds; at 500 atoms per class (2000-atom lattice) separate
@@ -197,6 +200,41 @@ inline int fail(sl_system *S, int code, const std::string &msg) {
     if (rc_) return rc_;  \
   } while (0)
 
+// Default launch shape (microseconds per launch on MI355X, FP64 unless stated).
+// Spin launch of a class of m atoms: 4 wavefronts per 64 atoms, one round of the
+// row: 500 atoms 4.2, 16 384 atoms 4.2, 32 000 atoms 5.1 (1 lane per atom: 6.9,
+// 6.9, 7.9; 2: 4.8, 5.0, 5.9); a class of up to kSpinSpread atoms leaves most
+// compute units idle that way and takes 8 lanes per atom of fewer atoms
+// (500 atoms: 3.6); beyond kSpinFull atoms with the exchange cache in FP64 the
+// device is full and one lane per atom is as fast (108 000 atoms: 9.1, 4 lanes
+// 9.4; FP32 6.8 and 6.4).
+constexpr int kSpinSpread = 3000, kSpinFull = 70000;
+inline bool jcache_on(const sl_system *S);
+inline int spin_lanes_for(const sl_system *S, int m) {
+  if (!S->spin_auto) return S->spin_lanes;
+  if (m <= kSpinSpread) return 8;
+  return m > kSpinFull && S->prec == SL_FP64 && jcache_on(S) ? 1 : 4;
+}
+// Force launch: wavefronts per 64 atoms. 1 / 4 / 8 wavefronts: 8192 atoms 23 /
+// 12.1 / 11.9, 27 648 atoms 23.5 / 15.0 / 15.9, 65 536 atoms 24.3 / 20.7 / 25.2,
+// 128 000 atoms 35.4 / 34.4 / 43.8, 432 000 atoms 85 / 94 / 129. A tuned shape
+// (1 or 2 lanes, or what the caller sets) is the least that the launch takes.
+// The split force takes 1 or 2.
+constexpr int kForceSpread = 12000, kForceFull = 120000;
+inline int force_lanes_for(const sl_system *S) {
+  if (S->overlap > 0) return S->force_lanes;
+  return std::max(S->force_lanes, S->n <= kForceSpread ? 8 : (S->n <= kForceFull ? 4 : 1));
+}
+// Exchange cache: on for FP32; in FP64 where what it takes off the spin launches
+// (0.4 us each, 0.7 us with the bath; 4K - 4 launches a step) outweighs its own
+// launch (7 us up to 65 536 atoms, 10.5 us at 128 000), for large classes
+// (110 592 atoms: 6.9 -> 5.6 us; 432 000 atoms, one lane: 14.3 -> 9.1), and on a
+// frozen lattice, whose coefficients never change.
+inline bool jcache_on(const sl_system *S) {
+  if (!S->jc_auto || S->prec == SL_FP32) return S->jcache > 0;
+  return S->prm.frozen || S->pc.langevin || S->K >= 7 || S->n > 4 * kSpinFull;
+}
+
 template <typename T>
 inline hipError_t dalloc(T **p, size_t count) {
   *p = nullptr;
@@ -235,7 +273,7 @@ inline SysView<real> view(sl_system *S, int posbuf) {
   v.id = A.id;
   v.tab = nullptr;
   v.spl = SplineView{};
-  const bool jc_use = (!S->mlp || S->mlp_mode == SL_MLP_SPLINE) && S->jcache > 0 && !S->pc.soc_on;
+  const bool jc_use = (!S->mlp || S->mlp_mode == SL_MLP_SPLINE) && jcache_on(S) && !S->pc.soc_on;
   v.jc = (jc_use && S->jc_ok[posbuf]) ? (const real *)S->jc[posbuf] : nullptr;
   v.eam = S->pc.eam_on ? S->eam : nullptr;
   v.held = 0;

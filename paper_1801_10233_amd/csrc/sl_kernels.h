@@ -6,14 +6,15 @@
 namespace sl {
 
 // --- per-step kernels (sl_dyn.hip) ---
-// `lanes` (1, 2, 4 or 8) consecutive lanes cooperate on one atom.
+// `lanes` (1, 2, 4 or 8) lanes cooperate on one atom (see TeamShape; in the
+// force launch each in its own wavefront of a workgroup).
 // With S2 (the same system at its other position buffer) the launch is the
 // dual update: A.nrep == 2, the first update's field at S, the second's at S2.
 template <typename real>
 void launch_spin_phase(const SysView<real> &S, const PotConst &P, const SpinPhaseArgs &A,
                        int lanes, hipStream_t st, const SysView<real> *S2 = nullptr);
 template <typename real>
-void launch_spin_tail(const SysView<real> &S, const PotConst &P, const TailArgs &T, int lanes,
+void launch_spin_tail(const SysView<real> &S, const PotConst &P, const TailArgs &T,
                       hipStream_t st);
 template <typename real>
 void launch_force(const SysView<real> &S, const PotConst &P, const ForceArgs &A, int lanes,
@@ -28,6 +29,7 @@ void launch_pair(const SysView<real> &S, const PotConst &P, const ForceArgs &A, 
 template <typename real>
 void launch_force_spin(const SysView<real> &S, const PotConst &P, const ForceArgs &A, int lanes,
                        hipStream_t st);
+int force_block_atoms(int lanes);  // atoms of one block of a force launch
 int force_blocks(int n, int lanes);
 // Joins the per-block rebuild predictor terms (pred[nb][3]) of a force launch
 // into the pinned host slot host_out, with the error word and the marker.
@@ -39,10 +41,11 @@ void launch_batch_run(RepDesc<real> *D, int R, int lanes, int variant, hipStream
 template <typename real>
 void launch_eam_density(const SysView<real> &S, const PotConst &P, hipStream_t st);
 // Exchange-coefficient cache: J(r_ij) per spin-segment entry (ELL layout);
-// tiles (or null): atom range of each 256-thread block.
+// tiles (or null): atom range of each 256-thread block; max_slots: the
+// largest spin segment.
 template <typename real>
 void launch_jcache(const SysView<real> &S, const PotConst &P, real *out, double rs2,
-                   const int2 *tiles, int ntiles, hipStream_t st);
+                   const int2 *tiles, int ntiles, int max_slots, hipStream_t st);
 // Phase-batched mode: one colour phase of every replica (max_class = the
 // largest class of any replica) and one force pass of every replica (max_n =
 // the largest replica; mode kModeNext at the call start, kModeFinal with or

@@ -2,7 +2,7 @@
 // single-system kernels (sl_dyn.hip, sl_force.hip) and the batched kernels
 // (sl_batch.hip): the spin update of one atom, the force gather of one atom
 // with the kicks and the drift, and the embedded-atom density of one atom.
-// One thread (or LANES lanes) per atom; per-atom data in structure-of-arrays
+// One lane per atom, one or several wavefronts per 64 atoms; per-atom data in structure-of-arrays
 // form so the own-atom loads and stores of a wavefront are coalesced, and
 // neighbour data gathered through L2 (atoms are sorted by cell inside a
 // colour class).
@@ -16,6 +16,9 @@
 #ifndef SL_SPIN_FIRST
 #define SL_SPIN_FIRST 7  // slots of the first round with one lane per atom
 #endif
+#ifndef SL_SPIN_TWO
+#define SL_SPIN_TWO 8    // slots per round with two wavefronts per 64 atoms
+#endif
 #ifndef SL_SPIN_LATER
 #define SL_SPIN_LATER 8  // slots of each later round with one lane per atom
 #endif
@@ -26,8 +29,12 @@
 #ifndef SL_FORCE_CHUNK1
 #define SL_FORCE_CHUNK1 SL_FORCE_CHUNK  // the same in the rest of the row (positions only)
 #endif
-
 namespace sl {
+
+// Workgroup of the per-atom launches with WAVES wavefronts per team of 64 atoms:
+// 256 threads, 512 with 8 wavefronts; its teams and its atoms.
+constexpr int team_block(int waves) { return waves == 8 ? 512 : kBlock; }
+constexpr int team_atoms(int waves) { return team_block(waves) / waves; }
 
 // Cayley rotation of Sec. 3 about w with step h, in place (an exact
 // rotation by 2 atan(h|w|/2); |s| is kept in exact arithmetic).
@@ -56,19 +63,44 @@ __device__ __forceinline__ void cayley_rot(real &sx, real &sy, real &sz, real wx
 // class in one launch (nothing else changes in between); the exchange sum
 // does not depend on s_i, so it is gathered once.
 // One spin update (or nrep successive ones) of atom i, shared by the
-// per-class launch and the fused small-class launch. All LANES lanes of an
-// atom must call it (cross-lane shuffles); `valid` masks the tail.
+// per-class launch and the fused small-class launch. All threads of the
+// workgroup must call it (with WAVES > 1 it holds a barrier); `valid` masks the
+// tail. The team's LDS may be used again after the caller's next barrier.
+// A spin update takes 64 / SUB consecutive atoms on WAVES wavefronts of a
+// workgroup (a "team"): LANES = WAVES * SUB lanes share an atom, lane group u
+// (the SUB runs of 64 / SUB lanes of wavefront 0, then of wavefront 1, ...)
+// gathers the slots u, u + LANES, ... of every row; the partial sums meet by
+// shuffles and in LDS, and the first lane group rotates. The lanes of a group
+// read the same slot of consecutive atoms, one run or two of memory (with
+// consecutive lanes sharing an atom a gather touched LANES times as many runs),
+// and the other wavefronts draw the noise of the updates while the gathers are
+// in flight. 27 648 atoms with the bath, FP64, microseconds per class launch:
+// 6.5 with 8 consecutive lanes per atom, 5.4 with 4 wavefronts, 4.7 with the
+// exchange cache. A class of a few thousand atoms is spread over more compute
+// units with SUB > 1 (500 atoms without the bath: 3.6 us with 8 lanes of one
+// wavefront per atom, 4.2 with 8 wavefronts on 64 atoms).
+template <int LANES, bool LANGEVIN>
+struct TeamShape {
+  static constexpr int sub = LANES == 8 ? (LANGEVIN ? 4 : 8) : 1;
+  static constexpr int waves = LANES / sub;
+  static constexpr int atoms = 64 / sub;
+};
+template <typename real, int WAVES>
+struct SpinTeam {
+  real sum[WAVES > 1 ? WAVES - 1 : 1][6][64];
+  real g[kMaxRep][3][64];
+};
+
 // Neighbour slots one lane gathers per round of the spin phase (value: the
-// first round, later: each later one). With one lane per atom a first round
-// of 7 and a second of 8 cover the 14 entries of a bcc spin segment at the
-// exchange cutoff and the 15 or 16 that thermal motion puts into some rows
+// first round, later: each later one). With one lane per atom a first
+// round of 7 and a second of 8 cover the 14 entries of a bcc spin segment at
+// the exchange cutoff and the 15 or 16 that thermal motion puts into some rows
 // (measured at 432 000 atoms: 7 + 7, 7 + 9, 6 + 8, 6 + 10, 5 + 9 and 8 + 8
-// were slower); with two lanes the same per lane (the batched replicas' step
-// 4 % faster than with rounds of 8).
+// were slower); with more lanes one round covers 16.
 template <int LANES, int MLP = 0>
 struct SpinChunk {
-  static constexpr int value = LANES >= 8 ? 2 : (LANES >= 4 ? 4 : (LANES == 2 ? 7 : SL_SPIN_FIRST));
-  static constexpr int later = LANES == 1 ? SL_SPIN_LATER : (LANES == 2 ? 8 : value);
+  static constexpr int value = LANES >= 8 ? 2 : (LANES >= 4 ? 4 : (LANES == 2 ? SL_SPIN_TWO : SL_SPIN_FIRST));
+  static constexpr int later = LANES == 1 ? SL_SPIN_LATER : value;
 };
 // The spin-orbit variant holds a field vector per slot besides the
 // coefficient, and its dual form a second one: 4 slots per round keep it
@@ -89,9 +121,11 @@ struct SpinChunk<LANES, 4> {
 // same list, the other position buffer) for the second; nrep must be 2.
 template <typename real, bool LANGEVIN, bool ANISO, int LANES, int MLP, bool DUAL = false>
 __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotConst &P, int i,
-                                            bool valid, int l, int nrep, const int64_t *step,
-                                            const int *sub, double hd, double ampd,
-                                            uint64_t seed, uint32_t replica, double rs2,
+                                            bool valid, int w,
+                                            SpinTeam<real, TeamShape<LANES, LANGEVIN>::waves> *team,
+                                            int nrep, const int64_t *step, const int *sub,
+                                            double hd, double ampd, uint64_t seed,
+                                            uint32_t replica, double rs2,
                                             const SysView<real> *S2 = nullptr,
                                             bool keep0 = false) {
   // Latency is what bounds this update, so every load that does not depend
@@ -102,6 +136,11 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
   // gathers of positions and spins follow in one batch, and the Philox
   // noise of the first update is computed while they are in flight.
   constexpr int CH0 = SpinChunk<LANES, MLP>::value, CH1 = SpinChunk<LANES, MLP>::later;
+  constexpr int WAVES = TeamShape<LANES, LANGEVIN>::waves, SUB = TeamShape<LANES, LANGEVIN>::sub;
+  constexpr int kAtoms = 64 / SUB;
+  const int sub_l = SUB > 1 ? (int)(threadIdx.x & 63) / kAtoms : 0;
+  const int lane = threadIdx.x & (kAtoms - 1);
+  const int u0 = w * SUB + sub_l;  // lane group
   real ax = 0, ay = 0, az = 0;
   real bx = 0, by = 0, bz = 0;  // DUAL: field at the positions of S2
   real sx = 0, sy = 0, sz = 0;
@@ -154,8 +193,19 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
         }
         qx[c] = S.sx[jj[c]]; qy[c] = S.sy[jj[c]]; qz[c] = S.sz[jj[c]];
       }
-      if (LANGEVIN && first && l == 0)
-        gauss3(seed, aid, step[0], replica, sub[0], g0);
+      if (LANGEVIN && first) {
+        if (WAVES == 1) {
+          gauss3(seed, aid, step[0], replica, sub[0], g0);
+        } else {  // rep r on a lane group of the last wavefronts
+          for (int r = (WAVES - 1 - w) * SUB + sub_l; r < nrep; r += LANES) {
+            real g[3];
+            gauss3(seed, aid, step[r], replica, sub[r], g);
+            team->g[r][0][lane] = g[0];
+            team->g[r][1][lane] = g[1];
+            team->g[r][2][lane] = g[2];
+          }
+        }
+      }
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const bool in = base + LANES * c < ns;
@@ -232,12 +282,12 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
         }
       }
     };
-    gather_round(std::integral_constant<int, CH0>{}, l, true);
-    for (int base = l + LANES * CH0; base < ns; base += LANES * CH1)
+    gather_round(std::integral_constant<int, CH0>{}, u0, true);
+    for (int base = u0 + LANES * CH0; base < ns; base += LANES * CH1)
       gather_round(std::integral_constant<int, CH1>{}, base, false);
   }
 #pragma unroll
-  for (int o = LANES / 2; o > 0; o >>= 1) {
+  for (int o = kAtoms; o < 64; o <<= 1) {
     ax += __shfl_xor(ax, o, 64);
     ay += __shfl_xor(ay, o, 64);
     az += __shfl_xor(az, o, 64);
@@ -247,7 +297,33 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
       bz += __shfl_xor(bz, o, 64);
     }
   }
-  if (!valid || l != 0) return;
+  if constexpr (WAVES > 1) {
+    if (w > 0) {
+      team->sum[w - 1][0][lane] = ax;
+      team->sum[w - 1][1][lane] = ay;
+      team->sum[w - 1][2][lane] = az;
+      if (DUAL) {
+        team->sum[w - 1][3][lane] = bx;
+        team->sum[w - 1][4][lane] = by;
+        team->sum[w - 1][5][lane] = bz;
+      }
+    }
+    __syncthreads();
+    if (w == 0) {
+#pragma unroll
+      for (int q = 0; q < WAVES - 1; ++q) {
+        ax += team->sum[q][0][lane];
+        ay += team->sum[q][1][lane];
+        az += team->sum[q][2][lane];
+        if (DUAL) {
+          bx += team->sum[q][3][lane];
+          by += team->sum[q][4][lane];
+          bz += team->sum[q][5][lane];
+        }
+      }
+    }
+  }
+  if (!valid || u0 != 0) return;
   const real h = (real)hd;
   const real ih = (real)(1.0 / kHbar);
   for (int rep = 0; rep < nrep; ++rep) {
@@ -286,7 +362,13 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
     real wx = ex * ih, wy = ey * ih, wz = ez * ih;
     if (LANGEVIN) {
       real g[3] = {g0[0], g0[1], g0[2]};
-      if (rep > 0) gauss3(seed, aid, step[rep], replica, sub[rep], g);
+      if (WAVES > 1) {
+        g[0] = team->g[rep][0][lane];
+        g[1] = team->g[rep][1][lane];
+        g[2] = team->g[rep][2][lane];
+      } else if (rep > 0) {
+        gauss3(seed, aid, step[rep], replica, sub[rep], g);
+      }
       const real lam = (real)P.lam, amp = (real)ampd, f = (real)P.lamfac;
       const real cx = sy * wz - sz * wy, cy = sz * wx - sx * wz, cz = sx * wy - sy * wx;
       wx = (wx + amp * g[0] + lam * cx) * f;
@@ -329,8 +411,10 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
 // after the launch hands them, with the sticky error word, to pinned host
 // memory.
 // Per-atom part of the force launch (shared with the batched persistent
-// kernel): force on atom i over its list row, split over LANES lanes, then on
-// the first lane the kicks, the drift into the other position buffer, the
+// kernel): force on atom i over its list row, split over the WAVES wavefronts
+// of a team of 64 atoms (as in the spin update: wavefront w takes the slots w,
+// w + WAVES, ..., partial sums through LDS), then on the first wavefront the
+// kicks, the drift into the other position buffer, the
 // energy terms e[8] = (kin, pair, exchange, Zeeman, aniso, Mx, My, Mz) and
 // the rebuild predictor terms |r - r_build| and |v|.
 // Variant MLP of the force gather: MLP & 7 selects the pair terms (0 analytic,
@@ -344,10 +428,17 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
 // the spin pass: the spin-dependent terms over the spin segment only, plus
 // the stored pair part, then the kicks, drift, energies and predictor as in
 // the fused form.
-template <typename real, int MODE, int LANES, int MLP>
+template <typename real, int WAVES>
+struct ForceTeam {
+  real f[WAVES > 1 ? WAVES - 1 : 1][5][64];
+  double wm[WAVES > 1 ? WAVES - 1 : 1][64];
+};
+
+template <typename real, int MODE, int WAVES, int MLP>
 __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotConst &P,
-                                           const ForceArgs &A, int i, bool valid, int l,
-                                           double e[8], double &dm, double &vm, double &wm) {
+                                           const ForceArgs &A, int i, bool valid, int w,
+                                           ForceTeam<real, WAVES> *team, double e[8], double &dm,
+                                           double &vm, double &wm) {
   constexpr int kV = MLP & 7;
   constexpr bool kEam = (MLP & 8) != 0;
   constexpr bool kPairPass = (MLP & 16) != 0, kSpinPass = (MLP & 32) != 0;
@@ -358,6 +449,16 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
   real ep = 0, ee = 0;
   double rix = 0, riy = 0, riz = 0;
   real six = 0, siy = 0, siz = 0;
+  // with several wavefronts per team the mass, velocity and build position of
+  // the closing part are loaded with the atom's other data, off the end of the
+  // chain
+  constexpr bool kEarly = WAVES > 1 && !kPairPass && (MODE & (kModeFinal | kModeNext)) != 0;
+  double em = 0, evx = 0, evy = 0, evz = 0, ebx = 0, eby = 0, ebz = 0;
+  if (kEarly && valid && w == 0) {
+    em = A.mass[i];
+    evx = A.vx[i]; evy = A.vy[i]; evz = A.vz[i];
+    ebx = A.bx[i]; eby = A.by[i]; ebz = A.bz[i];
+  }
   if (valid) {
     rix = S.rx[i]; riy = S.ry[i]; riz = S.rz[i];
     const int is = i < S.held ? S.n + i : i;
@@ -367,7 +468,7 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
     // the variant may serve replicas without the embedded-atom terms
     const bool eam = kEam && !kSpinPass && P.eam_on;
     const real fpi = eam ? (real)S.eam[i] : (real)0;
-    if (eam && (MODE & kModeEnergy) && l == 0) ep += (real)S.eam[ld + i];
+    if (eam && (MODE & kModeEnergy) && w == 0) ep += (real)S.eam[ld + i];
     // spin-segment slots holding a pair of one colour class are watched
     const unsigned long long wmk =
         (!kPairPass && (MODE & (kModeFinal | kModeNext)) && A.wmask) ? A.wmask[i] : 0ull;
@@ -385,11 +486,11 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
       constexpr int seg = decltype(segc)::value;
       constexpr int CHF = decltype(chunkc)::value;
       const int beg = seg == 0 ? 0 : ns, end = seg == 0 ? ns : na;
-      for (int base = beg + l; base < end; base += LANES * CHF) {
+      for (int base = beg + w; base < end; base += WAVES * CHF) {
         int jj[CHF];
 #pragma unroll
         for (int c = 0; c < CHF; ++c) {
-          const int k = base + LANES * c;
+          const int k = base + WAVES * c;
           jj[c] = k < end ? S.nbr[(size_t)k * ld + i] : i;
         }
         double px[CHF], py[CHF], pz[CHF];
@@ -412,18 +513,18 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
         if (kV == 1) {
 #pragma unroll
           for (int c = 0; c < CHF; ++c) {
-            const int k = base + LANES * c;
+            const int k = base + WAVES * c;
             tt[c] = k < end ? S.tab[(size_t)k * ld + i] : make_float4(0.f, 0.f, 0.f, 0.f);
           }
         }
 #pragma unroll
         for (int c = 0; c < CHF; ++c) {
-          const bool use = base + LANES * c < end;
+          const bool use = base + WAVES * c < end;
           const double dxd = min_image(rix - px[c], S.L[0], S.invL[0]);
           const double dyd = min_image(riy - py[c], S.L[1], S.invL[1]);
           const double dzd = min_image(riz - pz[c], S.L[2], S.invL[2]);
           const double r2d = use ? dxd * dxd + dyd * dyd + dzd * dzd : 1.0;
-          if (!kPairPass && seg == 0 && use && ((wmk >> (base + LANES * c)) & 1ull)) wm = fmin(wm, r2d);
+          if (!kPairPass && seg == 0 && use && ((wmk >> (base + WAVES * c)) & 1ull)) wm = fmin(wm, r2d);
           const real dx = (real)dxd, dy = (real)dyd, dz = (real)dzd;
           const double rinvd = rsqrt_nr(r2d);
           const real r = (real)(r2d * rinvd), rinv = (real)rinvd;
@@ -489,18 +590,35 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
     if (!kSpinPass)
       segment(std::integral_constant<int, 1>{}, std::integral_constant<int, SL_FORCE_CHUNK1>{});
   }
+  if constexpr (WAVES > 1) {
+    const int lane = threadIdx.x & 63;
+    if (w > 0) {
+      team->f[w - 1][0][lane] = fx;
+      team->f[w - 1][1][lane] = fy;
+      team->f[w - 1][2][lane] = fz;
+      if (MODE & kModeEnergy) {
+        team->f[w - 1][3][lane] = ep;
+        team->f[w - 1][4][lane] = ee;
+      }
+      if (!kPairPass) team->wm[w - 1][lane] = wm;
+    }
+    __syncthreads();
+    if (w == 0) {
 #pragma unroll
-  for (int o = LANES / 2; o > 0; o >>= 1) {
-    fx += __shfl_xor(fx, o, 64);
-    fy += __shfl_xor(fy, o, 64);
-    fz += __shfl_xor(fz, o, 64);
-    if (MODE & kModeEnergy) {
-      ep += __shfl_xor(ep, o, 64);
-      ee += __shfl_xor(ee, o, 64);
+      for (int q = 0; q < WAVES - 1; ++q) {
+        fx += team->f[q][0][lane];
+        fy += team->f[q][1][lane];
+        fz += team->f[q][2][lane];
+        if (MODE & kModeEnergy) {
+          ep += team->f[q][3][lane];
+          ee += team->f[q][4][lane];
+        }
+        if (!kPairPass) wm = fmin(wm, team->wm[q][lane]);
+      }
     }
   }
   if (kPairPass) {
-    if (valid && l == 0) {
+    if (valid && w == 0) {
       const int ld = S.ld;
       A.fp[i] = (double)fx;
       A.fp[ld + i] = (double)fy;
@@ -509,19 +627,19 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
     }
     return;
   }
-  if (kSpinPass && valid && l == 0) {
+  if (kSpinPass && valid && w == 0) {
     const int ld = S.ld;
     fx += (real)A.fp[i];
     fy += (real)A.fp[ld + i];
     fz += (real)A.fp[2 * ld + i];
     if (MODE & kModeEnergy) ep += (real)A.fp[3 * ld + i];
   }
-  if (valid && l == 0) {
+  if (valid && w == 0) {
     if (!isfinite((double)fx) || !isfinite((double)fy) || !isfinite((double)fz))
       atomicOr(A.err, kErrNonFinite);
     if (MODE & (kModeFinal | kModeNext)) {
-      const double m = A.mass[i];
-      double vx = A.vx[i], vy = A.vy[i], vz = A.vz[i];
+      const double m = kEarly ? em : A.mass[i];
+      double vx = kEarly ? evx : A.vx[i], vy = kEarly ? evy : A.vy[i], vz = kEarly ? evz : A.vz[i];
       const double kx = 0.5 * A.dt * (double)fx / m * A.ftm2v;
       const double ky = 0.5 * A.dt * (double)fy / m * A.ftm2v;
       const double kz = 0.5 * A.dt * (double)fz / m * A.ftm2v;
@@ -529,7 +647,8 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
       if (MODE & kModeEnergy) e[0] = 0.5 * m * (vx * vx + vy * vy + vz * vz) * kMvv2e;
       // rebuild predictor at this boundary
       {
-        const double bx = rix - A.bx[i], by = riy - A.by[i], bz = riz - A.bz[i];
+        const double bx = rix - (kEarly ? ebx : A.bx[i]), by = riy - (kEarly ? eby : A.by[i]),
+                     bz = riz - (kEarly ? ebz : A.bz[i]);
         dm = sqrt(bx * bx + by * by + bz * bz);
         vm = sqrt(vx * vx + vy * vy + vz * vz);
       }

@@ -228,7 +228,7 @@ int ensure_table(sl_system *S, int b) {
 // per drift; the analytic potential only).
 template <typename real>
 int ensure_jcache(sl_system *S, int b) {
-  if ((S->mlp && S->mlp_mode != SL_MLP_SPLINE) || S->jcache <= 0 || S->pc.soc_on || S->jc_ok[b])
+  if ((S->mlp && S->mlp_mode != SL_MLP_SPLINE) || !jcache_on(S) || S->pc.soc_on || S->jc_ok[b])
     return SL_OK;
   if (!S->jc[b]) {
     real *p = nullptr;
@@ -240,7 +240,8 @@ int ensure_jcache(sl_system *S, int b) {
     ProfScope ps(S, 3, (double)S->n);
     CHK(force_tiles(S));
     launch_jcache<real>(v, S->pc, (real *)S->jc[b], S->pot.ex_rc * S->pot.ex_rc,
-                        S->jtile_n > 0 ? S->jtile : nullptr, S->jtile_n, S->st);
+                        S->jtile_n > 0 ? S->jtile : nullptr, S->jtile_n,
+                        S->user_list ? S->max_nbr : std::min(S->seen_spin, S->max_nbr), S->st);
   }
   S->jc_ok[b] = true;
   return SL_OK;
@@ -271,12 +272,13 @@ void spin_launch(sl_system *S, int posbuf, int c, int nrep, const int64_t *steps
   A.replica = S->prm.replica;
   A.rs2 = S->pot.ex_rc * S->pot.ex_rc;
   A.keep = keep && nrep == 2 ? 1 : 0;
+  const int lanes = spin_lanes_for(S, A.end - A.begin);
   ProfScope ps(S, 0, (double)(A.end - A.begin) * nrep);  // atom updates
   if (dual) {
     const SysView<real> v2 = view<real>(S, 1 - posbuf);
-    launch_spin_phase<real>(view<real>(S, posbuf), S->pc, A, S->spin_lanes, S->st, &v2);
+    launch_spin_phase<real>(view<real>(S, posbuf), S->pc, A, lanes, S->st, &v2);
   } else {
-    launch_spin_phase<real>(view<real>(S, posbuf), S->pc, A, S->spin_lanes, S->st);
+    launch_spin_phase<real>(view<real>(S, posbuf), S->pc, A, lanes, S->st);
   }
 }
 
@@ -433,7 +435,7 @@ void run_updates(sl_system *S, int posbuf, const std::vector<Upd> &u, double h,
       T.replica = S->prm.replica;
       T.rs2 = S->pot.ex_rc * S->pot.ex_rc;
       ProfScope ps(S, 0, (double)upd);
-      launch_spin_tail<real>(view<real>(S, posbuf), S->pc, T, S->spin_lanes, S->st);
+      launch_spin_tail<real>(view<real>(S, posbuf), S->pc, T, S->st);
       q = r;
     } else {
       spin_launch<real>(S, posbuf, items[q].c, items[q].nrep, items[q].steps, items[q].subs, h,
@@ -455,8 +457,8 @@ int force_block_cap(int n) { return force_blocks(n, 8) + 8 * (kMaxClass + 8); }
 
 // Blocks of the current force launch (the rows of its partial sums).
 int force_nb(const sl_system *S) {
-  return S->ftile_n > 0 && S->ftile_lanes == S->force_lanes ? S->ftile_n
-                                                             : force_blocks(S->n, S->force_lanes);
+  const int lanes = force_lanes_for(S);
+  return S->ftile_n > 0 && S->ftile_lanes == lanes ? S->ftile_n : force_blocks(S->n, lanes);
 }
 
 // Tile tables of the force launch (per atoms per block) and of the
@@ -511,9 +513,10 @@ static int slab_tiles(sl_system *S, int per, int2 *dev, std::vector<int2> &host,
 }
 
 int force_tiles(sl_system *S) {
-  if (S->ftile_lanes == S->force_lanes) return SL_OK;
-  S->ftile_lanes = S->force_lanes;
-  CHK(slab_tiles(S, kBlock / S->force_lanes, S->ftile, S->ftile_host, S->ftile_n));
+  const int lanes = force_lanes_for(S);
+  if (S->ftile_lanes == lanes) return SL_OK;
+  S->ftile_lanes = lanes;
+  CHK(slab_tiles(S, force_block_atoms(lanes), S->ftile, S->ftile_host, S->ftile_n));
   return slab_tiles(S, kBlock, S->jtile, S->jtile_host, S->jtile_n);
 }
 
@@ -567,10 +570,10 @@ int force_launch(sl_system *S, int posbuf, int mode, double dt, int64_t boundary
     SysView<real> v = view<real>(S, posbuf);
     v.held = S->held ? S->class_off[1] : 0;
     if (split) {
-      launch_force_spin<real>(v, S->pc, F, S->force_lanes, S->st);
+      launch_force_spin<real>(v, S->pc, F, force_lanes_for(S), S->st);
     } else {
       launch_eam_density<real>(v, S->pc, S->st);
-      launch_force<real>(v, S->pc, F, S->force_lanes, S->st);
+      launch_force<real>(v, S->pc, F, force_lanes_for(S), S->st);
     }
   }
   if (mode & (kModeFinal | kModeNext))
@@ -583,7 +586,8 @@ int force_launch(sl_system *S, int posbuf, int mode, double dt, int64_t boundary
 // events and the pair buffer (made on first use), and the pair pass of a
 // boundary on the second stream (the embedded-atom density pass first).
 bool split_ok(const sl_system *S) {
-  return S->overlap > 0 && !S->mlp && (S->force_lanes == 1 || S->force_lanes == 2);
+  const int lanes = force_lanes_for(S);
+  return S->overlap > 0 && !S->mlp && (lanes == 1 || lanes == 2);
 }
 
 int ensure_split(sl_system *S) {
@@ -603,7 +607,7 @@ void pair_launch(sl_system *S, int posbuf, bool energy) {
   ProfScope ps(S, 4, (double)S->n, S->st2);
   const SysView<real> v = view<real>(S, posbuf);
   launch_eam_density<real>(v, S->pc, S->st2);
-  launch_pair<real>(v, S->pc, F, S->force_lanes, energy, S->st2);
+  launch_pair<real>(v, S->pc, F, force_lanes_for(S), energy, S->st2);
 }
 
 int record_thermo(sl_system *S, int64_t boundary) {
@@ -1483,6 +1487,8 @@ int sl_set_tuning(sl_system *S, const sl_tuning *t) {
   S->small_class = t->small_class == 0 ? kSmallClassDefault : t->small_class;
   S->jcache = t->jcache == 0 ? (S->prec == SL_FP32 ? 1 : -1) : t->jcache;
   S->overlap = t->overlap == 0 ? -1 : t->overlap;
+  S->spin_auto = t->spin_lanes == 0;
+  S->jc_auto = t->jcache == 0;
   return SL_OK;
 }
 
