@@ -145,27 +145,27 @@ template void launch_batch_run<float>(RepDesc<float> *, int, int, int, hipStream
 
 // ---------------------------------------------------------------------------
 // Phase-batched replicas: one launch covers every replica's share of one
-// colour phase (blockIdx.y = replica, blockIdx.x = tile of its class), so
-// the whole device works on each phase instead of one workgroup per replica.
-// All replicas advance in lockstep inside a call; replica r is at step
-// d.step + kk with its current positions in buffer d.pos ^ (kk & 1).
+// colour phase, so the whole device works on each phase instead of one
+// workgroup per replica. All replicas advance in lockstep inside a call;
+// replica r is at step d.step + kk with its current positions in buffer
+// d.pos ^ (kk & 1). The blocks follow a host-made list of (replica, tile),
+// replica by replica, cut into eight runs, one per XCD: a replica's gathers then
+// meet in one L2 (or two), and no block is launched for the tiles that smaller
+// replicas do not have (with blocks = tiles of the largest class x replicas, in
+// that order, two thirds of the blocks were empty and every replica was read by
+// all eight XCDs).
 template <typename real, int WAVES, int MLP>
-__global__ __launch_bounds__(kBlock) void k_batch_spin(const RepDesc<real> *D, BatchPhase bp) {
-  const RepDesc<real> &d = D[blockIdx.y];
-  const int K = d.K;
-  const int subf = 2 * bp.half;
-  int c, nrep = 1, s0 = subf, s1 = subf + 1;
-  if (bp.p < bp.Kmax) {
-    if (bp.p >= K) return;
-    c = bp.p;
-    if (c == K - 1) nrep = 2;
-  } else {
-    c = K - 2 - (bp.p - bp.Kmax);
-    if (c < 0) return;
-    s0 = subf + 1;
-  }
+__global__ __launch_bounds__(kBlock) void k_batch_spin(const RepDesc<real> *D, BatchPhase bp,
+                                                       const int2 *tiles) {
+  const int2 e = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+  const RepDesc<real> &d = D[e.x];
+  const int K = d.K, nbig = d.nbig;
+  const int subf = 2 * bp.half + bp.back;
+  const int c = bp.back ? (nbig < K ? nbig - 1 : K - 2) - bp.p : bp.p;
+  if (c < 0 || c >= nbig) return;
+  const int nrep = !bp.back && c == K - 1 ? 2 : 1;
   const int b0 = d.off[c], b1 = d.off[c + 1];
-  const int base = b0 + (int)blockIdx.x * team_atoms(WAVES);
+  const int base = b0 + e.y * team_atoms(WAVES);
   if (base >= b1) return;
   __shared__ SpinTeam<real, WAVES> team[WAVES > 1 ? kBlock / 64 / WAVES : 1];
   const int t = wave_id() / WAVES, w = wave_id() % WAVES;
@@ -173,23 +173,54 @@ __global__ __launch_bounds__(kBlock) void k_batch_spin(const RepDesc<real> *D, B
   const int pos = d.pos ^ (bp.kk & 1);
   const int64_t step = d.step + bp.kk;
   const int64_t st[kMaxRep] = {step, step, step, step};
-  const int sb[kMaxRep] = {s0, s1, 0, 0};
+  const int sb[kMaxRep] = {subf, subf + 1, 0, 0};
   spin_update<real, true, true, WAVES, MLP>(d.V[bp.half == 0 ? pos : 1 - pos], d.P, i, i < b1,
                                              w, team + t, nrep, st, sb, d.h, d.amp, d.seed,
                                              d.replica, d.rs2);
+}
+
+// The small classes of every replica, one workgroup each: classes nbig..K-1 and
+// back, with workgroup barriers between them (a launch of its own costs a class
+// of a few hundred atoms more than its turn here).
+constexpr int kBatchTailWaves = 4;
+template <typename real, int MLP>
+__global__ __launch_bounds__(kBatchBlock) void k_batch_tail(const RepDesc<real> *D, BatchPhase bp,
+                                                            const int2 *reps) {
+  constexpr int kTeams = kBatchBlock / 64 / kBatchTailWaves;
+  __shared__ SpinTeam<real, kBatchTailWaves> team[kTeams];
+  const RepDesc<real> &d = D[reps[blockIdx.x].x];
+  const int t = wave_id() / kBatchTailWaves, w = wave_id() % kBatchTailWaves;
+  const int K = d.K, nbig = d.nbig, m = K - nbig;
+  const int pos = d.pos ^ (bp.kk & 1);
+  const int64_t step = d.step + bp.kk;
+  const int64_t st[kMaxRep] = {step, step, step, step};
+  const SysView<real> &V = d.V[bp.half == 0 ? pos : 1 - pos];
+  for (int q = 0; q < 2 * m - 1; ++q) {
+    const int c = nbig + (q < m ? q : 2 * m - 2 - q);
+    const int s0 = 2 * bp.half + (q < m ? 0 : 1);
+    const int sb[kMaxRep] = {s0, s0 + 1, 0, 0};
+    const int nrep = q == m - 1 ? 2 : 1;
+    const int b0 = d.off[c], b1 = d.off[c + 1];
+    for (int base = b0; base < b1; base += 64 * kTeams) {
+      const int i = base + 64 * t + (int)(threadIdx.x & 63);
+      spin_update<real, true, true, kBatchTailWaves, MLP>(V, d.P, i, i < b1, w, team + t, nrep, st, sb,
+                                                          d.h, d.amp, d.seed, d.replica, d.rs2);
+      __syncthreads();
+    }
+  }
 }
 
 // Force, kicks and drift of every replica at one boundary; each block stores
 // its replica's rebuild predictor terms, which k_batch_pred_reduce joins into
 // the replica's pinned slot (as k_pred_reduce does for one system).
 template <typename real, int MODE, int WAVES, int MLP>
-__global__ __launch_bounds__(kBlock) void k_batch_force(const RepDesc<real> *D, BatchPhase bp) {
+__global__ __launch_bounds__(kBlock) void k_batch_force(const RepDesc<real> *D, BatchPhase bp,
+                                                        const int2 *tiles) {
   __shared__ double redm[kBlock / 64][3];
-  const RepDesc<real> &d = D[blockIdx.y];
+  const int2 tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+  const RepDesc<real> &d = D[tl.x];
   const int n = d.V[0].n;
   constexpr int per = team_atoms(WAVES);
-  const int nb = (n + per - 1) / per;
-  if ((int)blockIdx.x >= nb) return;
   __shared__ ForceTeam<real, WAVES> team[WAVES > 1 ? kBlock / 64 / WAVES : 1];
   const int t = wave_id() / WAVES, w = wave_id() % WAVES;
   // buffer holding this boundary's positions; the drift goes to the other
@@ -202,7 +233,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_force(const RepDesc<real> *D, 
   F.ny = const_cast<double *>(d.V[1 - cur].ry);
   F.nz = const_cast<double *>(d.V[1 - cur].rz);
   F.host_out = d.ring + 8 * (int)(boundary & 3);
-  const int i = (int)blockIdx.x * per + 64 * t + (int)(threadIdx.x & 63);
+  const int i = tl.y * per + 64 * t + (int)(threadIdx.x & 63);
   double e[8], dm = 0.0, vm = 0.0, wm = kInf;
   force_atom<real, MODE, WAVES, MLP>(d.V[cur], d.P, F, i, i < n, w, team + t, e, dm, vm, wm);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -217,9 +248,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_force(const RepDesc<real> *D, 
       z = fmin(z, redm[w][2]);
     }
     // per-block terms as plain stores, joined per replica by k_batch_pred_reduce
-    F.pred[(size_t)blockIdx.x * 3 + 0] = x;
-    F.pred[(size_t)blockIdx.x * 3 + 1] = y;
-    F.pred[(size_t)blockIdx.x * 3 + 2] = z;
+    F.pred[(size_t)tl.y * 3 + 0] = x;
+    F.pred[(size_t)tl.y * 3 + 1] = y;
+    F.pred[(size_t)tl.y * 3 + 2] = z;
   }
 }
 
@@ -263,41 +294,47 @@ __global__ __launch_bounds__(kBlock) void k_batch_pred_reduce(const RepDesc<real
 }
 
 template <typename real, int MLP>
-static void batch_spin_lanes(const RepDesc<real> *D, const dim3 &grid, const BatchPhase &bp,
+static void batch_spin_lanes(const RepDesc<real> *D, const int2 *tiles, int nt, const BatchPhase &bp,
                              int lanes, hipStream_t st) {
   switch (lanes) {
-    case 1: hipLaunchKernelGGL((k_batch_spin<real, 1, MLP>), grid, dim3(kBlock), 0, st, D, bp); break;
-    case 4: hipLaunchKernelGGL((k_batch_spin<real, 4, MLP>), grid, dim3(kBlock), 0, st, D, bp); break;
-    default: hipLaunchKernelGGL((k_batch_spin<real, 2, MLP>), grid, dim3(kBlock), 0, st, D, bp); break;
+    case 1: hipLaunchKernelGGL((k_batch_spin<real, 1, MLP>), dim3(nt), dim3(kBlock), 0, st, D, bp, tiles); break;
+    case 4: hipLaunchKernelGGL((k_batch_spin<real, 4, MLP>), dim3(nt), dim3(kBlock), 0, st, D, bp, tiles); break;
+    default: hipLaunchKernelGGL((k_batch_spin<real, 2, MLP>), dim3(nt), dim3(kBlock), 0, st, D, bp, tiles); break;
   }
 }
 
 template <typename real>
-void launch_batch_spin(const RepDesc<real> *D, int R, int max_class, const BatchPhase &bp,
+void launch_batch_spin(const RepDesc<real> *D, const int2 *tiles, int ntiles, const BatchPhase &bp,
                        int lanes, bool soc, hipStream_t st) {
-  if (R <= 0 || max_class <= 0) return;
-  const int per = kBlock / lanes;
-  const dim3 grid((max_class + per - 1) / per, R);
-  if (soc) batch_spin_lanes<real, 4>(D, grid, bp, lanes, st);
-  else batch_spin_lanes<real, 0>(D, grid, bp, lanes, st);
+  if (ntiles <= 0) return;
+  if (soc) batch_spin_lanes<real, 4>(D, tiles, ntiles, bp, lanes, st);
+  else batch_spin_lanes<real, 0>(D, tiles, ntiles, bp, lanes, st);
+}
+
+template <typename real>
+void launch_batch_tail(const RepDesc<real> *D, const int2 *reps, int nreps, const BatchPhase &bp,
+                       bool soc, hipStream_t st) {
+  if (nreps <= 0) return;
+  if (soc) hipLaunchKernelGGL((k_batch_tail<real, 4>), dim3(nreps), dim3(kBatchBlock), 0, st, D, bp, reps);
+  else hipLaunchKernelGGL((k_batch_tail<real, 0>), dim3(nreps), dim3(kBatchBlock), 0, st, D, bp, reps);
 }
 
 template <typename real, int MODE, int MLP>
 static void batch_force_mode(const RepDesc<real> *D, const dim3 &grid, const BatchPhase &bp,
-                             int lanes, hipStream_t st) {
+                             int lanes, const int2 *tiles, hipStream_t st) {
   switch (lanes) {
-    case 2: hipLaunchKernelGGL((k_batch_force<real, MODE, 2, MLP>), grid, dim3(kBlock), 0, st, D, bp); break;
-    case 4: hipLaunchKernelGGL((k_batch_force<real, MODE, 4, MLP>), grid, dim3(kBlock), 0, st, D, bp); break;
-    default: hipLaunchKernelGGL((k_batch_force<real, MODE, 1, MLP>), grid, dim3(kBlock), 0, st, D, bp); break;
+    case 2: hipLaunchKernelGGL((k_batch_force<real, MODE, 2, MLP>), grid, dim3(kBlock), 0, st, D, bp, tiles); break;
+    case 4: hipLaunchKernelGGL((k_batch_force<real, MODE, 4, MLP>), grid, dim3(kBlock), 0, st, D, bp, tiles); break;
+    default: hipLaunchKernelGGL((k_batch_force<real, MODE, 1, MLP>), grid, dim3(kBlock), 0, st, D, bp, tiles); break;
   }
 }
 
 template <typename real, int MLP>
 static void batch_force_any(const RepDesc<real> *D, const dim3 &grid, int mode,
-                            const BatchPhase &bp, int lanes, hipStream_t st) {
-  if (mode == kModeNext) batch_force_mode<real, kModeNext, MLP>(D, grid, bp, lanes, st);
-  else if (mode == kModeFinal) batch_force_mode<real, kModeFinal, MLP>(D, grid, bp, lanes, st);
-  else batch_force_mode<real, kModeFinal | kModeNext, MLP>(D, grid, bp, lanes, st);
+                            const BatchPhase &bp, int lanes, const int2 *tiles, hipStream_t st) {
+  if (mode == kModeNext) batch_force_mode<real, kModeNext, MLP>(D, grid, bp, lanes, tiles, st);
+  else if (mode == kModeFinal) batch_force_mode<real, kModeFinal, MLP>(D, grid, bp, lanes, tiles, st);
+  else batch_force_mode<real, kModeFinal | kModeNext, MLP>(D, grid, bp, lanes, tiles, st);
 }
 
 // Embedded-atom densities of every replica at the boundary a force pass with
@@ -311,28 +348,29 @@ __global__ __launch_bounds__(kBlock) void k_batch_density(const RepDesc<real> *D
 }
 
 template <typename real>
-void launch_batch_force(const RepDesc<real> *D, int R, int max_n, int mode, const BatchPhase &bp,
-                        int lanes, int variant, hipStream_t st) {
-  if (R <= 0 || max_n <= 0) return;
+void launch_batch_force(const RepDesc<real> *D, int R, const int2 *tiles, int ntiles, int max_n,
+                        int mode, const BatchPhase &bp, int lanes, int variant, hipStream_t st) {
+  if (R <= 0 || ntiles <= 0) return;
   if (variant & 8)
     hipLaunchKernelGGL((k_batch_density<real>), dim3((max_n + kBlock - 1) / kBlock, R), dim3(kBlock),
                        0, st, D, bp);
-  const int per = kBlock / lanes;
-  const dim3 grid((max_n + per - 1) / per, R);
+  const dim3 grid(ntiles);
   switch (variant) {
-    case 4: batch_force_any<real, 4>(D, grid, mode, bp, lanes, st); break;
-    case 8: batch_force_any<real, 8>(D, grid, mode, bp, lanes, st); break;
-    case 12: batch_force_any<real, 12>(D, grid, mode, bp, lanes, st); break;
-    default: batch_force_any<real, 0>(D, grid, mode, bp, lanes, st); break;
+    case 4: batch_force_any<real, 4>(D, grid, mode, bp, lanes, tiles, st); break;
+    case 8: batch_force_any<real, 8>(D, grid, mode, bp, lanes, tiles, st); break;
+    case 12: batch_force_any<real, 12>(D, grid, mode, bp, lanes, tiles, st); break;
+    default: batch_force_any<real, 0>(D, grid, mode, bp, lanes, tiles, st); break;
   }
   // atoms per block of the instance batch_force_mode ran (it takes 1 lane
   // for any count other than 2 and 4)
-  const int per_k = kBlock / ((lanes == 2 || lanes == 4) ? lanes : 1);
+  const int per_k = team_atoms((lanes == 2 || lanes == 4) ? lanes : 1);
   hipLaunchKernelGGL((k_batch_pred_reduce<real>), dim3(R), dim3(kBlock), 0, st, D, bp, per_k);
 }
-template void launch_batch_spin<double>(const RepDesc<double> *, int, int, const BatchPhase &, int, bool, hipStream_t);
-template void launch_batch_spin<float>(const RepDesc<float> *, int, int, const BatchPhase &, int, bool, hipStream_t);
-template void launch_batch_force<double>(const RepDesc<double> *, int, int, int, const BatchPhase &, int, int, hipStream_t);
-template void launch_batch_force<float>(const RepDesc<float> *, int, int, int, const BatchPhase &, int, int, hipStream_t);
+template void launch_batch_spin<double>(const RepDesc<double> *, const int2 *, int, const BatchPhase &, int, bool, hipStream_t);
+template void launch_batch_spin<float>(const RepDesc<float> *, const int2 *, int, const BatchPhase &, int, bool, hipStream_t);
+template void launch_batch_tail<double>(const RepDesc<double> *, const int2 *, int, const BatchPhase &, bool, hipStream_t);
+template void launch_batch_tail<float>(const RepDesc<float> *, const int2 *, int, const BatchPhase &, bool, hipStream_t);
+template void launch_batch_force<double>(const RepDesc<double> *, int, const int2 *, int, int, int, const BatchPhase &, int, int, hipStream_t);
+template void launch_batch_force<float>(const RepDesc<float> *, int, const int2 *, int, int, int, const BatchPhase &, int, int, hipStream_t);
 
 }  // namespace sl

@@ -33,6 +33,16 @@ struct sl_batch {
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   int64_t launches = 0, rebuilds = 0;
   std::string last_err;
+  // block lists of the phased launches: (replica, tile) of every forward phase,
+  // every backward phase, the tail (replicas) and the force pass, one after
+  // another in tiles; part[q], part[q + 1] bound list q
+  std::vector<int2> tiles_h;
+  std::vector<int> part;
+  int2 *tiles = nullptr;
+  size_t tiles_cap = 0;
+  int tiles_lanes = 0, nphase = 0;       // lanes the lists were made for; phases each way
+  std::vector<int> tiles_K, tiles_big;   // K and nbig of every replica then
+  std::vector<std::vector<int>> tiles_n; // tiles of every class of every replica then
 };
 
 namespace {
@@ -74,6 +84,79 @@ int batch_variant(const sl_batch *B) {
   return v;
 }
 
+// Leading classes of a replica that get launches of their own: all up to the last
+// one above kBatchTailAtoms atoms (the classes of a repair or a lattice seam
+// follow in falling size).
+#ifndef SL_BATCH_TAIL
+#define SL_BATCH_TAIL 256
+#endif
+constexpr int kBatchTailAtoms = SL_BATCH_TAIL;
+int batch_nbig(const sl_system *S) {
+  int c = S->K;
+  while (c > 0 && S->class_off[c] - S->class_off[c - 1] <= kBatchTailAtoms) --c;
+  return c;
+}
+
+// Block lists for the current classes. A list holds one tile more per class than
+// it needs, so that a rebuild that moves a few atoms between classes keeps it;
+// a replica whose classes outgrew it (or changed in number) makes all lists anew.
+int batch_tiles(sl_batch *B) {
+  const int R = B->R, per = kBlock / B->lanes;
+  bool ok = B->tiles_lanes == B->lanes && (int)B->tiles_K.size() == R;
+  auto need = [&](const sl_system *S, int c) {
+    return (S->class_off[c + 1] - S->class_off[c] + per - 1) / per;
+  };
+  for (int r = 0; r < R && ok; ++r) {
+    const sl_system *S = B->sys[r];
+    ok = B->tiles_K[r] == S->K && B->tiles_big[r] == batch_nbig(S);
+    for (int c = 0; c < S->K && ok; ++c) ok = need(S, c) <= B->tiles_n[r][c];
+  }
+  if (ok) return SL_OK;
+  B->tiles_K.assign(R, 0);
+  B->tiles_big.assign(R, 0);
+  B->tiles_n.assign(R, {});
+  B->nphase = 0;
+  for (int r = 0; r < R; ++r) {
+    const sl_system *S = B->sys[r];
+    B->tiles_K[r] = S->K;
+    B->tiles_big[r] = batch_nbig(S);
+    for (int c = 0; c < S->K; ++c) B->tiles_n[r].push_back(need(S, c) + 1);
+    B->nphase = std::max(B->nphase, B->tiles_big[r]);
+  }
+  auto &T = B->tiles_h;
+  T.clear();
+  B->part.assign(1, 0);
+  for (int back = 0; back < 2; ++back)
+    for (int p = 0; p < B->nphase; ++p) {
+      for (int r = 0; r < R; ++r) {
+        const int K = B->tiles_K[r], big = B->tiles_big[r];
+        const int c = back ? (big < K ? big - 1 : K - 2) - p : p;
+        if (c < 0 || c >= big) continue;
+        for (int t = 0; t < B->tiles_n[r][c]; ++t) T.push_back(make_int2(r, t));
+      }
+      B->part.push_back((int)T.size());
+    }
+  for (int r = 0; r < R; ++r)
+    if (B->tiles_big[r] < B->tiles_K[r]) T.push_back(make_int2(r, 0));
+  B->part.push_back((int)T.size());
+  for (int r = 0; r < R; ++r)
+    for (int t = 0; t * per < B->sys[r]->n; ++t) T.push_back(make_int2(r, t));
+  B->part.push_back((int)T.size());
+  B->tiles_lanes = 0;  // (not valid should the upload fail)
+  if (T.size() > B->tiles_cap) {
+    if (B->tiles) (void)hipFree(B->tiles);
+    B->tiles = nullptr;
+    B->tiles_cap = 0;
+    if (hipMalloc((void **)&B->tiles, sizeof(int2) * 2 * T.size()) != hipSuccess)
+      return bfail(B, SL_E_NOMEM, "block lists: allocation failed");
+    B->tiles_cap = 2 * T.size();
+  }
+  BCHK(B, hipMemcpyAsync(B->tiles, T.data(), sizeof(int2) * T.size(), hipMemcpyHostToDevice, B->st));
+  BCHK(B, hipStreamSynchronize(B->st));
+  B->tiles_lanes = B->lanes;
+  return SL_OK;
+}
+
 // Descriptor of replica r for the batched kernels (current buffers, class
 // offsets, step, predictor state of the last two boundaries).
 template <typename real>
@@ -97,6 +180,7 @@ int fill_desc(sl_batch *B, int r, double dt, int64_t target, RepDesc<real> &d) {
   d.F.replica = S->prm.replica;
   if (S->K > kMaxClass) return bfail(B, SL_E_COLOR, "replica " + std::to_string(r) + " has too many colours");
   d.K = S->K;
+  d.nbig = batch_nbig(S);
   for (int c = 0; c <= S->K; ++c) d.off[c] = S->class_off[c];
   d.pos = S->pos;
   d.step = S->step;
@@ -250,22 +334,22 @@ int batch_step_phased(sl_batch *B, int64_t n, double dt) {
   }
   BCHK(B, hipMemcpyAsync(B->d_desc, B->h_desc.data(), dsz * R, hipMemcpyHostToDevice, B->st));
   BCHK(B, hipStreamSynchronize(B->st));
-  auto extents = [&](int &Kmax, int &max_class, int &max_n) {
-    Kmax = 0; max_class = 0; max_n = 0;
-    for (auto *S : B->sys) {
-      Kmax = std::max(Kmax, S->K);
-      max_n = std::max(max_n, S->n);
-      for (int c = 0; c < S->K; ++c)
-        max_class = std::max(max_class, S->class_off[c + 1] - S->class_off[c]);
-    }
-  };
-  int Kmax, max_class, max_n;
-  extents(Kmax, max_class, max_n);
+  CHK(batch_tiles(B));
+  int max_n = 0;
+  for (auto *S : B->sys) max_n = std::max(max_n, S->n);
+  const bool soc = batch_soc(B);
+  const int variant = batch_variant(B);
+  auto count = [&](int q) { return B->part[q + 1] - B->part[q]; };
+  auto list = [&](int q) { return B->tiles + B->part[q]; };
   const RepDesc<real> *D = (const RepDesc<real> *)B->d_desc;
   BatchPhase bp{};
   bp.kk = 0;
   bp.after = 0;
-  launch_batch_force<real>(D, R, max_n, kModeNext, bp, B->lanes, batch_variant(B), B->st);
+  auto force = [&](int mode) {
+    const int q = 2 * B->nphase + 1;
+    launch_batch_force<real>(D, R, list(q), count(q), max_n, mode, bp, B->lanes, variant, B->st);
+  };
+  force(kModeNext);
   BCHK(B, hipEventRecord(B->ev[0], B->st));
   for (int64_t kk = 0; kk < n; ++kk) {
     if (kk > 0) {
@@ -301,16 +385,23 @@ int batch_step_phased(sl_batch *B, int64_t n, double dt) {
       }
       if (changed) {
         BCHK(B, hipStreamSynchronize(B->st));
-        extents(Kmax, max_class, max_n);
+        CHK(batch_tiles(B));
       }
     }
     bp.kk = (int)kk;
     for (int half = 0; half < 2; ++half) {
       bp.half = half;
-      bp.Kmax = Kmax;
-      for (int p = 0; p < 2 * Kmax - 1; ++p) {
-        bp.p = p;
-        launch_batch_spin<real>(D, R, max_class, bp, B->lanes, batch_soc(B), B->st);
+      for (bp.back = 0; bp.back < 2; ++bp.back) {
+        for (bp.p = 0; bp.p < B->nphase; ++bp.p) {
+          const int q = bp.back * B->nphase + bp.p;
+          launch_batch_spin<real>(D, list(q), count(q), bp, B->lanes, soc, B->st);
+          if (count(q) > 0) B->launches++;
+        }
+        if (bp.back == 0) {
+          const int q = 2 * B->nphase;
+          launch_batch_tail<real>(D, list(q), count(q), bp, soc, B->st);
+          if (count(q) > 0) B->launches++;
+        }
       }
     }
     const int mode = kk + 1 < n ? (kModeFinal | kModeNext) : kModeFinal;
@@ -326,10 +417,10 @@ int batch_step_phased(sl_batch *B, int64_t n, double dt) {
       S->step = b;
     }
     bp.after = 1;
-    launch_batch_force<real>(D, R, max_n, mode, bp, B->lanes, batch_variant(B), B->st);
+    force(mode);
     bp.after = 0;
     BCHK(B, hipEventRecord(B->ev[(kk + 1) & 3], B->st));
-    B->launches += 2 * (2 * Kmax - 1) + 1;
+    B->launches++;
   }
   BCHK(B, hipStreamSynchronize(B->st));
   // predictor state of the last two boundaries, for the next call's start
@@ -418,6 +509,7 @@ int sl_batch_destroy(sl_batch *B) {
   for (auto *S : B->sys)
     if (S) sl_destroy(S);
   if (B->d_desc) (void)hipFree(B->d_desc);
+  if (B->tiles) (void)hipFree(B->tiles);
   for (auto &e : B->ev)
     if (e) (void)hipEventDestroy(e);
   if (B->st) (void)hipStreamDestroy(B->st);

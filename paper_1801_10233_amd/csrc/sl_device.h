@@ -289,6 +289,7 @@ struct RepDesc {
   PotConst P;
   ForceArgs F;                 // mass, velocities, reference positions, error word
   int K;
+  int nbig;                    // classes with launches of their own (BatchPhase)
   int off[kMaxClass + 1];      // class offsets
   int pos;                     // buffer holding the positions of the current boundary
   int64_t step, target;
@@ -308,13 +309,15 @@ struct RepDesc {
   double *ring;                // pinned host predictor slots [4][8] (phase mode)
 };
 
-// One launch of the phase-batched mode: every replica's share of colour
-// phase p of a spin half-step, or of a force pass. Replica r (K_r classes)
-// visits class p for p < K_r - 1, its last class twice in a row at
-// p = K_r - 1 and class K_r - 2 - (p - Kmax) for p >= Kmax; any other phase
-// leaves it idle, so each replica keeps its own forward/backward order.
+// One launch of the phase-batched mode: every replica's share of phase p of a
+// spin half-step, or of a force pass. Replica r gives its first nbig classes
+// launches of their own and its remaining small ones to the tail launch:
+// forward phase p is class p (p < nbig), the tail runs classes nbig..K-1 and
+// back to nbig, backward phase p is class nbig - 1 - p. Without a tail (nbig =
+// K) the last class takes its two updates in its forward phase and backward
+// phase p is class K - 2 - p. Each replica keeps its own order that way.
 struct BatchPhase {
-  int p, Kmax;
+  int p, back;
   int half;   // spin: 0 first half-step (boundary positions), 1 second
   int kk;     // steps since the call started: replica step = step + kk
   int after;  // force: 1 at the boundary after step kk, 0 at the call start

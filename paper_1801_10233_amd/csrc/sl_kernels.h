@@ -46,19 +46,23 @@ void launch_eam_density(const SysView<real> &S, const PotConst &P, hipStream_t s
 template <typename real>
 void launch_jcache(const SysView<real> &S, const PotConst &P, real *out, double rs2,
                    const int2 *tiles, int ntiles, int max_slots, hipStream_t st);
-// Phase-batched mode: one colour phase of every replica (max_class = the
-// largest class of any replica) and one force pass of every replica (max_n =
-// the largest replica; mode kModeNext at the call start, kModeFinal with or
-// without kModeNext after a step). soc selects the spin variant with the
-// spin-orbit pair terms (needed when any replica has them); variant is the
-// force variant (4: spin-orbit terms, 8: embedded-atom terms, 12: both), the
-// embedded-atom densities being computed first.
+// Phase-batched mode: one colour phase, the small classes, or one force pass
+// (mode kModeNext at the call start, kModeFinal with or without kModeNext after a
+// step) of every replica. `tiles` lists (replica, tile) of the launch's blocks,
+// replica by replica; the tail's list is the replicas. soc selects the spin
+// variant with the spin-orbit pair terms (needed when any replica has them);
+// variant is the force variant (4: spin-orbit terms, 8: embedded-atom terms, 12:
+// both), the embedded-atom densities being computed first (max_n: the largest
+// replica).
 template <typename real>
-void launch_batch_spin(const RepDesc<real> *D, int R, int max_class, const BatchPhase &bp,
+void launch_batch_spin(const RepDesc<real> *D, const int2 *tiles, int ntiles, const BatchPhase &bp,
                        int lanes, bool soc, hipStream_t st);
 template <typename real>
-void launch_batch_force(const RepDesc<real> *D, int R, int max_n, int mode, const BatchPhase &bp,
-                        int lanes, int variant, hipStream_t st);
+void launch_batch_tail(const RepDesc<real> *D, const int2 *reps, int nreps, const BatchPhase &bp,
+                       bool soc, hipStream_t st);
+template <typename real>
+void launch_batch_force(const RepDesc<real> *D, int R, const int2 *tiles, int ntiles, int max_n,
+                        int mode, const BatchPhase &bp, int lanes, int variant, hipStream_t st);
 void launch_reduce8(const double *partial, int nb, double *out, hipStream_t st);
 
 // --- sectored ordering (sl_sect.hip) ---
