@@ -100,6 +100,7 @@ struct sl_system {
   int *err = nullptr, *seen = nullptr, *jpcnt = nullptr, *maxc = nullptr;
   int *jplist[2] = {nullptr, nullptr};  // ready lists of the colouring rounds
   unsigned long long *jpmask[2] = {nullptr, nullptr};  // conflict / earlier-key slot masks
+  int *jprow = nullptr;                 // packed conflict rows of the colouring [n][16]
   unsigned long long *dslot = nullptr;
   double *pred = nullptr;  // [force blocks][3] predictor terms of one launch
   int2 *ftile = nullptr;   // [force blocks] atom range of each force block (slabs per XCD)

@@ -127,6 +127,9 @@ struct ColourArgs {
   const double *rx, *ry, *rz;
   double L[3], invL[3];
   double cr2;
+  int *rows;       // [n][16] packed conflicting neighbours (k_colour_indeg)
+  int mutual;      // 1: j in the row of i means i in the row of j
+  const int *err;  // sticky error word
 };
 void launch_colour_fill(int n, int *colour, int value, hipStream_t st);
 // Uncolour every atom that shares its colour with an earlier-key neighbour,

@@ -19,6 +19,12 @@ static inline int nblocks(int n) { return (n + kBlock - 1) / kBlock; }
 
 __device__ __forceinline__ double wrap(double x, double L) { return x - L * floor(x / L); }
 
+__device__ __forceinline__ int wave_max_i(int x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
+  return x;
+}
+
 __device__ __forceinline__ int cell_coord(double x, double L, int nc) {
   int k = (int)(wrap(x, L) / L * nc);
   return k < 0 ? 0 : (k >= nc ? nc - 1 : k);
@@ -66,23 +72,66 @@ __global__ void k_bucket_scatter(int n, const int *key, const int *start, int *f
   out[start[b] + atomicAdd(&fill[b], 1)] = i;
 }
 
-__global__ void k_bucket_sort_x(int nbucket, const int *start, int *items, const double *x) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nbucket) return;
-  const int a = start[b], e = start[b + 1];
+// Buckets sorted ascending, one wavefront per bucket: up to 64 items sit one per
+// lane, each lane counts the smaller ones and stores its item at that rank (the
+// order is total). Larger buckets (a gas with a dense spot) are sorted by
+// insertion on one lane. (One thread per bucket by insertion took 43 us for the
+// 1000 cells of 16 000 atoms, a chain of dependent loads.)
+template <bool BYX>
+__device__ __forceinline__ void bucket_sort_one(int a, int e, int *items, const double *x) {
+  const int lane = threadIdx.x & 63, m = e - a;
+  if (m < 2) return;
+  if (m <= 64) {
+    const int v = lane < m ? items[a + lane] : 0;
+    const double xv = BYX && lane < m ? x[v] : 0.0;
+    int rank = 0;
+    for (int q = 0; q < m; ++q) {
+      const int u = __builtin_amdgcn_readlane(v, q);
+      if (BYX) {
+        const double xu = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(xv), q),
+                                           __builtin_amdgcn_readlane(__double2loint(xv), q));
+        rank += xu < xv || (xu == xv && u < v);
+      } else {
+        rank += u < v;
+      }
+    }
+    // (positions that are not numbers compare with nothing and would share a
+    // rank: such a bucket goes to the insertion below)
+    const unsigned long long bad = __ballot(BYX && lane < m && !(xv == xv));
+    if (!bad) {
+      if (lane < m) items[a + rank] = v;
+      return;
+    }
+  }
+  if (lane != 0) return;
   for (int p = a + 1; p < e; ++p) {
     const int v = items[p];
-    const double xv = x[v];
+    const double xv = BYX ? x[v] : 0.0;
     int q = p - 1;
     while (q >= a) {
       const int u = items[q];
-      const double xu = x[u];
-      if (xu < xv || (xu == xv && u < v)) break;
+      if (BYX) {
+        const double xu = x[u];
+        if (xu < xv || (xu == xv && u < v)) break;
+      } else if (u <= v) {
+        break;
+      }
       items[q + 1] = u;
       --q;
     }
     items[q + 1] = v;
   }
+}
+
+__global__ __launch_bounds__(kBlock) void k_bucket_sort_x(int nbucket, const int *start, int *items,
+                                                          const double *x) {
+  const int b = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  if (b < nbucket) bucket_sort_one<true>(start[b], start[b + 1], items, x);
+}
+
+__global__ __launch_bounds__(kBlock) void k_bucket_sort(int nbucket, const int *start, int *items) {
+  const int b = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  if (b < nbucket) bucket_sort_one<false>(start[b], start[b + 1], items, nullptr);
 }
 
 __global__ void k_cell_positions(int n, const int *catoms, const double *rx, const double *ry,
@@ -93,21 +142,6 @@ __global__ void k_cell_positions(int n, const int *catoms, const double *rx, con
   cx[p] = rx[j];
   cy[p] = ry[j];
   cz[p] = rz[j];
-}
-
-__global__ void k_bucket_sort(int nbucket, const int *start, int *items) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= nbucket) return;
-  const int a = start[b], e = start[b + 1];
-  for (int p = a + 1; p < e; ++p) {
-    const int x = items[p];
-    int q = p - 1;
-    while (q >= a && items[q] > x) {
-      items[q + 1] = items[q];
-      --q;
-    }
-    items[q + 1] = x;
-  }
 }
 
 // Full neighbour rows from the 27 surrounding cells (fewer when a side has
@@ -185,11 +219,17 @@ __global__ __launch_bounds__(kBlock) void k_nbr_build(NbrBuildArgs A) {
       cnt[1] = tr;
     }
   }
-  if (!valid || l != 0) return;
   const int ns = cnt[0], nt = cnt[0] + cnt[1];
+  // one maximum per wavefront, and only where it raises the stored one: an
+  // atomic per atom on the two words took most of the build's time (16 000
+  // atoms: 138 us, 20 without)
+  const int ws = wave_max_i(valid ? ns : 0), wt = wave_max_i(valid ? nt : 0);
+  if ((threadIdx.x & 63) == 0) {
+    if (ws > *(volatile int *)&A.seen[0]) atomicMax(&A.seen[0], ws);
+    if (wt > *(volatile int *)&A.seen[1]) atomicMax(&A.seen[1], wt);
+  }
+  if (!valid || l != 0) return;
   if (nt > A.max_nbr || ns > A.max_spin) atomicOr(A.err, kErrNbrOverflow);
-  atomicMax(&A.seen[0], ns);
-  atomicMax(&A.seen[1], nt);
   A.nspin[i] = min(ns, A.max_spin);
   A.nall[i] = min(nt, A.max_nbr);
   A.bx[i] = rix;
@@ -206,12 +246,18 @@ __global__ __launch_bounds__(kBlock) void k_nbr_build(NbrBuildArgs A) {
 // per thread (slot-major, so a wavefront's reads hit distinct banks), and
 // every entry goes straight to its rank (keys are unique: they end in j).
 // Segments longer than kOrderMax keep the cell-loop order.
+// SUB lanes share an atom (entries l, l + SUB, ...) where there are too few atoms
+// to fill the device: the m^2 comparisons of a row are a chain on one lane (16 000
+// atoms: 78 us with one lane).
 constexpr int kOrderBlock = 64, kOrderMax = 64;
+template <int SUB>
 __global__ __launch_bounds__(kOrderBlock) void k_row_order(NbrBuildArgs A, double invq) {
-  __shared__ unsigned long long key[kOrderMax * kOrderBlock];
-  const int t = threadIdx.x;
-  const int i = blockIdx.x * kOrderBlock + t;
-  if (i >= A.n) return;
+  constexpr int kAtoms = kOrderBlock / SUB;
+  __shared__ unsigned long long key[kOrderMax * kAtoms];
+  const int t = threadIdx.x % kAtoms, l = threadIdx.x / kAtoms;
+  const int i0 = blockIdx.x * kAtoms + t;
+  if (SUB == 1 && i0 >= A.n) return;
+  const int i = min(i0, A.n - 1);  // (lanes past the end repeat the last atom, storing nothing)
   const double Lx = A.G.L[0], Ly = A.G.L[1], Lz = A.G.L[2];
   const double iLx = 1.0 / Lx, iLy = 1.0 / Ly, iLz = 1.0 / Lz;
   const double rix = A.rx[i], riy = A.ry[i], riz = A.rz[i];
@@ -222,22 +268,24 @@ __global__ __launch_bounds__(kOrderBlock) void k_row_order(NbrBuildArgs A, doubl
   };
   for (int seg = 0; seg < 2; ++seg) {
     const int beg = seg == 0 ? 0 : ns, end = seg == 0 ? ns : na;
-    const int m = end - beg;
-    if (m < 2 || m > kOrderMax) continue;
-    for (int f = 0; f < m; ++f) {
+    const int m0 = end - beg;
+    const int m = m0 < 2 || m0 > kOrderMax ? 0 : m0;
+    for (int f = l; f < m; f += SUB) {
       const int j = A.nbr[(size_t)(beg + f) * A.ld + i];
       const double dx = min_image(A.rx[j] - rix, Lx, iLx);
       const double dy = min_image(A.ry[j] - riy, Ly, iLy);
       const double dz = min_image(A.rz[j] - riz, Lz, iLz);
       const unsigned long long q = (q10(dz) << 20) | (q10(dy) << 10) | q10(dx);
-      key[f * kOrderBlock + t] = (q << 32) | (unsigned)j;
+      key[f * kAtoms + t] = (q << 32) | (unsigned)j;
     }
-    for (int e = 0; e < m; ++e) {
-      const unsigned long long ke = key[e * kOrderBlock + t];
+    if (SUB > 1) __syncthreads();
+    for (int e = l; e < m; e += SUB) {
+      const unsigned long long ke = key[e * kAtoms + t];
       int rank = 0;
-      for (int f = 0; f < m; ++f) rank += key[f * kOrderBlock + t] < ke ? 1 : 0;
-      A.nbr[(size_t)(beg + rank) * A.ld + i] = (int)(unsigned)(ke & 0xffffffffull);
+      for (int f = 0; f < m; ++f) rank += key[f * kAtoms + t] < ke ? 1 : 0;
+      if (i0 < A.n) A.nbr[(size_t)(beg + rank) * A.ld + i] = (int)(unsigned)(ke & 0xffffffffull);
     }
+    if (SUB > 1) __syncthreads();
   }
 }
 
@@ -319,6 +367,11 @@ __device__ __forceinline__ bool colour_try(const ColourArgs &A, int i) {
 // ready list. Every atom is coloured once all its earlier-key neighbours
 // are, from the colours around it then -- the sequential greedy's choice --
 // and each round touches only the atoms that became ready.
+// Besides the masks the pass packs an atom's conflicting neighbours into one
+// 64-byte row (kRowInts words: index, with the top bit set for the later-key
+// ones, kRowNone behind the last; kRowLong in the last word when there are
+// more), so that a round reads a line per ready atom instead of a line per slot.
+constexpr int kRowInts = 16, kRowNone = -1, kRowLong = -2;
 __global__ void k_colour_indeg(ColourArgs A, int *indeg, unsigned long long *cmask,
                                unsigned long long *emask, int *list, int *count) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -326,17 +379,40 @@ __global__ void k_colour_indeg(ColourArgs A, int *indeg, unsigned long long *cma
   // spin-segment slots that are edges of the colouring graph, and those of
   // them whose atom comes earlier in key order (the segment has < 64 slots)
   unsigned long long cm = 0ull, em = 0ull;
-  int c = 0;
+  int c = 0, m = 0;
+  int *row = A.rows + (size_t)i * kRowInts;
   const int ns = A.nspin[i] < 64 ? A.nspin[i] : 64;
-  for (int k = 0; k < ns; ++k) {
-    const int j = A.nbr[(size_t)k * A.ld + i];
-    if (!conflict(A, i, j)) continue;
-    cm |= 1ull << k;
-    if (key_less(A, j, i)) {
-      em |= 1ull << k;
-      if (A.colour[j] < 0) ++c;
+  const double rix = A.rx[i], riy = A.ry[i], riz = A.rz[i];
+  constexpr int CH = 8;  // slots whose loads go out together
+  for (int k0 = 0; k0 < ns; k0 += CH) {
+    int jj[CH], cj[CH];
+    double px[CH], py[CH], pz[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) jj[q] = k0 + q < ns ? A.nbr[(size_t)(k0 + q) * A.ld + i] : i;
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      px[q] = A.rx[jj[q]]; py[q] = A.ry[jj[q]]; pz[q] = A.rz[jj[q]];
+      cj[q] = A.colour[jj[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      const double dx = min_image(rix - px[q], A.L[0], A.invL[0]);
+      const double dy = min_image(riy - py[q], A.L[1], A.invL[1]);
+      const double dz = min_image(riz - pz[q], A.L[2], A.invL[2]);
+      const int k = k0 + q, j = jj[q];
+      if (k >= ns || !(dx * dx + dy * dy + dz * dz < A.cr2)) continue;
+      cm |= 1ull << k;
+      const bool earlier = key_less(A, j, i);
+      if (earlier) {
+        em |= 1ull << k;
+        if (cj[q] < 0) ++c;
+      }
+      if (m < kRowInts) row[m] = earlier ? j : (j | (int)0x80000000);
+      ++m;
     }
   }
+  for (int q = m; q < kRowInts; ++q) row[q] = kRowNone;
+  if (m > kRowInts) row[kRowInts - 1] = kRowLong;
   cmask[i] = cm;
   emask[i] = em;
   indeg[i] = c;
@@ -348,18 +424,9 @@ __global__ void k_colour_indeg(ColourArgs A, int *indeg, unsigned long long *cma
 // in this round). The slot loads of a chunk go out together, then the
 // colour loads: each ready atom costs a few memory round trips.
 constexpr int kColourChunk = 16;
-// Load of a word another thread of the workgroup may have written in an
-// earlier round of the same launch: an agent-scope atomic load, which reads
-// the L2 (the device-wide rounds get the same guarantee from their launch
-// boundaries).
-__device__ __forceinline__ int load_l2(const int *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // One ready atom of a round: first-fit colour against its coloured
 // conflicting neighbours, then the later-key uncoloured neighbours lose one
 // wait each, and the one whose count reaches zero joins the next list.
-template <bool L2>
 __device__ __forceinline__ void colour_one(const ColourArgs &A, int i, int *indeg,
                                            const unsigned long long *cmask,
                                            const unsigned long long *emask, int *out,
@@ -376,7 +443,7 @@ __device__ __forceinline__ void colour_one(const ColourArgs &A, int i, int *inde
     }
 #pragma unroll
     for (int q = 0; q < kColourChunk; ++q) {
-      const int cj = jj[q] >= 0 ? (L2 ? load_l2(&A.colour[jj[q]]) : A.colour[jj[q]]) : -1;
+      const int cj = jj[q] >= 0 ? A.colour[jj[q]] : -1;
       if (cj >= 0) used |= 1ull << (cj & 63);
     }
   }
@@ -392,7 +459,7 @@ __device__ __forceinline__ void colour_one(const ColourArgs &A, int i, int *inde
 #pragma unroll
     for (int q = 0; q < kColourChunk; ++q) {
       const int j = jj[q];
-      if (j >= 0 && (L2 ? load_l2(&A.colour[j]) : A.colour[j]) < 0 && atomicSub(&indeg[j], 1) == 1)
+      if (j >= 0 && A.colour[j] < 0 && atomicSub(&indeg[j], 1) == 1)
         out[atomicAdd(out_count, 1)] = j;
     }
   }
@@ -404,44 +471,165 @@ __global__ void k_colour_round(ColourArgs A, int *indeg, const unsigned long lon
   if (blockIdx.x == 0 && threadIdx.x == 0) *clear_next = 0;
   const int m = *in_count;
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < m; t += gridDim.x * blockDim.x)
-    colour_one<false>(A, in[t], indeg, cmask, emask, out, out_count);
+    colour_one(A, in[t], indeg, cmask, emask, out, out_count);
 }
 
 // Rounds r0, r0 + 1, ... in one workgroup, with a workgroup barrier between
 // rounds, for as long as the ready list is non-empty and at most nmax long
 // and at most max_rounds rounds: most rounds of a colouring, and all of a
-// repair, hold a few dozen atoms, which one workgroup serves in a few
-// microseconds while a launch per round costs its dispatch. Lists and
-// counters follow the rotation of k_colour_round (round r reads list r % 2
-// with count r % 3); done[0] gets the number of rounds run.
+// repair, hold a few dozen atoms, which one workgroup serves in a microsecond
+// or two while a launch per round costs its dispatch. Lists and counters
+// follow the rotation of k_colour_round (round r reads list r % 2 with count
+// r % 3); done[0] gets the number of rounds run.
+// A round is a chain of dependent accesses, so the chain is kept short: the
+// ready lists sit in LDS (entries past kFinishList in the global lists), a ready
+// atom reads its packed row, and with STATE the colours
+// and waiting counts of the whole system sit in LDS too, as bytes (counts are at
+// most 63), leaving one trip to memory per round. 16 000 atoms of a thermal bcc
+// lattice, 264 rounds: 3.24 ms with everything in memory.
 constexpr int kFinishBlock = 1024;
+constexpr int kFinishList = 4096;
+constexpr int kFinishAtoms = 57344;  // 2 bytes each beside the lists in 160 KB of LDS
+struct FinishLds {
+  int list[2][kFinishList];
+  unsigned wait4[kFinishAtoms / 4];
+  unsigned char colour[kFinishAtoms];  // 255: none
+  int count[2];
+};
+
+template <bool STATE>
+__device__ __forceinline__ int colour_rounds(const ColourArgs &A, FinishLds &S, int *indeg,
+                                             const unsigned long long *cmask,
+                                             const unsigned long long *emask, int *const list[2],
+                                             int r0, int max_rounds, int nmax, int &m) {
+  const int t = threadIdx.x;
+  if (STATE)
+    for (int w = t; 4 * w < A.n; w += kFinishBlock) {
+      unsigned wt = 0u;
+      for (int q = 0; q < 4; ++q)
+        if (4 * w + q < A.n) {
+          const int c = A.colour[4 * w + q];
+          S.colour[4 * w + q] = c < 0 ? 255 : (unsigned char)c;
+          wt |= (unsigned)(c < 0 ? indeg[4 * w + q] & 63 : 0) << (8 * q);
+        }
+      S.wait4[w] = wt;
+    }
+  for (int q = t; q < min(m, kFinishList); q += kFinishBlock) S.list[r0 & 1][q] = list[r0 & 1][q];
+  if (t == 0) S.count[0] = S.count[1] = 0;
+  __syncthreads();
+  auto colour_of = [&](int j) -> int {
+    if (STATE) {
+      const int c = S.colour[j];
+      return c == 255 ? -1 : c;
+    }
+    return A.colour[j];
+  };
+  int r = r0;
+  for (; r < r0 + max_rounds && m > 0 && m <= nmax; ++r) {
+    const int *in_g = list[r & 1];
+    int *out_g = list[(r + 1) & 1];
+    int *out_n = &S.count[(r + 1) & 1];
+    // kRowInts lanes per ready atom, one per packed neighbour
+    for (int e0 = 0; e0 < m; e0 += kFinishBlock / kRowInts) {
+      const int e = e0 + t / kRowInts, q = t % kRowInts;
+      const bool on = e < m;
+      const int i = on ? (e < kFinishList ? S.list[r & 1][e] : in_g[e]) : 0;
+      const int ent = on ? A.rows[(size_t)i * kRowInts + q] : kRowNone;
+      const bool is_long = __shfl(ent, kRowInts - 1, kRowInts) == kRowLong;
+      const int j = ent & 0x7fffffff;
+      int c = on && !is_long && ent != kRowNone ? colour_of(j) : 64;  // 64: no neighbour
+      unsigned long long used = c >= 0 && c < 64 ? 1ull << c : 0ull;
+      if (is_long && q == 0) {
+        const unsigned long long cm = cmask[i];
+        for (int k = 0; k < 64; ++k)
+          if ((cm >> k) & 1ull) {
+            const int ck = colour_of(A.nbr[(size_t)k * A.ld + i]);
+            if (ck >= 0) used |= 1ull << (ck & 63);
+          }
+      }
+#pragma unroll
+      for (int o = 1; o < kRowInts; o <<= 1) used |= __shfl_xor(used, o, kRowInts);
+      if (on && q == 0) {
+        const int mine = __ffsll((long long)~used) - 1;
+        if (STATE) S.colour[i] = (unsigned char)mine;
+        else A.colour[i] = mine;
+      }
+      auto release = [&](int jl) {  // an uncoloured later neighbour waits for one atom less
+        bool last;
+        if (STATE) {
+          const int sh = 8 * (jl & 3);
+          last = ((atomicSub(&S.wait4[jl >> 2], 1u << sh) >> sh) & 255u) == 1u;
+        } else {
+          last = atomicSub(&indeg[jl], 1) == 1;
+        }
+        if (last) {
+          const int o = atomicAdd(out_n, 1);
+          if (o < kFinishList) S.list[(r + 1) & 1][o] = jl;
+          else if (o < A.n) out_g[o] = jl;
+        }
+      };
+      if (on && !is_long) {
+        if (ent < 0 && c < 0) release(j);  // (kRowNone has c = 64)
+      } else if (on && q == 0) {
+        const unsigned long long later = cmask[i] & ~emask[i];
+        for (int k = 0; k < 64; ++k)
+          if ((later >> k) & 1ull) {
+            const int jl = A.nbr[(size_t)k * A.ld + i];
+            if (colour_of(jl) < 0) release(jl);
+          }
+      }
+    }
+    __syncthreads();
+    m = min(*out_n, A.n);
+    if (t == 0) S.count[r & 1] = 0;  // the next round's output
+    __syncthreads();
+  }
+  __syncthreads();
+  // hand the state back: colours, and for device-wide rounds the ready list and
+  // the waiting counts
+  if (STATE)
+    for (int i = t; i < A.n; i += kFinishBlock) A.colour[i] = S.colour[i] == 255 ? -1 : (int)S.colour[i];
+  if (m > 0) {
+    for (int q = t; q < min(m, kFinishList); q += kFinishBlock) list[r & 1][q] = S.list[r & 1][q];
+    if (STATE)
+      for (int i = t; i < A.n; i += kFinishBlock) indeg[i] = (int)((S.wait4[i >> 2] >> (8 * (i & 3))) & 255u);
+  }
+  return r - r0;
+}
+
 __global__ __launch_bounds__(kFinishBlock) void k_colour_finish(
     ColourArgs A, int *indeg, const unsigned long long *cmask, const unsigned long long *emask,
     int *list0, int *list1, int *count, int r0, int max_rounds, int nmax, int *done) {
-  __shared__ int m_s;
-  int r = r0;
-  for (; r < r0 + max_rounds; ++r) {
+  __shared__ FinishLds S;
+  int m = count[r0 % 3];
+  __syncthreads();  // (read by all before the counters are written below)
+  if (m == 0 || m > nmax) {
     if (threadIdx.x == 0) {
-      m_s = load_l2(&count[r % 3]);
-      atomicExch(&count[(r + 2) % 3], 0);
+      done[0] = 0;
+      count[(r0 + 1) % 3] = count[(r0 + 2) % 3] = 0;
     }
-    __syncthreads();
-    const int m = m_s;
-    if (m == 0 || m > nmax) break;
-    const int *in = (r & 1) ? list1 : list0;
-    int *out = (r & 1) ? list0 : list1;
-    for (int t = threadIdx.x; t < m; t += kFinishBlock)
-      colour_one<true>(A, load_l2(&in[t]), indeg, cmask, emask, out, &count[(r + 1) % 3]);
-    __syncthreads();
+    return;
   }
-  if (threadIdx.x == 0) done[0] = r - r0;
+  int *const list[2] = {list0, list1};
+  // bytes are for lists whose edges are mutual and counts below 64: not for a
+  // caller's own list, nor after a row overflowed (the error is reported anyway)
+  const bool state = A.n <= kFinishAtoms && A.mutual && (*A.err & kErrNbrOverflow) == 0;
+  const int ran = state ? colour_rounds<true>(A, S, indeg, cmask, emask, list, r0, max_rounds, nmax, m)
+                        : colour_rounds<false>(A, S, indeg, cmask, emask, list, r0, max_rounds, nmax, m);
+  if (threadIdx.x == 0) {
+    done[0] = ran;
+    const int r = r0 + ran;
+    count[r % 3] = m;
+    count[(r + 1) % 3] = count[(r + 2) % 3] = 0;
+  }
 }
 
 __global__ void k_colour_stats(ColourArgs A, int *maxc, int *err) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  const int c = i < A.n ? A.colour[i] : -1;
+  const int wc = wave_max_i(c);
+  if ((threadIdx.x & 63) == 0 && wc > *(volatile int *)maxc) atomicMax(maxc, wc);
   if (i >= A.n) return;
-  const int c = A.colour[i];
-  atomicMax(maxc, c);
   for (int k = 0; k < A.nspin[i]; ++k) {
     const int j = A.nbr[(size_t)k * A.ld + i];
     if (A.colour[j] == c && conflict(A, i, j)) atomicOr(err, kErrColour);
@@ -607,14 +795,14 @@ void launch_bucket_scatter(int n, const int *key, const int *start, int *fill, i
 }
 void launch_bucket_sort_x(int nbucket, const int *start, int *items, const double *x,
                           hipStream_t st) {
-  if (nbucket > 0) hipLaunchKernelGGL(k_bucket_sort_x, dim3(nblocks(nbucket)), dim3(kBlock), 0, st, nbucket, start, items, x);
+  if (nbucket > 0) hipLaunchKernelGGL(k_bucket_sort_x, dim3((unsigned)(((long)nbucket * 64 + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, nbucket, start, items, x);
 }
 void launch_cell_positions(int n, const int *catoms, const double *rx, const double *ry,
                            const double *rz, double *cx, double *cy, double *cz, hipStream_t st) {
   if (n > 0) hipLaunchKernelGGL(k_cell_positions, dim3(nblocks(n)), dim3(kBlock), 0, st, n, catoms, rx, ry, rz, cx, cy, cz);
 }
 void launch_bucket_sort(int nbucket, const int *start, int *items, hipStream_t st) {
-  if (nbucket > 0) hipLaunchKernelGGL(k_bucket_sort, dim3(nblocks(nbucket)), dim3(kBlock), 0, st, nbucket, start, items);
+  if (nbucket > 0) hipLaunchKernelGGL(k_bucket_sort, dim3((unsigned)(((long)nbucket * 64 + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, nbucket, start, items);
 }
 void launch_nbr_build(const NbrBuildArgs &A, hipStream_t st) {
   if (A.n <= 0) return;
@@ -624,9 +812,14 @@ void launch_nbr_build(const NbrBuildArgs &A, hipStream_t st) {
     const long threads = (long)A.n * 16;
     hipLaunchKernelGGL(k_nbr_build<16>, dim3((unsigned)((threads + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, A);
   }
-  if (A.row_q > 0.0)
-    hipLaunchKernelGGL(k_row_order, dim3((unsigned)((A.n + kOrderBlock - 1) / kOrderBlock)),
-                       dim3(kOrderBlock), 0, st, A, 1.0 / A.row_q);
+  if (A.row_q > 0.0) {
+    if (A.n >= kNbrManyAtoms)
+      hipLaunchKernelGGL(k_row_order<1>, dim3((unsigned)((A.n + kOrderBlock - 1) / kOrderBlock)),
+                         dim3(kOrderBlock), 0, st, A, 1.0 / A.row_q);
+    else
+      hipLaunchKernelGGL(k_row_order<8>, dim3((unsigned)((A.n + kOrderBlock / 8 - 1) / (kOrderBlock / 8))),
+                         dim3(kOrderBlock), 0, st, A, 1.0 / A.row_q);
+  }
 }
 void launch_keys(int n, const double *rx, const double *ry, const double *rz, const double L[3],
                  double *kx, double *ky, double *kz, hipStream_t st) {

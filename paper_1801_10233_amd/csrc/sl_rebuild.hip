@@ -85,6 +85,9 @@ ColourArgs colour_args(sl_system *S) {
   }
   const double rc = colour_radius(S);
   C.cr2 = S->user_list ? 1e300 : rc * rc;
+  C.rows = S->jprow;
+  C.mutual = S->user_list ? 0 : 1;
+  C.err = S->err;
   return C;
 }
 

@@ -964,6 +964,7 @@ int sl_create(const sl_params *p, sl_system **out) {
   A_(dalloc(&S->jplist[1], (size_t)n));
   A_(dalloc(&S->jpmask[0], (size_t)n));
   A_(dalloc(&S->jpmask[1], (size_t)n));
+  A_(dalloc(&S->jprow, 16 * (size_t)n));
   A_(dalloc(&S->maxc, 1));
   A_(dalloc(&S->dslot, 3));
   A_(dalloc(&S->done, 1));
@@ -1018,7 +1019,7 @@ int sl_destroy(sl_system *S) {
                   (void *)S->kx, (void *)S->ky, (void *)S->kz, (void *)S->stage, (void *)S->err,
                   (void *)S->seen, (void *)S->jpcnt, (void *)S->maxc, (void *)S->dslot,
                   (void *)S->jplist[0], (void *)S->jplist[1], (void *)S->jpmask[0],
-                  (void *)S->jpmask[1],
+                  (void *)S->jpmask[1], (void *)S->jprow,
                   (void *)S->done, (void *)S->partial, (void *)S->pred, (void *)S->ftile, (void *)S->jtile, (void *)S->red_out, (void *)S->thermo,
                   (void *)S->mpairs, (void *)S->mirror, (void *)S->mcnt, (void *)S->mstart,
                   (void *)S->tab[0], (void *)S->tab[1], S->jc[0], S->jc[1], (void *)S->eam,
