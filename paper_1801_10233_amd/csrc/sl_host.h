@@ -394,6 +394,7 @@ ColourArgs colour_args(sl_system *S);
 int jp_rounds(sl_system *S, const ColourArgs &C);
 int mlp_pairs(sl_system *S);
 int colour_and_permute(sl_system *S, bool repair);
+int build_list(sl_system *S);
 int rebuild(sl_system *S);
 int ensure_ready(sl_system *S);
 

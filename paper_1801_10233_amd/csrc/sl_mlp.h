@@ -64,13 +64,15 @@ struct PairAdjArgs {
   float2 *shift;
 };
 void launch_pair_adjoint(const PairAdjArgs &A, hipStream_t st);
-void launch_sum_d(const double *x, int n, double *out, hipStream_t st);
-void launch_sum_f2(const float2 *x, int n, float4 *out, hipStream_t st);
+// part: scratch of kSumParts doubles (launch_sum_f2: kSumParts + 1 double2).
+constexpr int kSumParts = 256;
+void launch_sum_d(const double *x, int n, double *out, double *part, hipStream_t st);
+void launch_sum_f2(const float2 *x, int n, float4 *out, double2 *part, hipStream_t st);
 
 void launch_mlp_pair_count(int n, int ld, const int *nbr, const int *nall, int *cnt,
                            hipStream_t st);
-void launch_mlp_pair_fill(int n, int ld, const int *nbr, const int *nall, const int *start,
-                          int2 *pairs, int *mirror, int *err, hipStream_t st);
+void launch_mlp_pair_fill(int n, int ld, int max_row, const int *nbr, const int *nall,
+                          const int *start, int2 *pairs, int *mirror, int *err, hipStream_t st);
 void launch_mlp_swizzle(const float *p, MlpDevWeights *w, hipStream_t st);
 void launch_mlp_swizzle_t(const float *p, MlpDevWeightsT *w, hipStream_t st);
 // Reverse pass over P pairs: r[P] and raw output adjoints

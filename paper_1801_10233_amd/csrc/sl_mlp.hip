@@ -17,6 +17,7 @@
 // Layer 3 (2 outputs) is a VALU dot product plus one cross-half shuffle.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -324,25 +325,35 @@ __global__ void k_mlp_pair_count(int n, int ld, const int *nbr, const int *nall,
   cnt[i] = c;
 }
 
-__global__ void k_mlp_pair_fill(int n, int ld, const int *nbr, const int *nall, const int *start,
-                                int2 *pairs, int *mirror, int *err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+// One thread per list entry (blockIdx.y = slot): its place among the atom's
+// j > i entries, then the search of i in the row of j. (One thread per atom
+// walked the rows of all its neighbours one after another: 16 000 atoms 560 us.)
+__global__ __launch_bounds__(256) void k_mlp_pair_fill(int n, int ld, const int *nbr,
+                                                       const int *nall, const int *start,
+                                                       int2 *pairs, int *mirror, int *err) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
+  if (i >= n || k >= nall[i]) return;
+  const int j = nbr[(size_t)k * ld + i];
+  if (j <= i) return;
   int p = start[i];
-  for (int k = 0; k < nall[i]; ++k) {
-    const int j = nbr[(size_t)k * ld + i];
-    if (j <= i) continue;
-    int kk = -1;
-    for (int q = 0; q < nall[j]; ++q)
-      if (nbr[(size_t)q * ld + j] == i) { kk = q; break; }
-    if (kk < 0) {  // asymmetric list: cannot mirror
-      atomicOr(err, kErrNbrOverflow);
-      kk = k;
-    }
-    pairs[p] = make_int2(i, k);
-    mirror[p] = kk;
-    ++p;
+  for (int q = 0; q < k; ++q) p += nbr[(size_t)q * ld + i] > i;
+  int kk = -1;
+  const int nj = nall[j];
+  constexpr int CH = 8;  // entries whose loads go out together
+  for (int q0 = 0; q0 < nj && kk < 0; q0 += CH) {
+    int v[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) v[q] = q0 + q < nj ? nbr[(size_t)(q0 + q) * ld + j] : -1;
+#pragma unroll
+    for (int q = CH - 1; q >= 0; --q)
+      if (v[q] == i) kk = q0 + q;
   }
+  if (kk < 0) {  // asymmetric list: cannot mirror
+    atomicOr(err, kErrNbrOverflow);
+    kk = k;
+  }
+  pairs[p] = make_int2(i, k);
+  mirror[p] = kk;
 }
 
 void launch_mlp_pair_count(int n, int ld, const int *nbr, const int *nall, int *cnt,
@@ -350,9 +361,11 @@ void launch_mlp_pair_count(int n, int ld, const int *nbr, const int *nall, int *
   if (n > 0) hipLaunchKernelGGL(k_mlp_pair_count, dim3((n + 255) / 256), dim3(256), 0, st, n, ld, nbr, nall, cnt);
 }
 
-void launch_mlp_pair_fill(int n, int ld, const int *nbr, const int *nall, const int *start,
-                          int2 *pairs, int *mirror, int *err, hipStream_t st) {
-  if (n > 0) hipLaunchKernelGGL(k_mlp_pair_fill, dim3((n + 255) / 256), dim3(256), 0, st, n, ld, nbr, nall, start, pairs, mirror, err);
+void launch_mlp_pair_fill(int n, int ld, int max_row, const int *nbr, const int *nall,
+                          const int *start, int2 *pairs, int *mirror, int *err, hipStream_t st) {
+  if (n > 0 && max_row > 0)
+    hipLaunchKernelGGL(k_mlp_pair_fill, dim3((n + 255) / 256, max_row), dim3(256), 0, st, n, ld, nbr,
+                       nall, start, pairs, mirror, err);
 }
 
 }  // namespace sl
@@ -609,18 +622,43 @@ void launch_mlp_backward(const float *r, const float4 *ybar, int P, const MlpDev
                      wt, c, partial);
 }
 
-// grad[q] (+)= sum over waves of partial[w][q], in wave order.
-__global__ void k_mlp_grad_reduce(const float *partial, int nwave, float *grad, int acc) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= 5378) return;
+// grad[q] (+)= sum over waves of partial[w][q], in wave order (a gradient is a
+// small difference of large terms, so another order of the FP32 sum moves its
+// fifth digit). A block takes 64 parameters: its 16 wavefronts load kGradRows
+// rows at a time into LDS, and the first adds them in order while the next rows
+// are on their way. (One thread per parameter read the 2048 rows one after
+// another: 480 us; this 25.)
+constexpr int kGradParams = 5378, kGradRows = 128;
+__global__ __launch_bounds__(1024) void k_mlp_grad_reduce(const float *partial, int nwave, float *grad,
+                                                          int acc) {
+  __shared__ float buf[2][kGradRows][64];
+  constexpr int kPer = kGradRows / 16;  // rows of one wavefront per batch
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int q = blockIdx.x * 64 + lane;
+  const bool on = q < kGradParams;
+  const int nb = (nwave + kGradRows - 1) / kGradRows;
   float s = 0.f;
-  for (int w = 0; w < nwave; ++w) s += partial[(size_t)w * 5378 + q];
-  grad[q] = acc ? grad[q] + s : s;
+  for (int b = 0; b <= nb; ++b) {
+    float v[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      const int w = b * kGradRows + wv * kPer + r;
+      v[r] = on && w < nwave ? partial[(size_t)w * kGradParams + q] : 0.f;
+    }
+    if (b > 0 && wv == 0) {
+      const int m = min(kGradRows, nwave - (b - 1) * kGradRows);
+      for (int r = 0; r < m; ++r) s += buf[(b - 1) & 1][r][lane];
+    }
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) buf[b & 1][wv * kPer + r][lane] = v[r];
+    __syncthreads();
+  }
+  if (wv == 0 && on) grad[q] = acc ? grad[q] + s : s;
 }
 
 void launch_mlp_grad_reduce(const float *partial, int nwave, float *grad, int accumulate,
                             hipStream_t st) {
-  hipLaunchKernelGGL(k_mlp_grad_reduce, dim3((5378 + 255) / 256), dim3(256), 0, st, partial, nwave,
+  hipLaunchKernelGGL(k_mlp_grad_reduce, dim3((kGradParams + 63) / 64), dim3(1024), 0, st, partial, nwave,
                      grad, accumulate);
 }
 
@@ -653,15 +691,22 @@ namespace sl {
 // learned-potential table; with references, also the loss residual terms:
 //   gF_i = 2 wF (F_i - Fref_i)/(3N),  gW_i = 2 wW (hw_i - hwref_i)/(3N),
 //   lossp_i = [wF |F_i - Fref_i|^2 + wW |hw_i - hwref_i|^2]/(3N).
-template <typename real, int MLP>
-__global__ void k_fields(SysView<real> S, PotConst P, FieldArgs A) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= S.n) return;
+// WAVES wavefronts share 64 atoms (wavefront w the slots w, w + WAVES, ..., joined
+// in LDS): a row is a chain of dependent loads, exponentials and divisions, which a
+// small system cannot hide (16 000 atoms with one lane per atom: 81 us).
+template <typename real, int MLP, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_fields(SysView<real> S, PotConst P, FieldArgs A) {
+  __shared__ double part[WAVES > 1 ? WAVES - 1 : 1][7][64];
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const int i0 = blockIdx.x * 64 + lane;
+  const bool valid = i0 < S.n;
+  const int i = valid ? i0 : 0;
+  const int na = valid ? S.nall[i] : 0;
   const double rix = S.rx[i], riy = S.ry[i], riz = S.rz[i];
   const double six = S.sx[i], siy = S.sy[i], siz = S.sz[i];
   double f[3] = {0, 0, 0}, hw[3] = {0, 0, 0}, e = 0.0;
   const int ld = S.ld;
-  for (int k = 0; k < S.nall[i]; ++k) {
+  for (int k = w; k < na; k += WAVES) {
     const int j = S.nbr[(size_t)k * ld + i];
     const double dx = min_image(rix - S.rx[j], S.L[0], S.invL[0]);
     const double dy = min_image(riy - S.ry[j], S.L[1], S.invL[1]);
@@ -712,6 +757,19 @@ __global__ void k_fields(SysView<real> S, PotConst P, FieldArgs A) {
       e += 0.5 * soc_force<double>(P, dx, dy, dz, r2, six, siy, siz, sjx, sjy, sjz, f[0], f[1], f[2]);
     }
   }
+  if (WAVES > 1) {
+    if (w > 0) {
+      for (int c = 0; c < 3; ++c) { part[w - 1][c][lane] = f[c]; part[w - 1][3 + c][lane] = hw[c]; }
+      part[w - 1][6][lane] = e;
+    }
+    __syncthreads();
+    if (w == 0)
+      for (int q = 0; q < WAVES - 1; ++q) {
+        for (int c = 0; c < 3; ++c) { f[c] += part[q][c][lane]; hw[c] += part[q][3 + c][lane]; }
+        e += part[q][6][lane];
+      }
+  }
+  if (!valid || w > 0) return;
   const size_t n = S.n;
   if (!MLP && P.eam_on) e += S.eam[(size_t)S.ld + i];
   if (A.ts) {
@@ -777,24 +835,30 @@ __global__ void k_pair_adjoint(PairAdjArgs A) {
   A.shift[p] = sh;
 }
 
-// Fixed-order sums (one block): out[0] = sum of x (double), or of a float2.
-__global__ __launch_bounds__(256) void k_sum_d(const double *x, int n, double *out) {
+// Fixed-order sums: block b adds the terms of its slice into part[b]; with one
+// block that is the sum, else the same launch over the parts finishes it. (A
+// single block took 417 us for the 464 000 pairs of a 16 000-atom snapshot.)
+__global__ __launch_bounds__(256) void k_sum_d(const double *x, int n, double *part) {
   __shared__ double b[256];
+  const long n0 = (long)n * blockIdx.x / gridDim.x, n1 = (long)n * (blockIdx.x + 1) / gridDim.x;
   double s = 0.0;
-  for (int k = threadIdx.x; k < n; k += 256) s += x[k];
+  for (long k = n0 + threadIdx.x; k < n1; k += 256) s += x[k];
   b[threadIdx.x] = s;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) b[threadIdx.x] += b[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = b[0];
+  if (threadIdx.x == 0) part[blockIdx.x] = b[0];
 }
 
-__global__ __launch_bounds__(256) void k_sum_f2(const float2 *x, int n, float4 *out) {
+// The same for pairs of floats, summed in FP64: part[b] = (sum x, sum y).
+template <typename pair>
+__global__ __launch_bounds__(256) void k_sum_2(const pair *x, int n, double2 *part) {
   __shared__ double b0[256], b1[256];
+  const long n0 = (long)n * blockIdx.x / gridDim.x, n1 = (long)n * (blockIdx.x + 1) / gridDim.x;
   double s0 = 0.0, s1 = 0.0;
-  for (int k = threadIdx.x; k < n; k += 256) { s0 += x[k].x; s1 += x[k].y; }
+  for (long k = n0 + threadIdx.x; k < n1; k += 256) { s0 += x[k].x; s1 += x[k].y; }
   b0[threadIdx.x] = s0;
   b1[threadIdx.x] = s1;
   __syncthreads();
@@ -802,16 +866,26 @@ __global__ __launch_bounds__(256) void k_sum_f2(const float2 *x, int n, float4 *
     if ((int)threadIdx.x < w) { b0[threadIdx.x] += b0[threadIdx.x + w]; b1[threadIdx.x] += b1[threadIdx.x + w]; }
     __syncthreads();
   }
-  // raw adjoints of the single point r = rc: (0, 0, dL/dy1(rc), dL/dy1'(rc))
-  if (threadIdx.x == 0) *out = make_float4(0.f, 0.f, (float)b0[0], (float)b1[0]);
+  if (threadIdx.x == 0) part[blockIdx.x] = make_double2(b0[0], b1[0]);
+}
+// raw adjoints of the single point r = rc: (0, 0, dL/dy1(rc), dL/dy1'(rc))
+__global__ void k_shift_adjoint(const double2 *s, float4 *out) {
+  *out = make_float4(0.f, 0.f, (float)s->x, (float)s->y);
 }
 
+template <typename real, int MLP>
+static void fields_run(const SysView<real> &S, const PotConst &P, const FieldArgs &A, hipStream_t st) {
+  const int nb = (S.n + 63) / 64;
+  // (432 000 atoms fill the device with one wavefront per 64 atoms)
+  if (S.n <= 120000) hipLaunchKernelGGL((k_fields<real, MLP, 8>), dim3(nb), dim3(512), 0, st, S, P, A);
+  else hipLaunchKernelGGL((k_fields<real, MLP, 1>), dim3(nb), dim3(64), 0, st, S, P, A);
+}
 template <typename real>
 void launch_fields(const SysView<real> &S, const PotConst &P, const FieldArgs &A, hipStream_t st) {
-  const int nb = (S.n + 255) / 256;
-  if (sizeof(real) == 4 && S.spl.t) hipLaunchKernelGGL((k_fields<real, (sizeof(real) == 4 ? 2 : 0)>), dim3(nb), dim3(256), 0, st, S, P, A);
-  else if (sizeof(real) == 4 && S.tab) hipLaunchKernelGGL((k_fields<real, (sizeof(real) == 4 ? 1 : 0)>), dim3(nb), dim3(256), 0, st, S, P, A);
-  else hipLaunchKernelGGL((k_fields<real, 0>), dim3(nb), dim3(256), 0, st, S, P, A);
+  if (S.n <= 0) return;
+  if (sizeof(real) == 4 && S.spl.t) fields_run<real, (sizeof(real) == 4 ? 2 : 0)>(S, P, A, st);
+  else if (sizeof(real) == 4 && S.tab) fields_run<real, (sizeof(real) == 4 ? 1 : 0)>(S, P, A, st);
+  else fields_run<real, 0>(S, P, A, st);
 }
 template void launch_fields<double>(const SysView<double> &, const PotConst &, const FieldArgs &, hipStream_t);
 template void launch_fields<float>(const SysView<float> &, const PotConst &, const FieldArgs &, hipStream_t);
@@ -819,11 +893,17 @@ template void launch_fields<float>(const SysView<float> &, const PotConst &, con
 void launch_pair_adjoint(const PairAdjArgs &A, hipStream_t st) {
   if (A.npair > 0) hipLaunchKernelGGL(k_pair_adjoint, dim3((A.npair + 255) / 256), dim3(256), 0, st, A);
 }
-void launch_sum_d(const double *x, int n, double *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_sum_d, dim3(1), dim3(256), 0, st, x, n, out);
+static int sum_blocks(int n) { return n < 8192 ? 1 : std::min(kSumParts, n / 2048); }
+void launch_sum_d(const double *x, int n, double *out, double *part, hipStream_t st) {
+  const int nb = sum_blocks(n);
+  hipLaunchKernelGGL(k_sum_d, dim3(nb), dim3(256), 0, st, x, n, nb == 1 ? out : part);
+  if (nb > 1) hipLaunchKernelGGL(k_sum_d, dim3(1), dim3(256), 0, st, part, nb, out);
 }
-void launch_sum_f2(const float2 *x, int n, float4 *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_sum_f2, dim3(1), dim3(256), 0, st, x, n, out);
+void launch_sum_f2(const float2 *x, int n, float4 *out, double2 *part, hipStream_t st) {
+  const int nb = sum_blocks(n);
+  hipLaunchKernelGGL((k_sum_2<float2>), dim3(nb), dim3(256), 0, st, x, n, part);
+  if (nb > 1) hipLaunchKernelGGL((k_sum_2<double2>), dim3(1), dim3(256), 0, st, part, nb, part + kSumParts);
+  hipLaunchKernelGGL(k_shift_adjoint, dim3(1), dim3(1), 0, st, nb > 1 ? part + kSumParts : part, out);
 }
 
 }  // namespace sl

@@ -82,7 +82,7 @@ int sl_mlp_destroy(sl_mlp *m) {
   if (m->trainer) sl_destroy(m->trainer);
   for (void *p : {(void *)m->master, (void *)m->w, (void *)m->yc, (void *)m->scratch4,
                   (void *)m->wt, (void *)m->grad, (void *)m->adam_m, (void *)m->adam_v,
-                  (void *)m->spl})
+                  (void *)m->spl, m->work})
     if (p) (void)hipFree(p);
   if (m->own_stream && m->st) (void)hipStreamDestroy(m->st);
   delete m;

@@ -18,6 +18,8 @@ struct sl_mlp {
   float *grad = nullptr, *adam_m = nullptr, *adam_v = nullptr;
   int64_t adam_t = 0;
   struct sl_system *trainer = nullptr;  // geometry of the training snapshots
+  void *work = nullptr;                 // buffers of one loss and gradient, kept
+  size_t work_bytes = 0;
   bool have_weights = false;
   // raw outputs tabulated for the spline form of the dynamics
   static constexpr int kSplinePoints = 4096;

@@ -151,7 +151,8 @@ int mlp_pairs(sl_system *S) {
     HIPCHK(S, dalloc(&S->mpairs, S->mpair_cap));
     HIPCHK(S, dalloc(&S->mirror, S->mpair_cap));
   }
-  launch_mlp_pair_fill(n, S->ld, A.nbr, A.nall, S->mstart, S->mpairs, S->mirror, S->err, S->st);
+  launch_mlp_pair_fill(n, S->ld, S->max_nbr, A.nbr, A.nall, S->mstart, S->mpairs, S->mirror, S->err,
+                       S->st);
   S->npair = tot;
   S->tab_ok[0] = S->tab_ok[1] = false;
   return SL_OK;
@@ -284,9 +285,10 @@ int colour_and_permute(sl_system *S, bool repair) {
   return SL_OK;
 }
 
-// Full rebuild at the current boundary: cells, lists, colour repair, order.
-int rebuild(sl_system *S) {
-  if (S->user_list) return colour_and_permute(S, false);
+// Cells and neighbour list at the current positions. The build's error word and
+// largest rows stay on the device: they are read back with the colouring's report
+// (one host synchronisation for both), or by a caller that needs no colours.
+int build_list(sl_system *S) {
   CHK(check_box(S));
   {
     ProfScope ps(S, 2, (double)S->n);
@@ -325,12 +327,17 @@ int rebuild(sl_system *S) {
     B.row_q = S->row_q;
     HIPCHK(S, hipMemsetAsync(S->seen, 0, 2 * sizeof(int), S->st));
     launch_nbr_build(B, S->st);
-    // the build's error word and largest rows are read back with the
-    // colouring's report (one host synchronisation for both); an
-    // overflowing row only truncates what the colouring sees meanwhile
+    // (an overflowing row only truncates what the colouring sees meanwhile)
   }
   S->have_list = true;
   S->rebuilds++;
+  return SL_OK;
+}
+
+// Full rebuild at the current boundary: cells, lists, colour repair, order.
+int rebuild(sl_system *S) {
+  if (S->user_list) return colour_and_permute(S, false);
+  CHK(build_list(S));
   return colour_and_permute(S, true);
 }
 

@@ -869,15 +869,16 @@ int temps_now(sl_system *S, double *TL, double *TS) {
   }
   if (TS) {
     double *ts = nullptr;
-    HIPCHK(S, dalloc(&ts, 2 * (size_t)n + 2));
+    HIPCHK(S, dalloc(&ts, 2 * (size_t)n + 2 + kSumParts));
     CHK(ensure_table(S, S->pos));
     FieldArgs A;
     std::memset(&A, 0, sizeof(A));
     A.ts = ts;
     launch_eam_density<real>(view<real>(S, S->pos), S->pc, S->st);
     launch_fields<real>(view<real>(S, S->pos), S->pc, A, S->st);
-    launch_sum_d(ts, n, ts + 2 * (size_t)n, S->st);
-    launch_sum_d(ts + n, n, ts + 2 * (size_t)n + 1, S->st);
+    double *sums = ts + 2 * (size_t)n, *part = sums + 2;
+    launch_sum_d(ts, n, sums, part, S->st);
+    launch_sum_d(ts + n, n, sums + 1, part, S->st);
     double h[2] = {0.0, 0.0};
     hipError_t e1 = hipMemcpyAsync(h, ts + 2 * (size_t)n, 2 * sizeof(double), hipMemcpyDeviceToHost, S->st);
     hipError_t e2 = e1 == hipSuccess ? hipStreamSynchronize(S->st) : e1;

@@ -63,36 +63,51 @@ int sl_mlp_loss_grad(sl_mlp *m, const sl_dataset *d, int snap, const double w[3]
   sl_system *S = m->trainer;
   const int n = S->n;
   const size_t off = (size_t)snap * n * 3;
-  std::vector<double> zeros(3 * (size_t)n, 0.0), ones(n, 1.0);
-  int rc = sl_set_state(S, d->r + off, zeros.data(), d->s + off, ones.data(), SL_HOST);
+  int rc;
+  if (!S->have_state) {
+    const std::vector<double> zeros(3 * (size_t)n, 0.0), ones(n, 1.0);
+    rc = sl_set_state(S, d->r + off, zeros.data(), d->s + off, ones.data(), SL_HOST);
+  } else {  // (the snapshots have no velocities or masses)
+    rc = sl_set_state(S, d->r + off, nullptr, d->s + off, nullptr, SL_HOST);
+  }
   if (rc) return mfail_str(m, rc, std::string("snapshot state: ") + S->last_err);
   rc = sl_set_mlp(S, m);
   if (rc) return mfail_str(m, rc, S->last_err);
-  rc = ensure_ready(S);
-  if (rc) return mfail_str(m, rc, S->last_err);
-  rc = ensure_table(S, S->pos);
+  // A loss needs the list and its pairs, in any atom order: no colour classes (a
+  // colouring of 16 000 atoms took longer than all else here) and no permutation
+  rc = build_list(S);
+  if (!rc) rc = mlp_pairs(S);
+  if (!rc) rc = read_err(S);
+  if (!rc) rc = sticky_code(S);
+  if (!rc) rc = ensure_table(S, S->pos);
   if (rc) return mfail_str(m, rc, S->last_err);
   // references in internal order
   Atoms &A = S->a[S->cur];
-  double *ref = nullptr, *out = nullptr;
-  float *gbuf = nullptr, *rp = nullptr, *part = nullptr;
-  float4 *yb = nullptr, *s4 = nullptr;
-  float2 *sh = nullptr;
   const int P = S->npair;
   const int nw = mlp_backward_waves(P);
-  auto cleanup = [&]() {
-    for (void *q : {(void *)ref, (void *)out, (void *)gbuf, (void *)rp, (void *)part, (void *)yb, (void *)s4, (void *)sh})
-      dfree(q);
-  };
-#define TCHK(x) do { hipError_t e_ = (x); if (e_ != hipSuccess) { cleanup(); return mfail_str(m, SL_E_HIP, std::string(#x) + ": " + hipGetErrorString(e_)); } } while (0)
-  TCHK(dalloc(&ref, 6 * (size_t)n));
-  TCHK(dalloc(&out, 8 * (size_t)n + 8));
-  TCHK(dalloc(&gbuf, 6 * (size_t)n));
-  TCHK(dalloc(&rp, (size_t)P + 1));
-  TCHK(dalloc(&yb, (size_t)P + 1));
-  TCHK(dalloc(&sh, (size_t)P + 1));
-  TCHK(dalloc(&s4, 4));
-  TCHK(dalloc(&part, (size_t)nw * SL_MLP_NPARAM));
+#define TCHK(x) do { hipError_t e_ = (x); if (e_ != hipSuccess) return mfail_str(m, SL_E_HIP, std::string(#x) + ": " + hipGetErrorString(e_)); } while (0)
+  // one buffer, kept by the handle and grown as needed
+  size_t used = 0;
+  auto take = [&](size_t bytes) { const size_t o = used; used += (bytes + 255) / 256 * 256; return o; };
+  const size_t o_ref = take(sizeof(double) * 6 * n), o_out = take(sizeof(double) * (8 * (size_t)n + 8 + kSumParts)),
+               o_gbuf = take(sizeof(float) * 6 * n), o_rp = take(sizeof(float) * ((size_t)P + 1)),
+               o_yb = take(sizeof(float4) * ((size_t)P + 1)), o_sh = take(sizeof(float2) * ((size_t)P + 1)),
+               o_s4 = take(sizeof(float4) * 4), o_p2 = take(sizeof(double2) * (kSumParts + 1)),
+               o_part = take(sizeof(float) * (size_t)nw * SL_MLP_NPARAM);
+  if (used > m->work_bytes) {
+    if (m->work) (void)hipFree(m->work);
+    m->work = nullptr;
+    m->work_bytes = 0;
+    TCHK(hipMalloc(&m->work, used));
+    m->work_bytes = used;
+  }
+  char *const base = (char *)m->work;
+  double *const ref = (double *)(base + o_ref), *const out = (double *)(base + o_out);
+  float *const gbuf = (float *)(base + o_gbuf), *const rp = (float *)(base + o_rp);
+  float *const part = (float *)(base + o_part);
+  float4 *const yb = (float4 *)(base + o_yb), *const s4 = (float4 *)(base + o_s4);
+  float2 *const sh = (float2 *)(base + o_sh);
+  double2 *const part2 = (double2 *)(base + o_p2);
   for (int q = 0; q < 2; ++q) {
     const double *src = (q ? d->hw : d->F) + off;
     TCHK(hipMemcpyAsync(S->stage, src, sizeof(double) * 3 * n, hipMemcpyHostToDevice, S->st));
@@ -111,8 +126,8 @@ int sl_mlp_loss_grad(sl_mlp *m, const sl_dataset *d, int snap, const double w[3]
   Fa.gW = gbuf + 3 * (size_t)n;
   Fa.lossp = lossp;
   launch_fields<float>(view<float>(S, S->pos), S->pc, Fa, S->st);
-  launch_sum_d(e_at, n, sums, S->st);
-  launch_sum_d(lossp, n, sums + 1, S->st);
+  launch_sum_d(e_at, n, sums, sums + 8, S->st);
+  launch_sum_d(lossp, n, sums + 1, sums + 8, S->st);
   double hs[2];
   TCHK(hipMemcpyAsync(hs, sums, sizeof(hs), hipMemcpyDeviceToHost, S->st));
   TCHK(hipStreamSynchronize(S->st));
@@ -150,7 +165,7 @@ int sl_mlp_loss_grad(sl_mlp *m, const sl_dataset *d, int snap, const double w[3]
     launch_mlp_backward(rp, yb, P, m->w, m->wt, m->cfg(), part, S->st);
     launch_mlp_grad_reduce(part, nw, m->grad, 0, S->st);
     // the shifted-force constants y1(rc), y1'(rc): one more point
-    launch_sum_f2(sh, P, s4, S->st);
+    launch_sum_f2(sh, P, s4, part2, S->st);
     float rcf = (float)m->rc;
     TCHK(hipMemcpyAsync(rp + P, &rcf, sizeof(float), hipMemcpyHostToDevice, S->st));
     launch_mlp_backward(rp + P, s4, 1, m->w, m->wt, m->cfg(), part, S->st);
@@ -159,7 +174,6 @@ int sl_mlp_loss_grad(sl_mlp *m, const sl_dataset *d, int snap, const double w[3]
     TCHK(hipStreamSynchronize(S->st));
   }
 #undef TCHK
-  cleanup();
   return SL_OK;
 }
 
