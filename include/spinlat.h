@@ -295,8 +295,9 @@ int sl_synchronize(sl_system *sys);
  * differ at most by summation-order roundoff. lanes = 1, 2, 4 or 8 lanes
  * cooperate on one atom. 0 = default: in the spin phase chosen per class from
  * its size, in the force launch from the number of atoms (a value set there is
- * the least number taken; a system too small to fill the device takes more);
- * sl_get_tuning reports the defaults as 2 and 1.
+ * the least number taken; a system too small to fill the device takes more),
+ * and the spin half-steps of a system of a few thousand atoms in one workgroup
+ * (spin_lanes and jcache both 0). sl_get_tuning reports the defaults as 2 and 1.
  * Runs of consecutive colour classes of at most small_class atoms each are
  * applied by one single-workgroup launch (0 = default 128, -1 = never). */
 typedef struct {
@@ -323,7 +324,8 @@ int sl_get_tuning(sl_system *sys, sl_tuning *t);
 
 /* Autotuner. Runs windows of `steps` steps of length dt under each
  * candidate launch shape (spin lanes 1, 2, 4, 8; force lanes 1, 2; the
- * exchange-coefficient cache on or off) on a scratch copy of the system
+ * exchange-coefficient cache on or off; the default, where it runs the spin
+ * half-steps in one workgroup) on a scratch copy of the system
  * (same parameters, interactions, learned potential, user list, state and
  * step counter; its own stream and memory, freed before returning), times
  * each whole window with HIP events on the copy's stream (a window with a

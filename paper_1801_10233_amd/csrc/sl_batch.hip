@@ -5,6 +5,42 @@
 
 namespace sl {
 
+// A replica's descriptor does not change while a launch of the phase mode runs.
+// Read as constant memory its pointers are known to be global ones; otherwise
+// their address space is unknown and every access is a flat one, which also
+// waits for LDS.
+template <typename T>
+using Const4 = const __attribute__((address_space(4))) T;
+template <typename real>
+__device__ __forceinline__ SysView<real> rep_view(const RepDesc<real> *d, int pos) {
+  Const4<SysView<real>> *s = (Const4<SysView<real>> *)&d->V[pos];
+  SysView<real> V = d->V[pos];
+  V.rx = s->rx; V.ry = s->ry; V.rz = s->rz;
+  V.sx = s->sx; V.sy = s->sy; V.sz = s->sz;
+  V.nbr = s->nbr;
+  V.nspin = s->nspin;
+  V.nall = s->nall;
+  V.id = s->id;
+  V.eam = s->eam;
+  return V;
+}
+template <typename real>
+__device__ __forceinline__ ForceArgs rep_force_args(const RepDesc<real> *d, int next) {
+  Const4<ForceArgs> *s = (Const4<ForceArgs> *)&d->F;
+  Const4<SysView<real>> *v = (Const4<SysView<real>> *)&d->V[next];
+  ForceArgs F = d->F;
+  F.mass = s->mass;
+  F.vx = s->vx; F.vy = s->vy; F.vz = s->vz;
+  F.bx = s->bx; F.by = s->by; F.bz = s->bz;
+  F.wmask = s->wmask;
+  F.err = s->err;
+  F.pred = s->pred;
+  F.nx = const_cast<double *>(v->rx);
+  F.ny = const_cast<double *>(v->ry);
+  F.nz = const_cast<double *>(v->rz);
+  return F;
+}
+
 // ---------------------------------------------------------------------------
 // Batched replicas in one persistent launch: workgroup b owns replica b and
 // runs its steps one after another -- the colour classes of both spin
@@ -174,8 +210,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_spin(const RepDesc<real> *D, B
   const int64_t step = d.step + bp.kk;
   const int64_t st[kMaxRep] = {step, step, step, step};
   const int sb[kMaxRep] = {subf, subf + 1, 0, 0};
-  spin_update<real, true, true, WAVES, MLP>(d.V[bp.half == 0 ? pos : 1 - pos], d.P, i, i < b1,
-                                             w, team + t, nrep, st, sb, d.h, d.amp, d.seed,
+  const SysView<real> V = rep_view(&d, bp.half == 0 ? pos : 1 - pos);
+  const PotConst P = d.P;
+  spin_update<real, true, true, WAVES, MLP>(V, P, i, i < b1, w, team + t, nrep, st, sb, d.h, d.amp, d.seed,
                                              d.replica, d.rs2);
 }
 
@@ -183,28 +220,54 @@ __global__ __launch_bounds__(kBlock) void k_batch_spin(const RepDesc<real> *D, B
 // back, with workgroup barriers between them (a launch of its own costs a class
 // of a few hundred atoms more than its turn here).
 constexpr int kBatchTailWaves = 4;
+template <typename real>
+struct BatchTailSeq {
+  const RepDesc<real> &d;
+  int m, half, q, base;
+  int64_t k;
+  __device__ int cls() const { return d.nbig + (q < m ? q : 2 * m - 2 - q); }
+  __device__ bool more() const { return q < 2 * m - 1; }
+  __device__ int begin() const { return base; }
+  __device__ int end() const { return d.off[cls() + 1]; }
+  __device__ int nrep() const { return q == m - 1 ? 2 : 1; }
+  __device__ int64_t step(int) const { return k; }
+  __device__ int sub(int r) const { return 2 * half + (q < m ? r : 1); }
+  __device__ const float4 *tab(const SysView<real> &S) const { return S.tab; }
+  __device__ const real *jc(const SysView<real> &S) const { return S.jc; }
+  __device__ void advance() {
+    base += kBatchBlock / kBatchTailWaves;
+    if (base >= end() && ++q < 2 * m - 1) base = d.off[cls()];
+  }
+  __device__ BatchTailSeq(const RepDesc<real> &r, const BatchPhase &bp)
+      : d(r), m(r.K - r.nbig), half(bp.half), q(0), base(r.off[r.nbig]), k(r.step + bp.kk) {}
+  __device__ BatchTailSeq(const BatchTailSeq &o) = default;
+  __device__ BatchTailSeq &operator=(const BatchTailSeq &o) {
+    q = o.q;
+    base = o.base;
+    return *this;
+  }
+};
 template <typename real, int MLP>
 __global__ __launch_bounds__(kBatchBlock) void k_batch_tail(const RepDesc<real> *D, BatchPhase bp,
                                                             const int2 *reps) {
   constexpr int kTeams = kBatchBlock / 64 / kBatchTailWaves;
   __shared__ SpinTeam<real, kBatchTailWaves> team[kTeams];
   const RepDesc<real> &d = D[reps[blockIdx.x].x];
-  const int t = wave_id() / kBatchTailWaves, w = wave_id() % kBatchTailWaves;
-  const int K = d.K, nbig = d.nbig, m = K - nbig;
+  const BatchTailSeq<real> seq(d, bp);
   const int pos = d.pos ^ (bp.kk & 1);
-  const int64_t step = d.step + bp.kk;
-  const int64_t st[kMaxRep] = {step, step, step, step};
-  const SysView<real> &V = d.V[bp.half == 0 ? pos : 1 - pos];
-  for (int q = 0; q < 2 * m - 1; ++q) {
-    const int c = nbig + (q < m ? q : 2 * m - 2 - q);
-    const int s0 = 2 * bp.half + (q < m ? 0 : 1);
-    const int sb[kMaxRep] = {s0, s0 + 1, 0, 0};
-    const int nrep = q == m - 1 ? 2 : 1;
-    const int b0 = d.off[c], b1 = d.off[c + 1];
-    for (int base = b0; base < b1; base += 64 * kTeams) {
-      const int i = base + 64 * t + (int)(threadIdx.x & 63);
-      spin_update<real, true, true, kBatchTailWaves, MLP>(V, d.P, i, i < b1, w, team + t, nrep, st, sb,
-                                                          d.h, d.amp, d.seed, d.replica, d.rs2);
+  const SysView<real> V = rep_view(&d, bp.half == 0 ? pos : 1 - pos);
+  const PotConst P = d.P;
+  if constexpr (MLP != 4) {
+    spin_sequence<real, true, true, kBatchTailWaves, kTeams, MLP>(seq, V, P, V.sx, V.sy, V.sz, team, d.h, d.amp,
+                                                                  d.seed, d.replica, d.rs2);
+  } else {
+    const int t = wave_id() / kBatchTailWaves, w = wave_id() % kBatchTailWaves;
+    for (BatchTailSeq<real> s = seq; s.more(); s.advance()) {
+      const int i = s.begin() + 64 * t + (int)(threadIdx.x & 63);
+      const int64_t st[kMaxRep] = {s.step(0), s.step(0), 0, 0};
+      const int sb[kMaxRep] = {s.sub(0), s.sub(1), 0, 0};
+      spin_update<real, true, true, kBatchTailWaves, MLP>(V, P, i, i < s.end(), w, team + t, s.nrep(),
+                                                          st, sb, d.h, d.amp, d.seed, d.replica, d.rs2);
       __syncthreads();
     }
   }
@@ -226,16 +289,15 @@ __global__ __launch_bounds__(kBlock) void k_batch_force(const RepDesc<real> *D, 
   // buffer holding this boundary's positions; the drift goes to the other
   const int cur = bp.after ? 1 - (d.pos ^ (bp.kk & 1)) : d.pos;
   const int64_t boundary = d.step + bp.kk + bp.after;
-  ForceArgs F = d.F;
+  const SysView<real> V = rep_view(&d, cur);
+  const PotConst P = d.P;
+  ForceArgs F = rep_force_args(&d, 1 - cur);
   F.dt = d.dt;
   F.step = boundary;
-  F.nx = const_cast<double *>(d.V[1 - cur].rx);
-  F.ny = const_cast<double *>(d.V[1 - cur].ry);
-  F.nz = const_cast<double *>(d.V[1 - cur].rz);
   F.host_out = d.ring + 8 * (int)(boundary & 3);
   const int i = tl.y * per + 64 * t + (int)(threadIdx.x & 63);
   double e[8], dm = 0.0, vm = 0.0, wm = kInf;
-  force_atom<real, MODE, WAVES, MLP>(d.V[cur], d.P, F, i, i < n, w, team + t, e, dm, vm, wm);
+  force_atom<real, MODE, WAVES, MLP>(V, P, F, i, i < n, w, team + t, e, dm, vm, wm);
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const double a = wave_max(dm), b = wave_max(vm), c = wave_min(wm);
   if (lane == 0) { redm[wv][0] = a; redm[wv][1] = b; redm[wv][2] = c; }
@@ -344,7 +406,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_density(const RepDesc<real> *D
   const RepDesc<real> &d = D[blockIdx.y];
   const int cur = bp.after ? 1 - (d.pos ^ (bp.kk & 1)) : d.pos;
   const int i = (int)blockIdx.x * kBlock + (int)threadIdx.x;
-  if (i < d.V[cur].n && d.P.eam_on) eam_density_atom<real>(d.V[cur], d.P, i);
+  if (i < d.V[cur].n && d.P.eam_on) eam_density_atom<real>(rep_view(&d, cur), d.P, i);
 }
 
 template <typename real>

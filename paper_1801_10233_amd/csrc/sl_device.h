@@ -19,6 +19,7 @@ constexpr double kMvv2e = 1.0364269652680506e-4;  // eV per amu A^2/ps^2
 
 constexpr double kInf = 1e300;     // "no watched pair" distance squared
 constexpr int kMaxRep = 4;        // consecutive updates one spin launch can do
+constexpr int kMaxClass = 32;     // colour classes a kernel argument block can hold
 // Neighbours per lane gathered together in the force gather. With
 // displacement-ordered rows 4 beats 8 (117 against 128 us per launch at
 // 432 000 atoms: fewer registers, more waves in flight) and 16 (195 us).
@@ -250,6 +251,21 @@ struct TailArgs {
   double rs2;
 };
 
+// Half-steps of a small system in one workgroup, its spins in LDS.
+struct SpinLdsArgs {
+  int K;
+  int off[kMaxClass + 1];     // class offsets
+  int nhalf;                  // half-steps, alternating first and second of a step
+  int same;                   // 1: all at the same positions (frozen lattice)
+  int64_t step;               // step of the first half-step (the first of its step)
+  double h, amp;
+  uint64_t seed;
+  uint32_t replica;
+  double rs2;
+};
+// Spins that fit beside the partial sums of the teams in 160 KB of LDS.
+constexpr int kLdsSpins64 = 4608, kLdsSpins32 = 9216;
+
 struct ForceArgs {
   int mode;                   // bit 1: final kick, 2: next kick + drift, 4: energy
   double dt;
@@ -282,7 +298,6 @@ struct ForceArgs {
 enum : int { kModeFinal = 1, kModeNext = 2, kModeEnergy = 4 };
 
 // One replica of a batch, as seen by the persistent kernel.
-constexpr int kMaxClass = 32;
 template <typename real>
 struct RepDesc {
   SysView<real> V[2];          // views with position buffer 0 / 1

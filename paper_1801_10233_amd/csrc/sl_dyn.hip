@@ -37,21 +37,146 @@ __global__ __launch_bounds__((64 * TeamShape<LANES, LANGEVIN>::waves)) void k_sp
 // paying one launch for the whole run. Teams of kTailLanes wavefronts whatever
 // the launch shape of the large classes.
 constexpr int kTailLanes = 4;
+struct TailSeq {
+  const TailArgs &T;
+  int item, base;
+  __device__ bool more() const { return item < T.nitems; }
+  __device__ int begin() const { return base; }
+  __device__ int end() const { return T.item[item].end; }
+  __device__ int nrep() const { return T.item[item].nrep; }
+  __device__ int64_t step(int r) const { return T.item[item].step[r]; }
+  __device__ int sub(int r) const { return T.item[item].sub[r]; }
+  template <typename real> __device__ const float4 *tab(const SysView<real> &S) const { return S.tab; }
+  template <typename real> __device__ const real *jc(const SysView<real> &S) const { return S.jc; }
+  __device__ void advance() {
+    base += kTailBlock / kTailLanes;
+    if (base >= T.item[item].end && ++item < T.nitems) base = T.item[item].begin;
+  }
+  __device__ explicit TailSeq(const TailArgs &t) : T(t), item(0), base(t.item[0].begin) {}
+  __device__ TailSeq(const TailSeq &o) = default;
+  __device__ TailSeq &operator=(const TailSeq &o) {
+    item = o.item;
+    base = o.base;
+    return *this;
+  }
+};
 template <typename real, bool LANGEVIN, bool ANISO, int MLP>
 __global__ __launch_bounds__(kTailBlock) void k_spin_tail(SysView<real> S, PotConst P,
                                                           TailArgs T) {
   constexpr int kTeams = kTailBlock / 64 / kTailLanes;
   __shared__ SpinTeam<real, kTailLanes> team[kTeams];
-  const int t = wave_id() / kTailLanes, w = wave_id() % kTailLanes;
-  for (int q = 0; q < T.nitems; ++q) {
-    const TailItem &it = T.item[q];
-    for (int base = it.begin; base < it.end; base += 64 * kTeams) {
-      const int i = base + 64 * t + (int)(threadIdx.x & 63);
-      spin_update<real, LANGEVIN, ANISO, kTailLanes, MLP>(S, P, i, i < it.end, w, team + t, it.nrep,
-                                                          it.step, it.sub, T.h, T.amp, T.seed,
-                                                          T.replica, T.rs2);
+  if constexpr (MLP != 4) {
+    spin_sequence<real, LANGEVIN, ANISO, kTailLanes, kTeams, MLP>(TailSeq(T), S, P, S.sx, S.sy, S.sz, team, T.h,
+                                                                  T.amp, T.seed, T.replica, T.rs2);
+  } else {
+    const int t = wave_id() / kTailLanes, w = wave_id() % kTailLanes;
+    for (int q = 0; q < T.nitems; ++q) {
+      const TailItem &it = T.item[q];
+      for (int base = it.begin; base < it.end; base += 64 * kTeams) {
+        const int i = base + 64 * t + (int)(threadIdx.x & 63);
+        spin_update<real, LANGEVIN, ANISO, kTailLanes, MLP>(S, P, i, i < it.end, w, team + t, it.nrep,
+                                                            it.step, it.sub, T.h, T.amp, T.seed,
+                                                            T.replica, T.rs2);
+        __syncthreads();
+      }
+    }
+  }
+}
+
+// Spin half-steps of a small system: one workgroup holds every spin in LDS and
+// runs the sweeps' classes one after another with barriers between them. A class
+// of a few hundred atoms costs a launch of its own 3.3 us, most of it dispatch and
+// two trips to memory; here the neighbours' spins are in LDS and the list entries
+// and coefficients (from the exchange cache or the pair table) in L2. What bounds
+// a piece of 512 atoms is one compute unit's LDS and L1 bandwidth (FP64: 1500
+// clocks each). Two wavefronts per 64 atoms (four: 42 us instead of 28 per step of
+// 2000 frozen atoms, FP32). Fetching ahead pays in FP32 (28 us instead of 30; with
+// the bath and motion 72 instead of 85) and not in FP64 (41 instead of 36),
+// where the two sets of coefficients leave too few of the 128 registers.
+// Even half-steps use the positions of S, odd ones those of S2. With `same` the last
+// update of a half-step and the first of the next, both of class 0, are one pass over it.
+constexpr int kLdsLanes = 2, kLdsTeams = 16 / kLdsLanes;
+template <typename real>
+struct LdsSeq {
+  const SpinLdsArgs &A;
+  const float4 *tab2;  // at the positions of the odd half-steps
+  const real *jc2;
+  int hf, q, base;
+  bool both;  // a class 0 pass over two half-steps
+  __device__ int cls() const { return q < A.K ? q : 2 * A.K - 2 - q; }
+  __device__ bool more() const { return hf < A.nhalf; }
+  __device__ int begin() const { return base; }
+  __device__ int end() const { return A.off[cls() + 1]; }
+  __device__ int nrep() const { return q == A.K - 1 || both ? 2 : 1; }
+  __device__ int64_t step(int r) const { return A.step + ((hf + (both ? r : 0)) >> 1); }
+  __device__ int sub(int r) const {
+    if (both) return r ? 2 * ((hf + 1) & 1) : 2 * (hf & 1) + 1;
+    return 2 * (hf & 1) + (q < A.K ? r : 1);
+  }
+  __device__ const float4 *tab(const SysView<real> &S) const { return hf & 1 ? tab2 : S.tab; }
+  __device__ const real *jc(const SysView<real> &S) const { return hf & 1 ? jc2 : S.jc; }
+  __device__ void enter() {
+    both = A.same && A.K > 1 && q == 2 * A.K - 2 && hf + 1 < A.nhalf;
+    base = A.off[cls()];
+  }
+  __device__ void advance() {
+    base += 64 * kLdsTeams;
+    if (base < end()) return;
+    if (++q > 2 * A.K - 2) {
+      q = both ? 1 : 0;
+      ++hf;
+    }
+    enter();
+  }
+  __device__ LdsSeq(const SpinLdsArgs &a, const SysView<real> &S2)
+      : A(a), tab2(S2.tab), jc2(S2.jc), hf(0), q(0) {
+    enter();
+  }
+  __device__ LdsSeq(const LdsSeq &o) = default;
+  __device__ LdsSeq &operator=(const LdsSeq &o) {
+    hf = o.hf;
+    q = o.q;
+    base = o.base;
+    both = o.both;
+    return *this;
+  }
+};
+template <typename real, bool LANGEVIN, bool ANISO, int MLP>
+__global__ __launch_bounds__(1024) void k_spin_lds(SysView<real> S, PotConst P, SpinLdsArgs A,
+                                                   SysView<real> S2) {
+  __shared__ real spin[3][sizeof(real) == 8 ? kLdsSpins64 : kLdsSpins32];
+  __shared__ SpinTeam<real, kLdsLanes, 3, LANGEVIN ? 2 : 1> team[kLdsTeams];
+  for (int i = threadIdx.x; i < S.n; i += 1024) {
+    spin[0][i] = S.sx[i];
+    spin[1][i] = S.sy[i];
+    spin[2][i] = S.sz[i];
+  }
+  __syncthreads();
+  if constexpr (sizeof(real) == 4) {
+    spin_sequence<real, LANGEVIN, ANISO, kLdsLanes, kLdsTeams, MLP>(LdsSeq<real>(A, S2), S, P, spin[0], spin[1],
+                                                                    spin[2], team, A.h, A.amp, A.seed,
+                                                                    A.replica, A.rs2);
+  } else {
+    const int t = wave_id() / kLdsLanes, w = wave_id() % kLdsLanes;
+    SysView<real> V = S;
+    V.sx = spin[0];
+    V.sy = spin[1];
+    V.sz = spin[2];
+    for (LdsSeq<real> q(A, S2); q.more(); q.advance()) {
+      V.tab = q.tab(S);
+      V.jc = q.jc(S);
+      const int i = q.begin() + 64 * t + (int)(threadIdx.x & 63);
+      const int64_t st[kMaxRep] = {q.step(0), q.step(1), 0, 0};
+      const int sb[kMaxRep] = {q.sub(0), q.sub(1), 0, 0};
+      spin_update<real, LANGEVIN, ANISO, kLdsLanes, MLP>(V, P, i, i < q.end(), w, team + t, q.nrep(), st, sb,
+                                                         A.h, A.amp, A.seed, A.replica, A.rs2);
       __syncthreads();
     }
+  }
+  for (int i = threadIdx.x; i < S.n; i += 1024) {
+    S.sx[i] = spin[0][i];
+    S.sy[i] = spin[1][i];
+    S.sz[i] = spin[2][i];
   }
 }
 
@@ -225,6 +350,30 @@ void launch_spin_tail(const SysView<real> &S, const PotConst &P, const TailArgs 
   else spin_tail_run<real, 0>(S, P, T, st);
 }
 
+
+template <typename real, int MLP>
+static void spin_lds_run(const SysView<real> &S, const PotConst &P, const SpinLdsArgs &A,
+                         const SysView<real> &S2, hipStream_t st) {
+  const bool lg = P.langevin != 0, an = P.aniso_on != 0;
+  if (lg && an) hipLaunchKernelGGL((k_spin_lds<real, true, true, MLP>), dim3(1), dim3(1024), 0, st, S, P, A, S2);
+  else if (lg) hipLaunchKernelGGL((k_spin_lds<real, true, false, MLP>), dim3(1), dim3(1024), 0, st, S, P, A, S2);
+  else if (an) hipLaunchKernelGGL((k_spin_lds<real, false, true, MLP>), dim3(1), dim3(1024), 0, st, S, P, A, S2);
+  else hipLaunchKernelGGL((k_spin_lds<real, false, false, MLP>), dim3(1), dim3(1024), 0, st, S, P, A, S2);
+}
+
+template <typename real>
+bool launch_spin_lds(const SysView<real> &S, const PotConst &P, const SpinLdsArgs &A,
+                     const SysView<real> &S2, hipStream_t st) {
+  if (S.n > (sizeof(real) == 8 ? kLdsSpins64 : kLdsSpins32) || P.soc_on) return false;
+  if (S.jc && S2.jc) spin_lds_run<real, 3>(S, P, A, S2, st);
+  else if (sizeof(real) == 4 && S.tab && S2.tab) spin_lds_run<real, (sizeof(real) == 4 ? 1 : 3)>(S, P, A, S2, st);
+  else return false;
+  return true;
+}
+template bool launch_spin_lds<double>(const SysView<double> &, const PotConst &, const SpinLdsArgs &,
+                                      const SysView<double> &, hipStream_t);
+template bool launch_spin_lds<float>(const SysView<float> &, const PotConst &, const SpinLdsArgs &,
+                                     const SysView<float> &, hipStream_t);
 
 void launch_reduce8(const double *partial, int nb, double *out, hipStream_t st) {
   hipLaunchKernelGGL(k_reduce8, dim3(1), dim3(256), 0, st, partial, nb, out);

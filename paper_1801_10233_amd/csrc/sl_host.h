@@ -211,10 +211,36 @@ inline int fail(sl_system *S, int code, const std::string &msg) {
 // 9.4; FP32 6.8 and 6.4).
 constexpr int kSpinSpread = 3000, kSpinFull = 70000;
 inline bool jcache_on(const sl_system *S);
+inline bool spin_lds_on(const sl_system *S);
 inline int spin_lanes_for(const sl_system *S, int m) {
   if (!S->spin_auto) return S->spin_lanes;
   if (m <= kSpinSpread) return 8;
   return m > kSpinFull && S->prec == SL_FP64 && jcache_on(S) ? 1 : 4;
+}
+// Whether the spin half-steps of a small system run in one workgroup (k_spin_lds).
+// Not under a shape that the caller has set, nor while launches are timed one by one.
+// A piece of up to 512 atoms of a class takes 2.1 us there in FP32 (2.9 with the
+// bath) and 2.8 in FP64, a class's launch 3.3 to 3.6 whatever its size up to a few
+// thousand atoms; in FP64 the noise of 512 atoms alone takes the one compute unit
+// 1.6 us, so there a class may not exceed half a piece. Microseconds per step, one
+// workgroup and launches per class (bcc, K classes): FP32 without the bath, 1024 atoms
+// 45 and 62 (K 4), 2662 atoms 98 and 133 (K 9), 3456 atoms 76 and 72 (K 4), 117 and 148
+// (K 10); with it 2000 atoms 72 and 78 (K 4), 4394 atoms 182 and 174 (K 10); FP64
+// without it 2662 atoms 125 and 139, 3456 atoms 94 and 64; with it 1024 atoms 73
+// and 77, 2000 atoms 99 and 80.
+inline bool spin_lds_on(const sl_system *S) {
+  const bool f64 = S->prec == SL_FP64;
+  if (!S->spin_auto || !S->jc_auto || S->prof || S->ordering != SL_ORDER_COLOUR || S->pc.soc_on || S->K <= 0 ||
+      S->K > kMaxClass || S->n > (f64 ? kLdsSpins64 : kLdsSpins32) || (int)S->class_off.size() <= S->K)
+    return false;
+  const int piece = f64 && S->pc.langevin ? 256 : 512;
+  int pieces = 0;
+  for (int c = 0; c < S->K; ++c) pieces += (S->class_off[c + 1] - S->class_off[c] + piece - 1) / piece;
+  // (the network's pair table is read at 16 bytes an entry: 173 and 141 us with 4394
+  // atoms, K 9, 125 and 162 with 2662, K 10)
+  const bool table = S->mlp && S->mlp_mode == SL_MLP_PAIRWISE;
+  const int per10 = f64 ? (S->pc.langevin ? 10 : 11) : (S->pc.langevin || table ? 12 : 15);
+  return 10 * pieces <= per10 * S->K;
 }
 // Force launch: wavefronts per 64 atoms. 1 / 4 / 8 wavefronts: 8192 atoms 23 /
 // 12.1 / 11.9, 27 648 atoms 23.5 / 15.0 / 15.9, 65 536 atoms 24.3 / 20.7 / 25.2,
@@ -233,7 +259,7 @@ inline int force_lanes_for(const sl_system *S) {
 // frozen lattice, whose coefficients never change.
 inline bool jcache_on(const sl_system *S) {
   if (!S->jc_auto || S->prec == SL_FP32) return S->jcache > 0;
-  return S->prm.frozen || S->pc.langevin || S->K >= 7 || S->n > 4 * kSpinFull;
+  return S->prm.frozen || spin_lds_on(S) || S->pc.langevin || S->K >= 7 || S->n > 4 * kSpinFull;
 }
 
 template <typename T>

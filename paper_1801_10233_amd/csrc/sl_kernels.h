@@ -16,6 +16,11 @@ void launch_spin_phase(const SysView<real> &S, const PotConst &P, const SpinPhas
 template <typename real>
 void launch_spin_tail(const SysView<real> &S, const PotConst &P, const TailArgs &T,
                       hipStream_t st);
+// Spin half-steps of a system small enough for one workgroup's LDS, with the
+// exchange cache or the pair table at both sets of positions; false: not taken.
+template <typename real>
+bool launch_spin_lds(const SysView<real> &S, const PotConst &P, const SpinLdsArgs &A,
+                     const SysView<real> &S2, hipStream_t st);
 template <typename real>
 void launch_force(const SysView<real> &S, const PotConst &P, const ForceArgs &A, int lanes,
                   hipStream_t st);

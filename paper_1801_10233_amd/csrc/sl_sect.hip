@@ -88,7 +88,7 @@ __global__ __launch_bounds__(64) void k_sect_phase(SysView<real> S, PotConst P, 
   const int sub[kMaxRep] = {A.sub, A.sub, A.sub, A.sub};
   for (int t = 0; t < cnt; ++t) {
     const int i = A.order[A.backward ? beg + cnt - 1 - t : beg + t];
-    spin_update<real, LANGEVIN, ANISO, 1, MLP>(S, P, i, true, 0, nullptr, 1, step, sub, A.h, A.amp,
+    spin_update<real, LANGEVIN, ANISO, 1, MLP>(S, P, i, true, 0, (SpinTeam<real, 1> *)nullptr, 1, step, sub, A.h, A.amp,
                                                A.seed, A.replica, A.rs2);
   }
 }

@@ -52,6 +52,63 @@ __device__ __forceinline__ void cayley_rot(real &sx, real &sy, real &sz, real wx
   sx = nx; sy = ny; sz = nz;
 }
 
+// One update of a spin in the exchange field a (and the external field, the
+// anisotropy and, with the bath, the noise g).
+template <typename real, bool LANGEVIN, bool ANISO>
+__device__ __forceinline__ void spin_rotate(const PotConst &P, real h, real amp, real ax, real ay, real az,
+                                            const real g[3], real &sx, real &sy, real &sz) {
+  const real ih = (real)(1.0 / kHbar);
+  real ex = ax + (real)P.zB[0], ey = ay + (real)P.zB[1], ez = az + (real)P.zB[2];
+  if (ANISO && P.aniso_split) {  // set only without the spin bath
+    // symmetric split A(h/2) X(h) A(h/2): A rotates about n at the rate
+    // (2K/hbar)(s.n), which A itself keeps fixed; X about the field
+    // without the anisotropy (it does not depend on s_i)
+    const real n0 = (real)P.an[0], n1 = (real)P.an[1], n2 = (real)P.an[2];
+    const real k2 = (real)2 * (real)P.aK * ih;
+    const real hh = (real)0.5 * h;
+    real c = k2 * (sx * n0 + sy * n1 + sz * n2);
+    cayley_rot<real>(sx, sy, sz, c * n0, c * n1, c * n2, hh);
+    cayley_rot<real>(sx, sy, sz, ex * ih, ey * ih, ez * ih, h);
+    c = k2 * (sx * n0 + sy * n1 + sz * n2);
+    cayley_rot<real>(sx, sy, sz, c * n0, c * n1, c * n2, hh);
+    if (sizeof(real) == 4) {
+      const real rn = (real)rsqrtf((float)(sx * sx + sy * sy + sz * sz));
+      sx *= rn; sy *= rn; sz *= rn;
+    }
+    return;
+  }
+  if (ANISO) {
+    const real sn2 = (real)2 * (real)P.aK * (sx * (real)P.an[0] + sy * (real)P.an[1] + sz * (real)P.an[2]);
+    ex += sn2 * (real)P.an[0];
+    ey += sn2 * (real)P.an[1];
+    ez += sn2 * (real)P.an[2];
+  }
+  real wx = ex * ih, wy = ey * ih, wz = ez * ih;
+  if (LANGEVIN) {
+    const real lam = (real)P.lam, f = (real)P.lamfac;
+    const real cx = sy * wz - sz * wy, cy = sz * wx - sx * wz, cz = sx * wy - sy * wx;
+    wx = (wx + amp * g[0] + lam * cx) * f;
+    wy = (wy + amp * g[1] + lam * cy) * f;
+    wz = (wz + amp * g[2] + lam * cz) * f;
+  }
+  // Cayley rotation of Sec. 3 (Omelyan): exact rotation about W by
+  // 2 atan(h|W|/2); preserves |s| in exact arithmetic.
+  const real cx = wy * sz - wz * sy, cy = wz * sx - wx * sz, cz = wx * sy - wy * sx;
+  const real ws = wx * sx + wy * sy + wz * sz;
+  const real w2 = wx * wx + wy * wy + wz * wz;
+  const real q = h * h * (real)0.25;
+  const real inv = (real)1 / ((real)1 + q * w2);
+  real nx = (sx + h * cx + q * ((real)2 * wx * ws - w2 * sx)) * inv;
+  real ny = (sy + h * cy + q * ((real)2 * wy * ws - w2 * sy)) * inv;
+  real nz = (sz + h * cz + q * ((real)2 * wz * ws - w2 * sz)) * inv;
+  if (sizeof(real) == 4) {
+    // FP32 form: renormalise after every rotation.
+    const real rn = (real)rsqrtf((float)(nx * nx + ny * ny + nz * nz));
+    nx *= rn; ny *= rn; nz *= rn;
+  }
+  sx = nx; sy = ny; sz = nz;
+}
+
 // ---------------------------------------------------------------------------
 // Spin colour phase. For every atom i of one class (no two of them
 // interact): omega_i = (1/hbar)[sum_j J(r_ij) s_j + g mu_B B + 2K(s_i.n)n]
@@ -85,10 +142,11 @@ struct TeamShape {
   static constexpr int waves = LANES / sub;
   static constexpr int atoms = 64 / sub;
 };
-template <typename real, int WAVES>
+// (ROWS: 3 sums, 6 in the dual update; REPS: updates whose noise is held)
+template <typename real, int WAVES, int ROWS = 6, int REPS = kMaxRep>
 struct SpinTeam {
-  real sum[WAVES > 1 ? WAVES - 1 : 1][6][64];
-  real g[kMaxRep][3][64];
+  real sum[WAVES > 1 ? WAVES - 1 : 1][ROWS][64];
+  real g[REPS][3][64];
 };
 
 // Neighbour slots one lane gathers per round of the spin phase (value: the
@@ -119,11 +177,11 @@ struct SpinChunk<LANES, 4> {
 // moves in between), so they are gathered once and the exchange field is
 // summed at the positions of S for the first update and of S2 (same atoms,
 // same list, the other position buffer) for the second; nrep must be 2.
-template <typename real, bool LANGEVIN, bool ANISO, int LANES, int MLP, bool DUAL = false>
+template <typename real, bool LANGEVIN, bool ANISO, int LANES, int MLP, bool DUAL = false,
+          typename Team>
 __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotConst &P, int i,
-                                            bool valid, int w,
-                                            SpinTeam<real, TeamShape<LANES, LANGEVIN>::waves> *team,
-                                            int nrep, const int64_t *step, const int *sub,
+                                            bool valid, int w, Team *team, int nrep,
+                                            const int64_t *step, const int *sub,
                                             double hd, double ampd, uint64_t seed,
                                             uint32_t replica, double rs2,
                                             const SysView<real> *S2 = nullptr,
@@ -325,7 +383,6 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
   }
   if (!valid || u0 != 0) return;
   const real h = (real)hd;
-  const real ih = (real)(1.0 / kHbar);
   for (int rep = 0; rep < nrep; ++rep) {
     if (keep0 && rep == 1) {  // the state between the two updates, for the force
       S.sx[S.n + i] = sx;
@@ -333,68 +390,220 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
       S.sz[S.n + i] = sz;
     }
     const bool second = DUAL && rep == 1;
-    real ex = (second ? bx : ax) + (real)P.zB[0], ey = (second ? by : ay) + (real)P.zB[1],
-         ez = (second ? bz : az) + (real)P.zB[2];
-    if (ANISO && P.aniso_split) {  // set only without the spin bath
-      // symmetric split A(h/2) X(h) A(h/2): A rotates about n at the rate
-      // (2K/hbar)(s.n), which A itself keeps fixed; X about the field
-      // without the anisotropy (it does not depend on s_i)
-      const real n0 = (real)P.an[0], n1 = (real)P.an[1], n2 = (real)P.an[2];
-      const real k2 = (real)2 * (real)P.aK * ih;
-      const real hh = (real)0.5 * h;
-      real c = k2 * (sx * n0 + sy * n1 + sz * n2);
-      cayley_rot<real>(sx, sy, sz, c * n0, c * n1, c * n2, hh);
-      cayley_rot<real>(sx, sy, sz, ex * ih, ey * ih, ez * ih, h);
-      c = k2 * (sx * n0 + sy * n1 + sz * n2);
-      cayley_rot<real>(sx, sy, sz, c * n0, c * n1, c * n2, hh);
-      if (sizeof(real) == 4) {
-        const real rn = (real)rsqrtf((float)(sx * sx + sy * sy + sz * sz));
-        sx *= rn; sy *= rn; sz *= rn;
-      }
-      continue;
+    real g[3] = {g0[0], g0[1], g0[2]};
+    if (LANGEVIN && WAVES > 1) {
+      g[0] = team->g[rep][0][lane];
+      g[1] = team->g[rep][1][lane];
+      g[2] = team->g[rep][2][lane];
+    } else if (LANGEVIN && rep > 0) {
+      gauss3(seed, aid, step[rep], replica, sub[rep], g);
     }
-    if (ANISO) {
-      const real sn2 = (real)2 * (real)P.aK * (sx * (real)P.an[0] + sy * (real)P.an[1] + sz * (real)P.an[2]);
-      ex += sn2 * (real)P.an[0];
-      ey += sn2 * (real)P.an[1];
-      ez += sn2 * (real)P.an[2];
-    }
-    real wx = ex * ih, wy = ey * ih, wz = ez * ih;
-    if (LANGEVIN) {
-      real g[3] = {g0[0], g0[1], g0[2]};
-      if (WAVES > 1) {
-        g[0] = team->g[rep][0][lane];
-        g[1] = team->g[rep][1][lane];
-        g[2] = team->g[rep][2][lane];
-      } else if (rep > 0) {
-        gauss3(seed, aid, step[rep], replica, sub[rep], g);
-      }
-      const real lam = (real)P.lam, amp = (real)ampd, f = (real)P.lamfac;
-      const real cx = sy * wz - sz * wy, cy = sz * wx - sx * wz, cz = sx * wy - sy * wx;
-      wx = (wx + amp * g[0] + lam * cx) * f;
-      wy = (wy + amp * g[1] + lam * cy) * f;
-      wz = (wz + amp * g[2] + lam * cz) * f;
-    }
-    // Cayley rotation of Sec. 3 (Omelyan): exact rotation about W by
-    // 2 atan(h|W|/2); preserves |s| in exact arithmetic.
-    const real cx = wy * sz - wz * sy, cy = wz * sx - wx * sz, cz = wx * sy - wy * sx;
-    const real ws = wx * sx + wy * sy + wz * sz;
-    const real w2 = wx * wx + wy * wy + wz * wz;
-    const real q = h * h * (real)0.25;
-    const real inv = (real)1 / ((real)1 + q * w2);
-    real nx = (sx + h * cx + q * ((real)2 * wx * ws - w2 * sx)) * inv;
-    real ny = (sy + h * cy + q * ((real)2 * wy * ws - w2 * sy)) * inv;
-    real nz = (sz + h * cz + q * ((real)2 * wz * ws - w2 * sz)) * inv;
-    if (sizeof(real) == 4) {
-      // FP32 form: renormalise after every rotation.
-      const real rn = (real)rsqrtf((float)(nx * nx + ny * ny + nz * nz));
-      nx *= rn; ny *= rn; nz *= rn;
-    }
-    sx = nx; sy = ny; sz = nz;
+    spin_rotate<real, LANGEVIN, ANISO>(P, h, (real)ampd, second ? bx : ax, second ? by : ay,
+                                       second ? bz : az, g, sx, sy, sz);
   }
   S.sx[i] = sx;
   S.sy[i] = sy;
   S.sz[i] = sz;
+}
+
+// ---------------------------------------------------------------------------
+// Runs of classes in one workgroup (small classes; a whole small system). What
+// an update needs that no other update changes -- the list entries, the exchange
+// coefficients, the noise -- is fetched while the one before is still under way,
+// so that a turn waits for the neighbours' spins, the joined sums and the
+// rotation only. LANES wavefronts per team of 64 atoms; a first round of 16 slots
+// per row.
+template <typename real, int LANES, int MLP>
+struct SpinAhead {
+  static constexpr int kSlots = 16 / LANES;
+  int i, ns;              // atom (-1: none), row length
+  uint32_t aid;
+  int j[kSlots];
+  float jt[MLP == 1 ? kSlots : 1];
+  real J[kSlots];
+  real g[3];              // noise of update LANES - 1 - w
+};
+
+// The loads that depend on nothing.
+template <typename real, bool LANGEVIN, int LANES, int MLP, typename Seq>
+__device__ __forceinline__ void spin_ahead_load(const SysView<real> &S, const Seq &q, int w,
+                                                SpinAhead<real, LANES, MLP> &a) {
+  const int i = q.begin() + wave_id() / LANES * 64 + (int)(threadIdx.x & 63);
+  const bool valid = i < q.end();
+  const float4 *tab = q.tab(S);
+  const real *jc = q.jc(S);
+  a.i = valid ? i : -1;
+  a.ns = 0;
+  if (!valid) return;
+  a.ns = S.nspin[i];
+  if (LANGEVIN) a.aid = (uint32_t)S.id[i];
+#pragma unroll
+  for (int c = 0; c < a.kSlots; ++c) {
+    const int k = w + LANES * c;
+    const bool in = k < S.kcap;
+    a.j[c] = in ? S.nbr[(size_t)k * S.ld + i] : i;
+    if (MLP == 1) a.jt[c] = in ? tab[(size_t)k * S.ld + i].x : 0.f;
+    if (MLP == 3) a.J[c] = in ? jc[(size_t)k * S.ld + i] : (real)0;
+  }
+}
+
+// The coefficients from the positions, and the noise.
+template <typename real, bool LANGEVIN, int LANES, int MLP, typename Seq>
+__device__ __forceinline__ void spin_ahead_finish(const SysView<real> &S, const PotConst &P, const Seq &q,
+                                                  int w, uint64_t seed, uint32_t replica, double rs2,
+                                                  SpinAhead<real, LANES, MLP> &a) {
+  if (a.i < 0) return;
+  constexpr int CH = 16 / LANES;
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+    if ((unsigned)a.j[c] >= (unsigned)S.n) a.j[c] = a.i;
+  if (MLP == 0 || MLP == 2) {
+    const double rix = S.rx[a.i], riy = S.ry[a.i], riz = S.rz[a.i];
+    double px[CH], py[CH], pz[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) { px[c] = S.rx[a.j[c]]; py[c] = S.ry[a.j[c]]; pz[c] = S.rz[a.j[c]]; }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const double dx = min_image(rix - px[c], S.L[0], S.invL[0]);
+      const double dy = min_image(riy - py[c], S.L[1], S.invL[1]);
+      const double dz = min_image(riz - pz[c], S.L[2], S.invL[2]);
+      const double r2 = dx * dx + dy * dy + dz * dz;
+      if (MLP == 2) {
+        a.J[c] = (real)spline_phys(S.spl, (float)sqrt(r2)).x;
+      } else {
+        const real Jc = exch_J<real>(P, r2);
+        a.J[c] = r2 < rs2 ? Jc : (real)0;
+      }
+    }
+  }
+  if (LANGEVIN) {
+    const int r = LANES - 1 - w;
+    if (r < q.nrep()) gauss3(seed, a.aid, q.step(r), replica, q.sub(r), a.g);
+  }
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    if (MLP == 1) a.J[c] = (real)a.jt[c];
+    if (w + LANES * c >= a.ns) a.J[c] = (real)0;
+  }
+}
+
+// All updates of a sequence of classes, in order. Seq gives, for the current
+// piece of up to 64 * TEAMS atoms of a class, its atoms [begin, end), the number
+// of successive updates (at most LANES), their steps and stages, and the pair
+// table or exchange cache that holds; sx, sy, sz are the spins (global or LDS).
+template <typename real, bool LANGEVIN, bool ANISO, int LANES, int TEAMS, int MLP, typename Seq, typename Team>
+__device__ __forceinline__ void spin_sequence(Seq q, const SysView<real> &S, const PotConst &P, real *sx, real *sy, real *sz,
+                                              Team *teams, double hd, double ampd, uint64_t seed,
+                                              uint32_t replica, double rs2) {
+  constexpr int CH = 16 / LANES;
+  const int t = wave_id() / LANES, w = wave_id() % LANES, lane = threadIdx.x & 63;
+  Team *const team = teams + t;
+  SpinAhead<real, LANES, MLP> a;
+  if (!q.more()) return;
+  spin_ahead_load<real, LANGEVIN, LANES, MLP>(S, q, w, a);
+  spin_ahead_finish<real, LANGEVIN, LANES, MLP>(S, P, q, w, seed, replica, rs2, a);
+  while (q.more()) {
+    const int i = a.i, nrep = q.nrep();
+    const bool valid = i >= 0;
+    real ax = 0, ay = 0, az = 0, x = 0, y = 0, z = 0;
+    const int ns = a.ns;
+    // four slots at a time, the next piece's loads behind the last four
+    constexpr int G = CH < 4 ? CH : 4;
+    real qx[G], qy[G], qz[G], J[G];
+#pragma unroll
+    for (int g = 0; g < CH; g += G) {
+      if (valid) {
+#pragma unroll
+        for (int c = 0; c < G; ++c) {
+          const int j = a.j[g + c];
+          qx[c] = sx[j]; qy[c] = sy[j]; qz[c] = sz[j];
+          J[c] = a.J[g + c];
+        }
+        if (g + G < CH) {
+#pragma unroll
+          for (int c = 0; c < G; ++c) {
+            ax += J[c] * qx[c];
+            ay += J[c] * qy[c];
+            az += J[c] * qz[c];
+          }
+        }
+      }
+    }
+    if (valid) {
+      if (w == 0) { x = sx[i]; y = sy[i]; z = sz[i]; }
+      if (LANGEVIN && LANES - 1 - w < nrep) {
+        team->g[LANES - 1 - w][0][lane] = a.g[0];
+        team->g[LANES - 1 - w][1][lane] = a.g[1];
+        team->g[LANES - 1 - w][2][lane] = a.g[2];
+      }
+    }
+    Seq next = q;
+    next.advance();
+    if (next.more()) spin_ahead_load<real, LANGEVIN, LANES, MLP>(S, next, w, a);
+    if (valid) {
+#pragma unroll
+      for (int c = 0; c < G; ++c) {
+        ax += J[c] * qx[c];
+        ay += J[c] * qy[c];
+        az += J[c] * qz[c];
+      }
+      if (ns > 16) {  // longer rows, slot by slot
+        for (int k = w + 16; k < ns; k += LANES) {
+          const size_t at = (size_t)k * S.ld + i;
+          const int j = S.nbr[at];
+          real Jk;
+          if (MLP == 1) {
+            Jk = (real)q.tab(S)[at].x;
+          } else if (MLP == 3) {
+            Jk = q.jc(S)[at];
+          } else {
+            const double dx = min_image(S.rx[i] - S.rx[j], S.L[0], S.invL[0]);
+            const double dy = min_image(S.ry[i] - S.ry[j], S.L[1], S.invL[1]);
+            const double dz = min_image(S.rz[i] - S.rz[j], S.L[2], S.invL[2]);
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            if (MLP == 2) {
+              Jk = (real)spline_phys(S.spl, (float)sqrt(r2)).x;
+            } else {
+              Jk = exch_J<real>(P, r2);
+              if (!(r2 < rs2)) Jk = (real)0;
+            }
+          }
+          ax += Jk * sx[j];
+          ay += Jk * sy[j];
+          az += Jk * sz[j];
+        }
+      }
+      if (w > 0) {
+        team->sum[w - 1][0][lane] = ax;
+        team->sum[w - 1][1][lane] = ay;
+        team->sum[w - 1][2][lane] = az;
+      }
+    }
+    __syncthreads();
+    if (valid && w == 0) {
+#pragma unroll
+      for (int o = 0; o < LANES - 1; ++o) {
+        ax += team->sum[o][0][lane];
+        ay += team->sum[o][1][lane];
+        az += team->sum[o][2][lane];
+      }
+      for (int r = 0; r < nrep; ++r) {
+        real g[3] = {0, 0, 0};
+        if (LANGEVIN) {
+          g[0] = team->g[r][0][lane];
+          g[1] = team->g[r][1][lane];
+          g[2] = team->g[r][2][lane];
+        }
+        spin_rotate<real, LANGEVIN, ANISO>(P, (real)hd, (real)ampd, ax, ay, az, g, x, y, z);
+      }
+      sx[i] = x;
+      sy[i] = y;
+      sz[i] = z;
+    }
+    if (next.more()) spin_ahead_finish<real, LANGEVIN, LANES, MLP>(S, P, next, w, seed, replica, rs2, a);
+    q = next;
+    __syncthreads();
+  }
 }
 
 

@@ -445,6 +445,32 @@ void run_updates(sl_system *S, int posbuf, const std::vector<Upd> &u, double h,
   }
 }
 
+// nhalf half-steps from the first of step `step`, the even ones at buffer posbuf,
+// the odd ones at the other (frozen: all at posbuf), in one workgroup; false: not
+// taken (the caller launches the classes).
+template <typename real>
+bool spin_lds(sl_system *S, int posbuf, int64_t step, int nhalf, double h) {
+  if (!spin_lds_on(S)) return false;
+  const int other = S->prm.frozen ? posbuf : 1 - posbuf;
+  for (int b : {posbuf, other}) {
+    if (ensure_table(S, b)) return false;
+    (void)ensure_jcache<real>(S, b);
+  }
+  SpinLdsArgs A;
+  std::memset(&A, 0, sizeof(A));
+  A.K = S->K;
+  for (int c = 0; c <= S->K; ++c) A.off[c] = S->class_off[c];
+  A.nhalf = nhalf;
+  A.same = S->prm.frozen;
+  A.step = step;
+  A.h = h;
+  A.amp = noise_amp(S, h);
+  A.seed = S->prm.seed;
+  A.replica = S->prm.replica;
+  A.rs2 = S->pot.ex_rc * S->pot.ex_rc;
+  return launch_spin_lds<real>(view<real>(S, posbuf), S->pc, A, view<real>(S, other), S->st);
+}
+
 // Forward (classes 1..K) then backward (K..1) sweep of one spin half-step.
 void half_step_updates(const sl_system *S, int64_t step, int sub_fwd, std::vector<Upd> &u) {
   for (int c = 0; c < S->K; ++c) u.push_back({c, step, sub_fwd});
@@ -677,7 +703,7 @@ int step_frozen(sl_system *S, int64_t n, double dt) {
         sect_half<real>(S, S->pos, S->step + q, 0, h);
         sect_half<real>(S, S->pos, S->step + q, 2, h);
       }
-    } else {
+    } else if (!spin_lds<real>(S, S->pos, S->step, 2 * (int)chunk, h)) {
       std::vector<Upd> u;
       for (int64_t q = 0; q < chunk; ++q) {
         half_step_updates(S, S->step + q, 0, u);
@@ -768,7 +794,7 @@ int step_coupled(sl_system *S, int64_t n, double dt, bool built) {
       CHK(sect_prepare(S, S->pos));
       sect_half<real>(S, S->pos, k, 0, h);
       sect_half<real>(S, 1 - S->pos, k, 2, h);
-    } else {
+    } else if (S->held || !spin_lds<real>(S, S->pos, k, 2, h)) {
       std::vector<Upd> u, w;
       half_step_updates(S, k, 0, u);
       half_step_updates(S, k, 2, w);

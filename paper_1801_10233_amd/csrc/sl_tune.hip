@@ -135,9 +135,12 @@ int sl_autotune(sl_system *S, int steps, double dt, sl_tuning *chosen) {
     // all candidates, the best window of each counts.
     // (8 lanes per atom pays on small lattices: every class is then many
     // wavefronts instead of a few)
-    constexpr int kTrials = 10;
+    // The last candidate is the default, for the small systems whose spin
+    // half-steps it runs in one workgroup (no set shape does).
+    constexpr int kTrials = 11;
     const int trial[kTrials][3] = {{2, 1, -1}, {1, 1, 1}, {2, 1, 1}, {1, 1, -1}, {4, 1, 1},
-                                   {4, 1, -1}, {2, 2, -1}, {1, 2, 1}, {8, 1, -1}, {8, 2, -1}};
+                                   {4, 1, -1}, {2, 2, -1}, {1, 2, 1}, {8, 1, -1}, {8, 2, -1},
+                                   {0, 0, 0}};
     double best[kTrials];
     for (double &b : best) b = 1e300;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -153,6 +156,7 @@ int sl_autotune(sl_system *S, int steps, double dt, sl_tuning *chosen) {
         const int t = (q + 3 * pass) % kTrials;
         sl_tuning tt{trial[t][0], trial[t][1], S->small_class, trial[t][2], S->overlap};
         if ((rc = sl_set_tuning(C, &tt))) break;
+        if (trial[t][0] == 0 && !spin_lds_on(C)) continue;
         if ((rc = sl_step(C, 3, dt))) break;
         for (int attempt = 0; attempt < 3 && rc == SL_OK; ++attempt) {
           const int64_t rb0 = C->rebuilds;
@@ -178,15 +182,14 @@ int sl_autotune(sl_system *S, int steps, double dt, sl_tuning *chosen) {
     for (int t = 1; t < kTrials; ++t)
       if (best[t] < best[bt]) bt = t;
     v[0] = trial[bt][0];
-    v[1] = S->prm.frozen ? 1 : trial[bt][1];
+    v[1] = S->prm.frozen && v[0] ? 1 : trial[bt][1];
     v[2] = S->small_class;
     v[3] = trial[bt][2];
     cache_store(key, v);
   }
   sl_tuning t{v[0], v[1], v[2], v[3], S->overlap};
   CHK(sl_set_tuning(S, &t));
-  if (chosen) *chosen = t;
-  return SL_OK;
+  return chosen ? sl_get_tuning(S, chosen) : SL_OK;
 }
 
 }  // extern "C"
