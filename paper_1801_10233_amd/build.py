@@ -20,6 +20,8 @@ FLAGS = [
     "-std=c++17",
     "-fPIC",
     "-shared",
+    # leading scalar arguments of a kernel start in registers
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     # no packed-FP32 instructions anywhere in the device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",

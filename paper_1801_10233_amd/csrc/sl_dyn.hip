@@ -20,15 +20,43 @@ namespace sl {
 
 constexpr int kJcSplitAtoms = SL_JC_SPLIT;  // below: the row's slots split over grid.y
 
+// (an argument block is written across the bus for each launch: no second view
+// where it isn't read)
+struct NoView {};
+template <typename real, bool DUAL>
+using SecondView = std::conditional_t<DUAL, SysView<real>, NoView>;
+
 template <typename real, bool LANGEVIN, bool ANISO, int LANES, int MLP, bool DUAL>
 __global__ __launch_bounds__((64 * TeamShape<LANES, LANGEVIN>::waves)) void k_spin_phase(
-    SysView<real> S, PotConst P, SpinPhaseArgs A, SysView<real> S2) {
+    const int *nbr, const void *p1, const void *p2, const void *p3, const void *p4, int begin, int end, int ld,
+    int kcap, SysView<real> S, PotConst P, SpinPhaseArgs A, SecondView<real, DUAL> S2) {
   using T = TeamShape<LANES, LANGEVIN>;  // one workgroup per team
   __shared__ SpinTeam<real, T::waves> team[1];
-  const int i = A.begin + xcd_tile(blockIdx.x, gridDim.x) * T::atoms + (int)(threadIdx.x & (T::atoms - 1));
-  spin_update<real, LANGEVIN, ANISO, LANES, MLP, DUAL>(S, P, i, i < A.end, wave_id(), team, A.nrep,
-                                                       A.step, A.sub, A.h, A.amp, A.seed,
-                                                       A.replica, A.rs2, &S2, !DUAL && A.keep != 0);
+  constexpr bool kCoeff = MLP == 1 || MLP == 3;
+  // what the first loads need, in registers when the wavefront starts
+  // (-amdgpu-kernarg-preload-count): the argument block itself is a trip to memory
+  S.nbr = nbr;
+  if (kCoeff) {
+    if (MLP == 3) S.jc = (const real *)p1;
+    else S.tab = (const float4 *)p1;
+    S.sx = (real *)p2;
+    S.sy = (real *)p3;
+    S.sz = (real *)p4;
+  } else {
+    S.rx = (const double *)p1;
+    S.ry = (const double *)p2;
+    S.rz = (const double *)p3;
+    S.sx = (real *)p4;
+  }
+  S.ld = ld;
+  S.kcap = kcap;
+  const int nb = (end - begin + T::atoms - 1) / T::atoms;
+  const int i = begin + xcd_tile(blockIdx.x, nb) * T::atoms + (int)(threadIdx.x & (T::atoms - 1));
+  const SysView<real> *V2 = nullptr;
+  if constexpr (DUAL) V2 = &S2;
+  spin_update<real, LANGEVIN, ANISO, LANES, MLP, DUAL>(S, P, i, i < end, wave_id(), team, A.nrep, A.step, A.sub,
+                                                       A.h, A.amp, A.seed, A.replica, A.rs2, V2,
+                                                       !DUAL && A.keep != 0);
 }
 
 // A run of small classes (a few atoms each, e.g. the extra colours a repair
@@ -287,8 +315,17 @@ static void spin_phase_run(const SysView<real> &S, const PotConst &P, const Spin
                            const SysView<real> &S2, hipStream_t st) {
   using T = TeamShape<LANES, LG>;
   const int nb = (A.end - A.begin + T::atoms - 1) / T::atoms;
+  const void *p[4] = {S.rx, S.ry, S.rz, S.sx};
+  if (MLP == 1 || MLP == 3) {
+    p[0] = MLP == 3 ? (const void *)S.jc : (const void *)S.tab;
+    p[1] = S.sx;
+    p[2] = S.sy;
+    p[3] = S.sz;
+  }
+  SecondView<real, DUAL> V2;
+  if constexpr (DUAL) V2 = S2;
   hipLaunchKernelGGL((k_spin_phase<real, LG, AN, LANES, MLP, DUAL>), dim3(nb), dim3(64 * T::waves), 0,
-                     st, S, P, A, S2);
+                     st, S.nbr, p[0], p[1], p[2], p[3], A.begin, A.end, S.ld, S.kcap, S, P, A, V2);
 }
 
 template <typename real, int LANES, int MLP, bool DUAL>

@@ -188,9 +188,10 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
                                             bool keep0 = false) {
   // Latency is what bounds this update, so every load that does not depend
   // on another is issued at once: the row length, the own position, spin
-  // and id, and the list entries of the first round (taken unconditionally
-  // up to the list capacity; a slot past the row end is masked afterwards,
-  // and any index outside [0, n) is replaced by i before it is used). The
+  // and id, and the list entries of the first round (taken unconditionally, the
+  // last one again past the list capacity; a slot past the row end is masked
+  // afterwards, and any index outside [0, n) is replaced by i before it is used),
+  // those whose addresses are known first in front. The
   // gathers of positions and spins follow in one batch, and the Philox
   // noise of the first update is computed while they are in flight.
   constexpr int CH0 = SpinChunk<LANES, MLP>::value, CH1 = SpinChunk<LANES, MLP>::later;
@@ -206,26 +207,34 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
   uint32_t aid = 0;
   if (valid) {
     const int ld = S.ld;
-    const int ns = S.nspin[i];
-    const double rix = S.rx[i], riy = S.ry[i], riz = S.rz[i];
-    double rix2 = 0, riy2 = 0, riz2 = 0;
-    if (DUAL) { rix2 = S2->rx[i]; riy2 = S2->ry[i]; riz2 = S2->rz[i]; }
-    sx = S.sx[i]; sy = S.sy[i]; sz = S.sz[i];
-    if (LANGEVIN) aid = (uint32_t)S.id[i];
+    int ns = 0;
+    double rix = 0, riy = 0, riz = 0, rix2 = 0, riy2 = 0, riz2 = 0;
     // one round of CH slots from base (a generic lambda, so that the first
     // round and the later ones can differ in size)
     auto gather_round = [&](auto chunk, int base, bool first) {
       // the first round loads its slots before the row length is known;
       // later ones (the row length has arrived) load only the row's own
       constexpr int CH = decltype(chunk)::value;
-      const int kend = first ? S.kcap : ns;
       int jj[CH];
+      size_t at[CH];
+      bool has[CH];
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const int k = base + LANES * c;
-        const int j = k < kend ? S.nbr[(size_t)k * ld + i] : i;
-        jj[c] = (unsigned)j < (unsigned)S.n ? j : i;
+        has[c] = first || k < ns;
+        at[c] = (size_t)(first && k >= S.kcap ? S.kcap - 1 : k) * ld + i;
+        jj[c] = has[c] ? S.nbr[at[c]] : i;
       }
+      if (first) {
+        ns = S.nspin[i];
+        sx = S.sx[i]; sy = S.sy[i]; sz = S.sz[i];
+        if (LANGEVIN) aid = (uint32_t)S.id[i];
+        rix = S.rx[i]; riy = S.ry[i]; riz = S.rz[i];
+        if (DUAL) { rix2 = S2->rx[i]; riy2 = S2->ry[i]; riz2 = S2->rz[i]; }
+      }
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+        if ((unsigned)jj[c] >= (unsigned)S.n) jj[c] = i;
       real qx[CH], qy[CH], qz[CH], J[CH];
       real hx[CH], hy[CH], hz[CH];  // MLP == 4: Neel and DMI field of the pair
       double px[CH], py[CH], pz[CH];
@@ -238,13 +247,12 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
       real jr2[CH];
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
-        const int k = base + LANES * c;
         if (MLP == 1) {
-          jt[c] = k < kend ? S.tab[(size_t)k * ld + i].x : 0.f;
-          if (DUAL) jt2[c] = k < kend ? S2->tab[(size_t)k * ld + i].x : 0.f;
+          jt[c] = has[c] ? S.tab[at[c]].x : 0.f;
+          if (DUAL) jt2[c] = has[c] ? S2->tab[at[c]].x : 0.f;
         } else if (MLP == 3) {
-          jr[c] = k < kend ? S.jc[(size_t)k * ld + i] : (real)0;
-          if (DUAL) jr2[c] = k < kend ? S2->jc[(size_t)k * ld + i] : (real)0;
+          jr[c] = has[c] ? S.jc[at[c]] : (real)0;
+          if (DUAL) jr2[c] = has[c] ? S2->jc[at[c]] : (real)0;
         } else {
           px[c] = S.rx[jj[c]]; py[c] = S.ry[jj[c]]; pz[c] = S.rz[jj[c]];
           if (DUAL) { px2[c] = S2->rx[jj[c]]; py2[c] = S2->ry[jj[c]]; pz2[c] = S2->rz[jj[c]]; }
