@@ -911,12 +911,13 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
 // First pass of the embedded-atom terms: rho_i = sum_j f(r_ij) over the whole
 // list row, then F'(rho_i) and F(rho_i) for the force pass (one thread per
 // atom; one force-gather chunk of neighbours' positions in flight together).
-template <typename real>
-__device__ __forceinline__ void eam_density_atom(const SysView<real> &S, const PotConst &P, int i) {
+template <typename real, int WAVES>
+__device__ __forceinline__ real eam_density_sum(const SysView<real> &S, const PotConst &P, int i, int w) {
   const int na = S.nall[i], ld = S.ld;
   const double rix = S.rx[i], riy = S.ry[i], riz = S.rz[i];
+  const real bd = (real)(P.fbeta / P.fd);
   real rho = 0;
-  for (int base = 0; base < na; base += kForceChunk) {
+  for (int base = w * kForceChunk; base < na; base += WAVES * kForceChunk) {
     int jj[kForceChunk];
 #pragma unroll
     for (int c = 0; c < kForceChunk; ++c) {
@@ -936,13 +937,23 @@ __device__ __forceinline__ void eam_density_atom(const SysView<real> &S, const P
       const double r2 = dx * dx + dy * dy + dz * dz;
       if (base + c < na && r2 < P.fd2) {
         const real x = (real)sqrt(r2) - (real)P.fd;
-        rho += x * x + (real)P.fbeta * x * x * x / (real)P.fd;
+        rho += x * x + bd * x * x * x;
       }
     }
   }
+  return rho;
+}
+
+template <typename real>
+__device__ __forceinline__ void eam_density_store(const SysView<real> &S, const PotConst &P, int i, real rho) {
   const double sq = rho > (real)0 ? sqrt((double)rho) : 0.0;
   S.eam[i] = sq > 0.0 ? -0.5 * P.fA / sq : 0.0;
-  S.eam[ld + i] = -P.fA * sq;
+  S.eam[S.ld + i] = -P.fA * sq;
+}
+
+template <typename real>
+__device__ __forceinline__ void eam_density_atom(const SysView<real> &S, const PotConst &P, int i) {
+  eam_density_store<real>(S, P, i, eam_density_sum<real, 1>(S, P, i, 0));
 }
 
 
