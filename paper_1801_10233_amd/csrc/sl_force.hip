@@ -112,7 +112,7 @@ __global__ __launch_bounds__(team_block(WAVES), kForceWaves) void k_force(SysVie
 // exact in any order) and writes them, with the sticky error word, to the
 // pinned host slot; the written marker goes last.
 __global__ __launch_bounds__(kBlock) void k_pred_reduce(const double *pred, int nb, int *err,
-                                                        double *host_out) {
+                                                        double *host_out, double mark) {
   __shared__ double s[3][kBlock / 64];
   double a = 0.0, b = 0.0, c = kInf;
   for (int k = threadIdx.x; k < nb; k += kBlock) {
@@ -138,12 +138,13 @@ __global__ __launch_bounds__(kBlock) void k_pred_reduce(const double *pred, int 
     host_out[2] = (double)e;
     host_out[4] = c;
     __threadfence_system();
-    host_out[3] = 1.0;  // written marker
+    host_out[3] = mark;  // written marker
   }
 }
 
-void launch_pred_reduce(const double *pred, int nb, int *err, double *host_out, hipStream_t st) {
-  hipLaunchKernelGGL(k_pred_reduce, dim3(1), dim3(kBlock), 0, st, pred, nb, err, host_out);
+void launch_pred_reduce(const double *pred, int nb, int *err, double *host_out, double mark,
+                        hipStream_t st) {
+  hipLaunchKernelGGL(k_pred_reduce, dim3(1), dim3(kBlock), 0, st, pred, nb, err, host_out, mark);
 }
 
 

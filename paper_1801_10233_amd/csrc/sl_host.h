@@ -54,6 +54,7 @@ struct ProfRec {
 struct SlotMeta {
   int64_t boundary = -1;
   double dt = 0.0;
+  double mark = 0.0;           // written marker of the launch that fills the slot
   bool rebuilt_after = false;
 };
 
@@ -117,8 +118,8 @@ struct sl_system {
   double *ring_dev = nullptr;  // device alias of ring
   int *pin = nullptr;          // pinned host words read back by a rebuild [kPinWords]
   int *pin_dev = nullptr;      // device alias of pin
-  hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   SlotMeta meta[4];
+  double pred_mark = 1.0;      // marker of the last predictor launch (the batch uses 1)
 
   // state
   bool have_state = false, have_list = false, user_list = false, have_colour = false;

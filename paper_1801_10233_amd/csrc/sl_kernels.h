@@ -38,7 +38,7 @@ int force_block_atoms(int lanes);  // atoms of one block of a force launch
 int force_blocks(int n, int lanes);
 // Joins the per-block rebuild predictor terms (pred[nb][3]) of a force launch
 // into the pinned host slot host_out, with the error word and the marker.
-void launch_pred_reduce(const double *pred, int nb, int *err, double *host_out, hipStream_t st);
+void launch_pred_reduce(const double *pred, int nb, int *err, double *host_out, double mark, hipStream_t st);
 template <typename real>
 void launch_batch_run(RepDesc<real> *D, int R, int lanes, int variant, hipStream_t st);
 // Embedded-atom first pass (F'(rho), F(rho) of every atom) at the positions

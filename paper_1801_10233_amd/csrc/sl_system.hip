@@ -586,8 +586,8 @@ int force_launch(sl_system *S, int posbuf, int mode, double dt, int64_t boundary
   const int slot = (int)(boundary & 3);
   F.host_out = S->ring_dev + 8 * slot;
   if (mode & (kModeFinal | kModeNext)) {
-    S->ring[8 * slot + 3] = 0.0;
     S->meta[slot].boundary = boundary;
+    S->meta[slot].mark = S->pred_mark += 1.0;
     S->meta[slot].dt = dt;
     S->meta[slot].rebuilt_after = false;
   }
@@ -603,8 +603,7 @@ int force_launch(sl_system *S, int posbuf, int mode, double dt, int64_t boundary
     }
   }
   if (mode & (kModeFinal | kModeNext))
-    launch_pred_reduce(S->pred, force_nb(S), S->err, F.host_out, S->st);
-  if (mode & (kModeFinal | kModeNext)) HIPCHK(S, hipEventRecord(S->ev[slot], S->st));
+    launch_pred_reduce(S->pred, force_nb(S), S->err, F.host_out, S->meta[slot].mark, S->st);
   return SL_OK;
 }
 
@@ -669,9 +668,26 @@ int wait_predictor(sl_system *S, int64_t boundary, double dt_next, bool *due) {
   *due = false;
   const int slot = (int)(boundary & 3);
   if (boundary < 0 || S->meta[slot].boundary != boundary) return SL_OK;
-  HIPCHK(S, hipEventSynchronize(S->ev[slot]));
+  // The marker in the pinned slot is written last, behind a system-scope fence, and
+  // is another one for each launch: the slot then holds that launch's terms. (An event
+  // would be one more packet on the stream for each step.) A stream that has run
+  // dry, or failed, without the marker ends the wait.
   const double *o = S->ring + 8 * slot;
-  if (o[3] != 1.0) return fail(S, SL_E_HIP, "rebuild predictor not written");
+  double mark;
+  const auto written = [&] {
+    __atomic_load(o + 3, &mark, __ATOMIC_ACQUIRE);
+    return mark == S->meta[slot].mark;
+  };
+  for (unsigned spin = 1; !written(); ++spin) {
+    if (spin & 0xfff) {
+      __builtin_ia32_pause();
+      continue;
+    }
+    const hipError_t q = hipStreamQuery(S->st);
+    if (q == hipErrorNotReady) continue;
+    HIPCHK(S, q);
+    if (!written()) return fail(S, SL_E_HIP, "rebuild predictor not written");
+  }
   S->sticky |= (int)o[2];
   CHK(sticky_code(S));
   const bool rb = S->meta[slot].rebuilt_after;
@@ -1002,7 +1018,6 @@ int sl_create(const sl_params *p, sl_system **out) {
   A_(dalloc(&S->red_out, 8));
   A_(dalloc(&S->thermo, (size_t)kThermoCap * 8));
   A_(hipHostMalloc((void **)&S->ring, 32 * sizeof(double), hipHostMallocCoherent | hipHostMallocMapped));
-  for (int k = 0; k < 4; ++k) A_(hipEventCreateWithFlags(&S->ev[k], hipEventDisableTiming));
   A_(hipHostGetDevicePointer((void **)&S->ring_dev, S->ring, 0));
   A_(hipHostMalloc((void **)&S->pin, kPinWords * sizeof(int), hipHostMallocCoherent | hipHostMallocMapped));
   A_(hipHostGetDevicePointer((void **)&S->pin_dev, S->pin, 0));
@@ -1037,7 +1052,6 @@ int sl_destroy(sl_system *S) {
   }
   for (auto e : S->ev_pool) (void)hipEventDestroy(e);
   for (int k = 0; k < 4; ++k)
-    if (S->ev[k]) (void)hipEventDestroy(S->ev[k]);
   free_atoms(S->a[0]);
   free_atoms(S->a[1]);
   for (void *p : {(void *)S->ccount, (void *)S->cstart, (void *)S->cfill, (void *)S->catoms,
