@@ -419,8 +419,9 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
 // an update needs that no other update changes -- the list entries, the exchange
 // coefficients, the noise -- is fetched while the one before is still under way,
 // so that a turn waits for the neighbours' spins, the joined sums and the
-// rotation only. LANES wavefronts per team of 64 atoms; a first round of 16 slots
-// per row.
+// rotation only (24 334 atoms with the bath, two tails of a few hundred atoms per
+// step: 222 us per step with spin_update in the tails, 204 so). LANES wavefronts per
+// team of 64 atoms; a first round of 16 slots per row.
 template <typename real, int LANES, int MLP>
 struct SpinAhead {
   static constexpr int kSlots = 16 / LANES;
@@ -500,8 +501,8 @@ __device__ __forceinline__ void spin_ahead_finish(const SysView<real> &S, const 
 // of successive updates (at most LANES), their steps and stages, and the pair
 // table or exchange cache that holds; sx, sy, sz are the spins (global or LDS).
 template <typename real, bool LANGEVIN, bool ANISO, int LANES, int TEAMS, int MLP, typename Seq, typename Team>
-__device__ __forceinline__ void spin_sequence(Seq q, const SysView<real> &S, const PotConst &P, real *sx, real *sy, real *sz,
-                                              Team *teams, double hd, double ampd, uint64_t seed,
+__device__ __forceinline__ void spin_sequence(Seq q, const SysView<real> &S, const PotConst &P, real *sx,
+                                              real *sy, real *sz, Team *teams, double hd, double ampd, uint64_t seed,
                                               uint32_t replica, double rs2) {
   constexpr int CH = 16 / LANES;
   const int t = wave_id() / LANES, w = wave_id() % LANES, lane = threadIdx.x & 63;
@@ -909,8 +910,9 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
 }
 
 // First pass of the embedded-atom terms: rho_i = sum_j f(r_ij) over the whole
-// list row, then F'(rho_i) and F(rho_i) for the force pass (one thread per
-// atom; one force-gather chunk of neighbours' positions in flight together).
+// list row, then F'(rho_i) and F(rho_i) for the force pass; wavefront w of WAVES
+// sums every WAVES-th round (one force-gather chunk of neighbours' positions in
+// flight together).
 template <typename real, int WAVES>
 __device__ __forceinline__ real eam_density_sum(const SysView<real> &S, const PotConst &P, int i, int w) {
   const int na = S.nall[i], ld = S.ld;
