@@ -221,6 +221,11 @@ __global__ __launch_bounds__(kBlock) void k_batch_spin(const RepDesc<real> *D, B
 // back, with workgroup barriers between them (a launch of its own costs a class
 // of a few hundred atoms more than its turn here).
 constexpr int kBatchTailWaves = 4;
+// One piece per class of up to 256 atoms in FP32 (64 replicas, 2 lanes: 0.664 ms per
+// step with 512 threads, 0.645 with 1024); FP64 needs more than the 128 registers
+// that 1024 threads leave.
+template <typename real>
+constexpr int kBatchTailBlock = sizeof(real) == 4 ? 1024 : 512;
 template <typename real>
 struct BatchTailSeq {
   const RepDesc<real> &d;
@@ -236,7 +241,7 @@ struct BatchTailSeq {
   __device__ const float4 *tab(const SysView<real> &S) const { return S.tab; }
   __device__ const real *jc(const SysView<real> &S) const { return S.jc; }
   __device__ void advance() {
-    base += kBatchBlock / kBatchTailWaves;
+    base += kBatchTailBlock<real> / kBatchTailWaves;
     if (base >= end() && ++q < 2 * m - 1) base = d.off[cls()];
   }
   __device__ BatchTailSeq(const RepDesc<real> &r, const BatchPhase &bp)
@@ -249,9 +254,9 @@ struct BatchTailSeq {
   }
 };
 template <typename real, int MLP>
-__global__ __launch_bounds__(kBatchBlock) void k_batch_tail(const RepDesc<real> *D, BatchPhase bp,
+__global__ __launch_bounds__(kBatchTailBlock<real>) void k_batch_tail(const RepDesc<real> *D, BatchPhase bp,
                                                             const int2 *reps) {
-  constexpr int kTeams = kBatchBlock / 64 / kBatchTailWaves;
+  constexpr int kTeams = kBatchTailBlock<real> / 64 / kBatchTailWaves;
   __shared__ SpinTeam<real, kBatchTailWaves> team[kTeams];
   const RepDesc<real> &d = D[reps[blockIdx.x].x];
   const BatchTailSeq<real> seq(d, bp);
@@ -378,8 +383,8 @@ template <typename real>
 void launch_batch_tail(const RepDesc<real> *D, const int2 *reps, int nreps, const BatchPhase &bp,
                        bool soc, hipStream_t st) {
   if (nreps <= 0) return;
-  if (soc) hipLaunchKernelGGL((k_batch_tail<real, 4>), dim3(nreps), dim3(kBatchBlock), 0, st, D, bp, reps);
-  else hipLaunchKernelGGL((k_batch_tail<real, 0>), dim3(nreps), dim3(kBatchBlock), 0, st, D, bp, reps);
+  if (soc) hipLaunchKernelGGL((k_batch_tail<real, 4>), dim3(nreps), dim3(kBatchTailBlock<real>), 0, st, D, bp, reps);
+  else hipLaunchKernelGGL((k_batch_tail<real, 0>), dim3(nreps), dim3(kBatchTailBlock<real>), 0, st, D, bp, reps);
 }
 
 template <typename real, int MODE, int MLP>
