@@ -419,8 +419,8 @@ __device__ __forceinline__ void spin_update(const SysView<real> &S, const PotCon
 // an update needs that no other update changes -- the list entries, the exchange
 // coefficients, the noise -- is fetched while the one before is still under way,
 // so that a turn waits for the neighbours' spins, the joined sums and the
-// rotation only (24 334 atoms with the bath, two tails of a few hundred atoms per
-// step: 222 us per step with spin_update in the tails, 204 so). LANES wavefronts per
+// rotation only (a tail launch of 24 334 atoms with the bath, FP64, five
+// turns: 18.9 us with spin_update, 17.7 so; of 64 replicas, FP32: 49 us and 41). LANES wavefronts per
 // team of 64 atoms; a first round of 16 slots per row.
 template <typename real, int LANES, int MLP>
 struct SpinAhead {
