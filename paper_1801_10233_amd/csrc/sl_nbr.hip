@@ -529,31 +529,24 @@ __device__ __forceinline__ int colour_rounds(const ColourArgs &A, FinishLds &S, 
     const int *in_g = list[r & 1];
     int *out_g = list[(r + 1) & 1];
     int *out_n = &S.count[(r + 1) & 1];
-    // kRowInts lanes per ready atom, one per packed neighbour
+    // kRowInts lanes per ready atom, one per packed neighbour; of a long row, which
+    // the list row holds, lane q takes the slots q, q + kRowInts, ... (one lane on all
+    // of them: 128 000 atoms with 26 neighbours each 71 ms per build, 9.5 so)
     for (int e0 = 0; e0 < m; e0 += kFinishBlock / kRowInts) {
       const int e = e0 + t / kRowInts, q = t % kRowInts;
       const bool on = e < m;
       const int i = on ? (e < kFinishList ? S.list[r & 1][e] : in_g[e]) : 0;
       const int ent = on ? A.rows[(size_t)i * kRowInts + q] : kRowNone;
       const bool is_long = __shfl(ent, kRowInts - 1, kRowInts) == kRowLong;
-      const int j = ent & 0x7fffffff;
-      int c = on && !is_long && ent != kRowNone ? colour_of(j) : 64;  // 64: no neighbour
-      unsigned long long used = c >= 0 && c < 64 ? 1ull << c : 0ull;
-      if (is_long && q == 0) {
-        const unsigned long long cm = cmask[i];
-        for (int k = 0; k < 64; ++k)
-          if ((cm >> k) & 1ull) {
-            const int ck = colour_of(A.nbr[(size_t)k * A.ld + i]);
-            if (ck >= 0) used |= 1ull << (ck & 63);
-          }
-      }
+      auto take = [&](unsigned long long used) {  // the first colour none of the row has
 #pragma unroll
-      for (int o = 1; o < kRowInts; o <<= 1) used |= __shfl_xor(used, o, kRowInts);
-      if (on && q == 0) {
-        const int mine = __ffsll((long long)~used) - 1;
-        if (STATE) S.colour[i] = (unsigned char)mine;
-        else A.colour[i] = mine;
-      }
+        for (int o = 1; o < kRowInts; o <<= 1) used |= __shfl_xor(used, o, kRowInts);
+        if (on && q == 0) {
+          const int mine = __ffsll((long long)~used) - 1;
+          if (STATE) S.colour[i] = (unsigned char)mine;
+          else A.colour[i] = mine;
+        }
+      };
       auto release = [&](int jl) {  // an uncoloured later neighbour waits for one atom less
         bool last;
         if (STATE) {
@@ -568,15 +561,38 @@ __device__ __forceinline__ int colour_rounds(const ColourArgs &A, FinishLds &S, 
           else if (o < A.n) out_g[o] = jl;
         }
       };
-      if (on && !is_long) {
-        if (ent < 0 && c < 0) release(j);  // (kRowNone has c = 64)
-      } else if (on && q == 0) {
-        const unsigned long long later = cmask[i] & ~emask[i];
-        for (int k = 0; k < 64; ++k)
-          if ((later >> k) & 1ull) {
-            const int jl = A.nbr[(size_t)k * A.ld + i];
-            if (colour_of(jl) < 0) release(jl);
+      if (!__any(is_long)) {
+        const int j = ent & 0x7fffffff;
+        const int c = on && ent != kRowNone ? colour_of(j) : 64;  // 64: no neighbour
+        take(c >= 0 && c < 64 ? 1ull << c : 0ull);
+        if (on && ent < 0 && c < 0) release(j);  // (kRowNone has c = 64)
+      } else {
+        constexpr int kLong = 64 / kRowInts;
+        int j[kLong], c[kLong];
+        unsigned later = 0u;
+        if (is_long) {
+          const unsigned long long cm = cmask[i], lm = cm & ~emask[i];
+#pragma unroll
+          for (int h = 0; h < kLong; ++h) {
+            const int k = q + kRowInts * h;
+            j[h] = (cm >> k) & 1ull ? A.nbr[(size_t)k * A.ld + i] : -1;
+            later |= (unsigned)((lm >> k) & 1ull) << h;
           }
+        } else {
+#pragma unroll
+          for (int h = 0; h < kLong; ++h) j[h] = -1;
+          if (ent != kRowNone) j[0] = ent & 0x7fffffff;
+          later = ent < 0 ? 1u : 0u;
+        }
+#pragma unroll
+        for (int h = 0; h < kLong; ++h) c[h] = j[h] >= 0 ? colour_of(j[h]) : 64;
+        unsigned long long used = 0ull;
+#pragma unroll
+        for (int h = 0; h < kLong; ++h) used |= c[h] >= 0 && c[h] < 64 ? 1ull << c[h] : 0ull;
+        take(used);
+#pragma unroll
+        for (int h = 0; h < kLong; ++h)
+          if (c[h] < 0 && ((later >> h) & 1u)) release(j[h]);
       }
     }
     __syncthreads();
