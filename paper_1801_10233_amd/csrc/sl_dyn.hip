@@ -350,11 +350,14 @@ static void spin_phase_lanes2(const SysView<real> &S, const PotConst &P, const S
 template <typename real, int LANES>
 static void spin_phase_lanes(const SysView<real> &S, const PotConst &P, const SpinPhaseArgs &A,
                              const SysView<real> *S2, hipStream_t st) {
-  if (P.soc_on) spin_phase_lanes2<real, LANES, 4>(S, P, A, S2, st);
-  else if (S.jc) spin_phase_lanes2<real, LANES, 3>(S, P, A, S2, st);
-  else if (sizeof(real) == 4 && S.spl.t) spin_phase_lanes2<real, LANES, (sizeof(real) == 4 ? 2 : 0)>(S, P, A, S2, st);
-  else if (sizeof(real) == 4 && S.tab) spin_phase_lanes2<real, LANES, (sizeof(real) == 4 ? 1 : 0)>(S, P, A, S2, st);
-  else spin_phase_lanes2<real, LANES, 0>(S, P, A, S2, st);
+  constexpr bool f32 = sizeof(real) == 4;
+  switch (spin_variant(S, P, S2)) {
+    case 4: spin_phase_lanes2<real, LANES, 4>(S, P, A, S2, st); break;
+    case 3: spin_phase_lanes2<real, LANES, 3>(S, P, A, S2, st); break;
+    case 2: spin_phase_lanes2<real, LANES, (f32 ? 2 : 0)>(S, P, A, S2, st); break;
+    case 1: spin_phase_lanes2<real, LANES, (f32 ? 1 : 0)>(S, P, A, S2, st); break;
+    default: spin_phase_lanes2<real, LANES, 0>(S, P, A, S2, st); break;
+  }
 }
 
 template <typename real>
@@ -382,13 +385,15 @@ static void spin_tail_run(const SysView<real> &S, const PotConst &P, const TailA
 template <typename real>
 void launch_spin_tail(const SysView<real> &S, const PotConst &P, const TailArgs &T, hipStream_t st) {
   if (T.nitems <= 0) return;
-  if (P.soc_on) spin_tail_run<real, 4>(S, P, T, st);
-  else if (S.jc) spin_tail_run<real, 3>(S, P, T, st);
-  else if (sizeof(real) == 4 && S.spl.t) spin_tail_run<real, (sizeof(real) == 4 ? 2 : 0)>(S, P, T, st);
-  else if (sizeof(real) == 4 && S.tab) spin_tail_run<real, (sizeof(real) == 4 ? 1 : 0)>(S, P, T, st);
-  else spin_tail_run<real, 0>(S, P, T, st);
+  constexpr bool f32 = sizeof(real) == 4;
+  switch (spin_variant<real>(S, P, nullptr)) {
+    case 4: spin_tail_run<real, 4>(S, P, T, st); break;
+    case 3: spin_tail_run<real, 3>(S, P, T, st); break;
+    case 2: spin_tail_run<real, (f32 ? 2 : 0)>(S, P, T, st); break;
+    case 1: spin_tail_run<real, (f32 ? 1 : 0)>(S, P, T, st); break;
+    default: spin_tail_run<real, 0>(S, P, T, st); break;
+  }
 }
-
 
 template <typename real, int MLP>
 static void spin_lds_run(const SysView<real> &S, const PotConst &P, const SpinLdsArgs &A,

@@ -6,6 +6,18 @@
 namespace sl {
 
 // --- per-step kernels (sl_dyn.hip) ---
+// Pair terms of a spin launch: 4 with the spin-orbit terms, 3 from the exchange
+// cache, 2 from the spline, 1 from the pair table, 0 analytic from the positions.
+// A dual launch reads its coefficients at both sets of positions, so a cache
+// that is there for one of them only (the other's allocation failed) isn't used.
+template <typename real>
+inline int spin_variant(const SysView<real> &S, const PotConst &P, const SysView<real> *S2) {
+  if (P.soc_on) return 4;
+  if (S.jc && (!S2 || S2->jc)) return 3;
+  if (sizeof(real) == 4 && S.spl.t) return 2;
+  if (sizeof(real) == 4 && S.tab) return 1;
+  return 0;
+}
 // `lanes` (1, 2, 4 or 8) lanes cooperate on one atom (see TeamShape; in the
 // force launch each in its own wavefront of a workgroup).
 // With S2 (the same system at its other position buffer) the launch is the

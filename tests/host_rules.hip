@@ -1,0 +1,28 @@
+// Rules by which the host code picks kernels and launch shapes, printed as
+// "name value" lines (no device is used).
+#include <cstdio>
+
+#include "../paper_1801_10233_amd/csrc/sl_host.h"
+
+using namespace sl;
+
+template <typename real>
+static void variants(const char *tag) {
+  real c[1];
+  SysView<real> with{}, without{};
+  PotConst P{};
+  with.jc = c;
+  std::printf("%s_cache_at_both %d\n", tag, spin_variant(with, P, &with));
+  std::printf("%s_cache_at_first %d\n", tag, spin_variant(with, P, &without));
+  std::printf("%s_cache_at_second %d\n", tag, spin_variant(without, P, &with));
+  std::printf("%s_cache_single %d\n", tag, spin_variant<real>(with, P, nullptr));
+  float4 t[1];
+  with.spl.t = without.spl.t = t;
+  std::printf("%s_spline_cache_at_first %d\n", tag, spin_variant(with, P, &without));
+}
+
+int main() {
+  variants<double>("fp64");
+  variants<float>("fp32");
+  return 0;
+}

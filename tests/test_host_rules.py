@@ -1,0 +1,28 @@
+"""Rules by which the host code picks kernels and launch shapes, from its own
+headers compiled as a host program (no GPU)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    exe = str(tmp_path_factory.mktemp("host_rules") / "host_rules")
+    subprocess.run([hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature",
+                    "-Xclang", "-packed-fp32-ops", "-o", exe, os.path.join(HERE, "host_rules.hip")],
+                   check=True, capture_output=True, text=True)
+    out = subprocess.run([exe], check=True, capture_output=True, text=True).stdout
+    return {k: int(v) for k, v in (line.split() for line in out.splitlines())}
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_dual_launch_needs_the_cache_at_both_positions(rules, precision):
+    # 3 reads the exchange cache, 2 the spline, 0 the positions
+    assert rules[precision + "_cache_at_both"] == rules[precision + "_cache_single"] == 3
+    assert rules[precision + "_cache_at_first"] == rules[precision + "_cache_at_second"] == 0
+    assert rules[precision + "_spline_cache_at_first"] == (2 if precision == "fp32" else 0)
