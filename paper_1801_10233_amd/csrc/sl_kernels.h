@@ -105,6 +105,11 @@ void launch_scan(const int *in, int *out, int n, hipStream_t st);
 // result does not depend on the order the atomics were served in.
 void launch_bucket_scatter(int n, const int *key, const int *start, int *fill, int *out,
                            hipStream_t st);
+// Workgroups of a bucket sort, a wavefront per bucket up to 16 384 wavefronts (twice
+// what the device holds).
+constexpr int bucket_sort_blocks(int nbucket) {
+  return nbucket < 4096 * (kBlock / 64) ? (nbucket + kBlock / 64 - 1) / (kBlock / 64) : 4096;
+}
 void launch_bucket_sort(int nbucket, const int *start, int *items, hipStream_t st);
 // Each bucket's items ascending by (x[item], item).
 void launch_bucket_sort_x(int nbucket, const int *start, int *items, const double *x,

@@ -123,15 +123,14 @@ __device__ __forceinline__ void bucket_sort_one(int a, int e, int *items, const 
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_bucket_sort_x(int nbucket, const int *start, int *items,
-                                                          const double *x) {
-  const int b = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  if (b < nbucket) bucket_sort_one<true>(start[b], start[b + 1], items, x);
-}
-
-__global__ __launch_bounds__(kBlock) void k_bucket_sort(int nbucket, const int *start, int *items) {
-  const int b = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  if (b < nbucket) bucket_sort_one<false>(start[b], start[b + 1], items, nullptr);
+// (a wavefront takes every so many buckets: one each would be more threads than a
+// launch may have in a box with tens of millions of cells or lattice rows)
+template <bool BYX>
+__global__ __launch_bounds__(kBlock) void k_bucket_sort(int nbucket, const int *start, int *items,
+                                                        const double *x) {
+  const long nwave = (long)gridDim.x * (kBlock / 64);
+  for (long b = (long)blockIdx.x * (kBlock / 64) + wave_id(); b < nbucket; b += nwave)
+    bucket_sort_one<BYX>(start[b], start[b + 1], items, x);
 }
 
 __global__ void k_cell_positions(int n, const int *catoms, const double *rx, const double *ry,
@@ -811,14 +810,14 @@ void launch_bucket_scatter(int n, const int *key, const int *start, int *fill, i
 }
 void launch_bucket_sort_x(int nbucket, const int *start, int *items, const double *x,
                           hipStream_t st) {
-  if (nbucket > 0) hipLaunchKernelGGL(k_bucket_sort_x, dim3((unsigned)(((long)nbucket * 64 + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, nbucket, start, items, x);
+  if (nbucket > 0) hipLaunchKernelGGL(k_bucket_sort<true>, dim3(bucket_sort_blocks(nbucket)), dim3(kBlock), 0, st, nbucket, start, items, x);
 }
 void launch_cell_positions(int n, const int *catoms, const double *rx, const double *ry,
                            const double *rz, double *cx, double *cy, double *cz, hipStream_t st) {
   if (n > 0) hipLaunchKernelGGL(k_cell_positions, dim3(nblocks(n)), dim3(kBlock), 0, st, n, catoms, rx, ry, rz, cx, cy, cz);
 }
 void launch_bucket_sort(int nbucket, const int *start, int *items, hipStream_t st) {
-  if (nbucket > 0) hipLaunchKernelGGL(k_bucket_sort, dim3((unsigned)(((long)nbucket * 64 + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, nbucket, start, items);
+  if (nbucket > 0) hipLaunchKernelGGL(k_bucket_sort<false>, dim3(bucket_sort_blocks(nbucket)), dim3(kBlock), 0, st, nbucket, start, items, (const double *)nullptr);
 }
 void launch_nbr_build(const NbrBuildArgs &A, hipStream_t st) {
   if (A.n <= 0) return;

@@ -24,5 +24,7 @@ static void variants(const char *tag) {
 int main() {
   variants<double>("fp64");
   variants<float>("fp32");
+  for (long nbucket : {1L, 5L, 16384L, 1L << 26, 1L << 30})
+    std::printf("sort_threads_%ld %ld\n", nbucket, (long)bucket_sort_blocks((int)nbucket) * kBlock);
   return 0;
 }

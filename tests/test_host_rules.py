@@ -26,3 +26,11 @@ def test_dual_launch_needs_the_cache_at_both_positions(rules, precision):
     assert rules[precision + "_cache_at_both"] == rules[precision + "_cache_single"] == 3
     assert rules[precision + "_cache_at_first"] == rules[precision + "_cache_at_second"] == 0
     assert rules[precision + "_spline_cache_at_first"] == (2 if precision == "fp32" else 0)
+
+
+def test_bucket_sort_launch_is_within_the_device_limit(rules):
+    # at most 2^32 - 1 threads in a launch: cells (two per atom) and lattice rows
+    # times colours can be 2^26 and more
+    for nbucket in (1, 5, 16384, 1 << 26, 1 << 30):
+        threads = rules[f"sort_threads_{nbucket}"]
+        assert 64 <= threads < 1 << 32 and threads >= 64 * min(nbucket, 16384)
