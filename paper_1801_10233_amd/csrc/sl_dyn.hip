@@ -278,8 +278,8 @@ void launch_jcache(const SysView<real> &S, const PotConst &P, real *out, double 
   if (S.n <= 0) return;
   const int nx = tiles ? ntiles : (S.n + kBlock - 1) / kBlock;
   const bool split = S.n < kJcSplitAtoms && max_slots > SL_JC_CHUNK;
-  const int slots = split ? SL_JC_CHUNK : INT_MAX / 2;
-  const dim3 grid(nx, split ? (max_slots + SL_JC_CHUNK - 1) / SL_JC_CHUNK : 1);
+  const int slots = split ? slots_per_group(max_slots, SL_JC_CHUNK) : INT_MAX / 2;
+  const dim3 grid(nx, split ? (max_slots + slots - 1) / slots : 1);
   if (S.spl.t) hipLaunchKernelGGL((k_jcache<real, true>), grid, dim3(kBlock), 0, st, S, P, out, rs2, tiles, slots);
   else hipLaunchKernelGGL((k_jcache<real, false>), grid, dim3(kBlock), 0, st, S, P, out, rs2, tiles, slots);
 }

@@ -57,6 +57,14 @@ void launch_batch_run(RepDesc<real> *D, int R, int lanes, int variant, hipStream
 // of a view, before the force launch that reads them.
 template <typename real>
 void launch_eam_density(const SysView<real> &S, const PotConst &P, hipStream_t st);
+// Launches over (atom, slot of its row) put the slots on grid.y, at most this many
+// groups of them: a list's capacity is the caller's, and a row may have any length.
+constexpr int kSlotGroups = 128;
+// Slots of one group when rows of up to max_slots go in groups of whole rounds of
+// `round` slots.
+constexpr int slots_per_group(int max_slots, int round) {
+  return (((max_slots + round - 1) / round + kSlotGroups - 1) / kSlotGroups) * round;
+}
 // Exchange-coefficient cache: J(r_ij) per spin-segment entry (ELL layout);
 // tiles (or null): atom range of each 256-thread block; max_slots: the
 // largest spin segment.

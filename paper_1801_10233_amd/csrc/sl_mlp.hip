@@ -325,35 +325,39 @@ __global__ void k_mlp_pair_count(int n, int ld, const int *nbr, const int *nall,
   cnt[i] = c;
 }
 
-// One thread per list entry (blockIdx.y = slot): its place among the atom's
-// j > i entries, then the search of i in the row of j. (One thread per atom
-// walked the rows of all its neighbours one after another: 16 000 atoms 560 us.)
+// One thread per list entry (blockIdx.y = slot, beyond kSlotGroups slots every so
+// many): its place among the atom's j > i entries, then the search of i in the row
+// of j. (One thread per atom walked the rows of all its neighbours one after
+// another: 16 000 atoms 560 us.)
 __global__ __launch_bounds__(256) void k_mlp_pair_fill(int n, int ld, const int *nbr,
                                                        const int *nall, const int *start,
                                                        int2 *pairs, int *mirror, int *err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
-  if (i >= n || k >= nall[i]) return;
-  const int j = nbr[(size_t)k * ld + i];
-  if (j <= i) return;
-  int p = start[i];
-  for (int q = 0; q < k; ++q) p += nbr[(size_t)q * ld + i] > i;
-  int kk = -1;
-  const int nj = nall[j];
-  constexpr int CH = 8;  // entries whose loads go out together
-  for (int q0 = 0; q0 < nj && kk < 0; q0 += CH) {
-    int v[CH];
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int ni = nall[i];
+  for (int k = blockIdx.y; k < ni; k += gridDim.y) {
+    const int j = nbr[(size_t)k * ld + i];
+    if (j <= i) continue;
+    int p = start[i];
+    for (int q = 0; q < k; ++q) p += nbr[(size_t)q * ld + i] > i;
+    int kk = -1;
+    const int nj = nall[j];
+    constexpr int CH = 8;  // entries whose loads go out together
+    for (int q0 = 0; q0 < nj && kk < 0; q0 += CH) {
+      int v[CH];
 #pragma unroll
-    for (int q = 0; q < CH; ++q) v[q] = q0 + q < nj ? nbr[(size_t)(q0 + q) * ld + j] : -1;
+      for (int q = 0; q < CH; ++q) v[q] = q0 + q < nj ? nbr[(size_t)(q0 + q) * ld + j] : -1;
 #pragma unroll
-    for (int q = CH - 1; q >= 0; --q)
-      if (v[q] == i) kk = q0 + q;
+      for (int q = CH - 1; q >= 0; --q)
+        if (v[q] == i) kk = q0 + q;
+    }
+    if (kk < 0) {  // asymmetric list: cannot mirror
+      atomicOr(err, kErrNbrOverflow);
+      kk = k;
+    }
+    pairs[p] = make_int2(i, k);
+    mirror[p] = kk;
   }
-  if (kk < 0) {  // asymmetric list: cannot mirror
-    atomicOr(err, kErrNbrOverflow);
-    kk = k;
-  }
-  pairs[p] = make_int2(i, k);
-  mirror[p] = kk;
 }
 
 void launch_mlp_pair_count(int n, int ld, const int *nbr, const int *nall, int *cnt,
@@ -364,7 +368,7 @@ void launch_mlp_pair_count(int n, int ld, const int *nbr, const int *nall, int *
 void launch_mlp_pair_fill(int n, int ld, int max_row, const int *nbr, const int *nall,
                           const int *start, int2 *pairs, int *mirror, int *err, hipStream_t st) {
   if (n > 0 && max_row > 0)
-    hipLaunchKernelGGL(k_mlp_pair_fill, dim3((n + 255) / 256, max_row), dim3(256), 0, st, n, ld, nbr,
+    hipLaunchKernelGGL(k_mlp_pair_fill, dim3((n + 255) / 256, std::min(max_row, kSlotGroups)), dim3(256), 0, st, n, ld, nbr,
                        nall, start, pairs, mirror, err);
 }
 

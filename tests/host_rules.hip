@@ -26,5 +26,10 @@ int main() {
   variants<float>("fp32");
   for (long nbucket : {1L, 5L, 16384L, 1L << 26, 1L << 30})
     std::printf("sort_threads_%ld %ld\n", nbucket, (long)bucket_sort_blocks((int)nbucket) * kBlock);
+  for (int rows : {1, 5, 6, 63, 80, 640, 641, 400000}) {
+    const int slots = slots_per_group(rows, 5);
+    std::printf("slots_%d %d\n", rows, slots);
+    std::printf("groups_%d %d\n", rows, (rows + slots - 1) / slots);
+  }
   return 0;
 }

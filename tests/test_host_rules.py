@@ -34,3 +34,10 @@ def test_bucket_sort_launch_is_within_the_device_limit(rules):
     for nbucket in (1, 5, 16384, 1 << 26, 1 << 30):
         threads = rules[f"sort_threads_{nbucket}"]
         assert 64 <= threads < 1 << 32 and threads >= 64 * min(nbucket, 16384)
+
+
+def test_slot_groups_are_bounded_and_cover_the_row(rules):
+    for rows in (1, 5, 6, 63, 80, 640, 641, 400000):
+        slots, groups = rules[f"slots_{rows}"], rules[f"groups_{rows}"]
+        assert slots % 5 == 0 and slots * groups >= rows and groups <= 128
+        assert slots == 5 or rows > 640            # one round per group up to there
