@@ -175,7 +175,7 @@ template <typename real>
 struct SysView {
   int n;          // atoms
   int ld;         // leading dimension of the ELL lists (>= n, padded)
-  int kcap;       // slots per ELL row (list capacity)
+  int kcap;       // slots per ELL row (list capacity; that of jc where it is set)
   double L[3], invL[3];
   const double *rx, *ry, *rz;  // positions used by this launch
   real *sx, *sy, *sz;          // spins

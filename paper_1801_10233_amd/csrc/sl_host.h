@@ -161,6 +161,7 @@ struct sl_system {
   void *jc[2] = {nullptr, nullptr};
   double *eam = nullptr;  // embedded-atom F'(rho), F(rho) per atom [2][ld]
   bool jc_ok[2] = {false, false};
+  int jc_rows[2] = {0, 0};  // slots per row that each cache was allocated for
 
   bool prof = false;
   int prof_every = 1;     // time the launches of every prof_every-th step
@@ -263,6 +264,10 @@ inline bool jcache_on(const sl_system *S) {
   return S->prm.frozen || spin_lds_on(S) || S->pc.langevin || S->K >= 7 || S->n > 4 * kSpinFull;
 }
 
+// Slots per row of the exchange cache: spin-segment entries only, so the segment's
+// capacity (a caller's list may hold more, up to the row's).
+inline int jcache_rows(const sl_system *S) { return S->user_list ? S->max_nbr : S->max_spin; }
+
 template <typename T>
 inline hipError_t dalloc(T **p, size_t count) {
   *p = nullptr;
@@ -303,6 +308,7 @@ inline SysView<real> view(sl_system *S, int posbuf) {
   v.spl = SplineView{};
   const bool jc_use = (!S->mlp || S->mlp_mode == SL_MLP_SPLINE) && jcache_on(S) && !S->pc.soc_on;
   v.jc = (jc_use && S->jc_ok[posbuf]) ? (const real *)S->jc[posbuf] : nullptr;
+  if (v.jc) v.kcap = jcache_rows(S);
   v.eam = S->pc.eam_on ? S->eam : nullptr;
   v.held = 0;
   if (S->mlp && S->mlp_mode == SL_MLP_SPLINE) {

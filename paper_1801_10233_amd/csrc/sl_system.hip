@@ -230,10 +230,15 @@ template <typename real>
 int ensure_jcache(sl_system *S, int b) {
   if ((S->mlp && S->mlp_mode != SL_MLP_SPLINE) || !jcache_on(S) || S->pc.soc_on || S->jc_ok[b])
     return SL_OK;
-  if (!S->jc[b]) {
+  const int rows = jcache_rows(S);
+  if (S->jc_rows[b] < rows) {
+    dfree(S->jc[b]);
+    S->jc[b] = nullptr;
+    S->jc_rows[b] = 0;
     real *p = nullptr;
-    HIPCHK(S, dalloc(&p, (size_t)S->ld * S->max_nbr));
+    HIPCHK(S, dalloc(&p, (size_t)S->ld * rows));
     S->jc[b] = p;
+    S->jc_rows[b] = rows;
   }
   SysView<real> v = view<real>(S, b);
   {
@@ -1233,6 +1238,7 @@ int sl_set_neighbor(sl_system *S, double skin, int max_nbr) {
       }
       dfree(S->jc[b]);  // reallocated at the next use with the new capacity
       S->jc[b] = nullptr;
+      S->jc_rows[b] = 0;
       S->jc_ok[b] = false;
     }
   }

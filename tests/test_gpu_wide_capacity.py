@@ -1,6 +1,7 @@
 """A list capacity far above the rows it holds (the caller's choice, which also
 bounds the launches over slots) changes nothing: the learned potential's pairs and
 the exchange cache of a caller's list, 128 atoms, bit for bit as with the default."""
+import ctypes
 import os
 
 import numpy as np
@@ -11,6 +12,13 @@ from paper_1801_10233_amd import workloads as W
 from tests.common import make_gpu
 
 pytestmark = pytest.mark.gpu
+
+
+def _free_bytes():
+    hip = ctypes.CDLL("libamdhip64.so.7")
+    free, total = ctypes.c_size_t(), ctypes.c_size_t()
+    assert hip.hipMemGetInfo(ctypes.byref(free), ctypes.byref(total)) == 0
+    return free.value
 
 
 def _states_equal(a, b):
@@ -48,3 +56,45 @@ def test_exchange_cache_of_a_callers_list(precision):
         g.step(5, w.dt)
         runs.append(g)
     _states_equal(*runs)
+
+
+@pytest.mark.parametrize("precision", [sl.SL_FP64, sl.SL_FP32])
+def test_exchange_cache_is_sized_by_the_spin_segment(precision):
+    # 8192 atoms, rows of up to 4000 slots, at most 32 of them in the spin segment:
+    # two caches of 32 slots are 4.2 MB in FP64, of 4000 slots 524 MB
+    w = W.large_langevin(n=16)
+    g = make_gpu(w, precision=precision, max_nbr=4000)
+    g.set_tuning(2, 2, -1, 1)
+    g.step(0, w.dt)
+    free0 = _free_bytes()
+    g.step(2, w.dt)
+    g.synchronize()
+    assert free0 - _free_bytes() < 64 << 20
+
+
+def test_exchange_cache_follows_a_callers_longer_rows():
+    # the spin segment of a caller's list may be longer than max_spin_nbr: the caches
+    # of the built list (16 slots) grow for it, and the run
+    # is the one of a system that held the list from the start
+    w = W.coupled_nve(n=6)
+    w.pot = dict(w.pot, ex_rc=4.2)
+    full = make_gpu(w)
+    full.step(0, w.dt)
+    _, na, rows = full.neighbor_list()
+    off, idx = np.concatenate([[0], np.cumsum(na)]), np.concatenate(rows)
+    runs = []
+    for first in (True, False):
+        g = make_gpu(w, max_spin_nbr=16)
+        g.set_tuning(2, 2, -1, 1)
+        if first:                              # caches of 16 slots, at both positions
+            short = dict(w.pot, ex_rc=3.5)
+            g.set_potential(short)
+            g.step(3, w.dt)
+            g.set_potential(w.pot)
+            g.set_state(w.r, w.v, w.s)
+            g.set_step(0)
+        g.set_neighbor_list(off, idx)
+        g.step(5, w.dt)
+        runs.append(g)
+    for x, y in zip(runs[0].get_state(), runs[1].get_state()):
+        assert np.abs(x - y).max() < 1e-12 * max(1.0, np.abs(y).max())
