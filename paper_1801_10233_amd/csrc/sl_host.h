@@ -428,6 +428,7 @@ int jp_rounds(sl_system *S, const ColourArgs &C);
 int mlp_pairs(sl_system *S);
 int colour_and_permute(sl_system *S, bool repair);
 int build_list(sl_system *S);
+int read_build(sl_system *S);
 int rebuild(sl_system *S);
 int ensure_ready(sl_system *S);
 

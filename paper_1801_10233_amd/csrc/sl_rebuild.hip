@@ -287,7 +287,7 @@ int colour_and_permute(sl_system *S, bool repair) {
 
 // Cells and neighbour list at the current positions. The build's error word and
 // largest rows stay on the device: they are read back with the colouring's report
-// (one host synchronisation for both), or by a caller that needs no colours.
+// (one host synchronisation for both), or by read_build.
 int build_list(sl_system *S) {
   CHK(check_box(S));
   {
@@ -331,6 +331,16 @@ int build_list(sl_system *S) {
   }
   S->have_list = true;
   S->rebuilds++;
+  return SL_OK;
+}
+
+// Error word and largest rows of a list that is used without colours.
+int read_build(sl_system *S) {
+  launch_rebuild_report(S->jpcnt, S->err, S->seen, S->pin_dev, S->st);
+  HIPCHK(S, hipStreamSynchronize(S->st));
+  S->sticky |= S->pin[6];
+  S->seen_spin = S->pin[7];
+  S->seen_all = S->pin[8];
   return SL_OK;
 }
 

@@ -77,7 +77,7 @@ int sl_mlp_loss_grad(sl_mlp *m, const sl_dataset *d, int snap, const double w[3]
   // colouring of 16 000 atoms took longer than all else here) and no permutation
   rc = build_list(S);
   if (!rc) rc = mlp_pairs(S);
-  if (!rc) rc = read_err(S);
+  if (!rc) rc = read_build(S);
   if (!rc) rc = sticky_code(S);
   if (!rc) rc = ensure_table(S, S->pos);
   if (rc) return mfail_str(m, rc, S->last_err);
