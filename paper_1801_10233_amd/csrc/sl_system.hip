@@ -1056,7 +1056,6 @@ int sl_destroy(sl_system *S) {
     (void)hipEventDestroy(r.b);
   }
   for (auto e : S->ev_pool) (void)hipEventDestroy(e);
-  for (int k = 0; k < 4; ++k)
   free_atoms(S->a[0]);
   free_atoms(S->a[1]);
   for (void *p : {(void *)S->ccount, (void *)S->cstart, (void *)S->cfill, (void *)S->catoms,
