@@ -167,6 +167,18 @@ TUNE_STEPS = 50      # steps per autotuner window (ten launch shapes, four round
 SUSTAINED_STEPS = 1000  # steps per window of the sustained (rebuilds included) figure
 
 
+def default_spin_lanes(precision, class_atoms, jcache):
+    """Lanes per atom that the library's default takes for a class of this size."""
+    if class_atoms <= 3000:
+        return 8
+    return 1 if class_atoms > 70000 and precision == sl.SL_FP64 and jcache else 4
+
+
+def default_force_lanes(n_atoms):
+    """Lanes per atom that the library's default takes for the force launch."""
+    return 8 if n_atoms <= 12000 else (4 if n_atoms <= 120000 else 1)
+
+
 def timed_run(S, steps, dt, profile=False):
     S.synchronize()
     sync()
@@ -565,14 +577,19 @@ def main():
     launches, ms, work = kinds[dom]
     n_prof = kinds[sl.PROF_FORCE][0]          # one force launch per timed step
     tun = S.tuning()
-    jc_on = tun["jcache"] > 0
+    # (the table launches of an analytic run are the exchange cache's)
+    jc_on = tun["jcache"] > 0 or (tun["jcache"] == 0 and sl.PROF_TABLE in kinds)
+    if (tun["spin_lanes"], tun["force_lanes"], tun["jcache"]) == (2, 1, 0):  # the default
+        tun = dict(tun, spin_lanes=0, force_lanes=0)
+    spin_lanes = tun["spin_lanes"] or default_spin_lanes(prec, w.N / st["n_colours"], jc_on)
+    force_lanes = tun["force_lanes"] or default_force_lanes(w.N)
     # the method's bytes per update; the cached form reads its 14 coefficients
     # in place of the own position (moved_bytes_per_unit), which makes the
     # launch faster but is not counted as more work done
     per_unit = SPIN_BYTES[prec] if dom == sl.PROF_SPIN else FORCE_BYTES[prec]
     moved_unit = (SPIN_BYTES_JC if jc_on else SPIN_BYTES)[prec] if dom == sl.PROF_SPIN else per_unit
-    shape = (f"lanes={tun['spin_lanes']},jcache={int(jc_on)}" if dom == sl.PROF_SPIN
-             else f"lanes={tun['force_lanes']}")
+    shape = (f"lanes={spin_lanes},jcache={int(jc_on)}" if dom == sl.PROF_SPIN
+             else f"lanes={force_lanes}")
     step_bytes = STEP_BYTES[prec]
     avg_ms = ms / launches
     bytes_per_launch = per_unit * work / launches

@@ -297,7 +297,10 @@ int sl_synchronize(sl_system *sys);
  * its size, in the force launch from the number of atoms (a value set there is
  * the least number taken; a system too small to fill the device takes more),
  * and the spin half-steps of a system of a few thousand atoms in one workgroup
- * (spin_lanes and jcache both 0). sl_get_tuning reports the defaults as 2 and 1.
+ * (spin_lanes and jcache both 0). sl_get_tuning reports a field at its default
+ * as 0, and all three of spin_lanes, force_lanes and jcache at their defaults as
+ * 2, 1 and 0, which sl_set_tuning takes for the default too: setting what is
+ * reported, on this system or another, leaves or makes the launches the same.
  * Runs of consecutive colour classes of at most small_class atoms each are
  * applied by one single-workgroup launch (0 = default 128, -1 = never). */
 typedef struct {
@@ -310,7 +313,7 @@ typedef struct {
                          read by the spin phases; 0 = default (on for the
                          FP32 form; for FP64 on where it pays: with the spin
                          bath, with seven or more classes, in large systems
-                         and on frozen lattices, reported as -1), 1 on, -1 off */
+                         and on frozen lattices), 1 on, -1 off */
     int overlap;      /* split force (analytic potentials, 1 or 2 force
                          lanes): the spin-independent pair terms of a step's
                          closing force run on a second stream of the library

@@ -76,7 +76,7 @@ struct sl_system {
   // lanes per atom (tuning only); while a field of the tuning is left at its
   // default the launches take the shape of the rules below instead
   int spin_lanes = 2, force_lanes = 1;
-  bool spin_auto = true, jc_auto = true;
+  bool spin_auto = true, force_auto = true, jc_auto = true;
   // Runs of consecutive classes of at most this many atoms share one
   // single-workgroup launch (-1: never). Meant for the few-atom classes a
   // colour repair adds; at 500 atoms per class (2000-atom lattice) separate

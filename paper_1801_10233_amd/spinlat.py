@@ -384,6 +384,8 @@ class System:
         self._check(lib().sl_set_tuning(self.h, C.byref(t)))
 
     def tuning(self):
+        """The launch shape as set: 0 for a default field, and 2, 1 and 0 for spin_lanes,
+        force_lanes and jcache all at their defaults; set_tuning(**tuning()) keeps it."""
         t = sl_tuning()
         self._check(lib().sl_get_tuning(self.h, C.byref(t)))
         return dict(spin_lanes=t.spin_lanes, force_lanes=t.force_lanes,

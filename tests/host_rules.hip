@@ -31,5 +31,19 @@ int main() {
     std::printf("slots_%d %d\n", rows, slots);
     std::printf("groups_%d %d\n", rows, (rows + slots - 1) / slots);
   }
+  for (int prec : {SL_FP64, SL_FP32})
+    for (int jc : {-1, 1})
+      for (int m : {1, 3000, 3001, 70000, 70001, 108000}) {
+        sl_system S;
+        S.prec = prec;
+        S.jcache = jc;
+        S.jc_auto = false;
+        std::printf("spin_lanes_%d_%d_%d %d\n", prec, jc, m, spin_lanes_for(&S, m));
+      }
+  for (int n : {1, 12000, 12001, 120000, 120001, 432000}) {
+    sl_system S;
+    S.n = n;
+    std::printf("force_lanes_%d %d\n", n, force_lanes_for(&S));
+  }
   return 0;
 }

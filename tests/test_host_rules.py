@@ -41,3 +41,15 @@ def test_slot_groups_are_bounded_and_cover_the_row(rules):
         slots, groups = rules[f"slots_{rows}"], rules[f"groups_{rows}"]
         assert slots % 5 == 0 and slots * groups >= rows and groups <= 128
         assert slots == 5 or rows > 640            # one round per group up to there
+
+
+def test_benchmark_reports_the_default_lanes(rules):
+    import sys
+    sys.path.insert(0, os.path.dirname(HERE))
+    import bench
+    for prec in (bench.sl.SL_FP64, bench.sl.SL_FP32):
+        for jc in (-1, 1):
+            for m in (1, 3000, 3001, 70000, 70001, 108000):
+                assert rules[f"spin_lanes_{prec}_{jc}_{m}"] == bench.default_spin_lanes(prec, m, jc > 0)
+    for n in (1, 12000, 12001, 120000, 120001, 432000):
+        assert rules[f"force_lanes_{n}"] == bench.default_force_lanes(n)
