@@ -163,7 +163,7 @@ def sync():
 
 PROFILE_EVERY = 50   # HIP events bracket the launches of every 50th timed step (every 10th
                      # cost 8.5 us per step at 432 000 atoms, with the same per-launch means)
-TUNE_STEPS = 50      # steps per autotuner window (ten launch shapes, four rounds)
+TUNE_STEPS = 50      # steps per autotuner window (up to eleven launch shapes, four rounds)
 SUSTAINED_STEPS = 1000  # steps per window of the sustained (rebuilds included) figure
 
 

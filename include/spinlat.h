@@ -326,9 +326,9 @@ int sl_set_tuning(sl_system *sys, const sl_tuning *t);
 int sl_get_tuning(sl_system *sys, sl_tuning *t);
 
 /* Autotuner. Runs windows of `steps` steps of length dt under each
- * candidate launch shape (spin lanes 1, 2, 4, 8; force lanes 1, 2; the
- * exchange-coefficient cache on or off; the default, where it runs the spin
- * half-steps in one workgroup) on a scratch copy of the system
+ * candidate launch shape (the default; spin lanes 1, 2, 4, 8 with the
+ * exchange-coefficient cache on or off; 2 force lanes; shapes whose launches
+ * would be the same once) on a scratch copy of the system
  * (same parameters, interactions, learned potential, user list, state and
  * step counter; its own stream and memory, freed before returning), times
  * each whole window with HIP events on the copy's stream (a window with a

@@ -264,6 +264,54 @@ inline bool jcache_on(const sl_system *S) {
   return S->prm.frozen || spin_lds_on(S) || S->pc.langevin || S->K >= 7 || S->n > 4 * kSpinFull;
 }
 
+// Fields of a valid tuning; (2, 1, 0) is what sl_get_tuning reports for the default of
+// spin lanes, force lanes and cache together.
+inline void apply_tuning(sl_system *S, const sl_tuning &t) {
+  const bool all = t.spin_lanes == 2 && t.force_lanes == 1 && t.jcache == 0;
+  S->spin_auto = all || t.spin_lanes == 0;
+  S->force_auto = all || t.force_lanes == 0;
+  S->jc_auto = t.jcache == 0;
+  S->spin_lanes = S->spin_auto ? 2 : t.spin_lanes;
+  S->force_lanes = S->force_auto ? 1 : t.force_lanes;
+  S->small_class = t.small_class == 0 ? kSmallClassDefault : t.small_class;
+  S->jcache = S->jc_auto ? (S->prec == SL_FP32 ? 1 : -1) : t.jcache;
+  S->overlap = t.overlap == 0 ? -1 : t.overlap;
+}
+
+// What the launches of a step look like under the tuning as set: lanes of every
+// class's spin launches (0: all in one workgroup), of the force launch (0: none) and
+// whether the cache is read.
+inline std::vector<int> launch_shape(const sl_system *S) {
+  std::vector<int> v;
+  const bool one = spin_lds_on(S);
+  for (int c = 0; c < S->K; ++c) v.push_back(one ? 0 : spin_lanes_for(S, S->class_off[c + 1] - S->class_off[c]));
+  v.push_back(S->prm.frozen ? 0 : force_lanes_for(S));
+  v.push_back(jcache_on(S) && !S->pc.soc_on && (!S->mlp || S->mlp_mode == SL_MLP_SPLINE));
+  return v;
+}
+
+// Shapes for the autotuner to time: first the default, which picks the lanes class by
+// class (or one workgroup) as no uniform shape does, then uniform ones; force lanes by
+// rule, and 2, which the rule never takes. A shape that launches what an earlier one
+// does is left out.
+inline std::vector<sl_tuning> tune_candidates(const sl_system *S) {
+  const int shape[][3] = {{0, 0, 0}, {1, 0, 1}, {2, 0, 1}, {4, 0, 1}, {8, 0, 1}, {1, 0, -1}, {2, 0, -1},
+                          {4, 0, -1}, {8, 0, -1}, {1, 2, 1}, {2, 2, -1}};
+  std::vector<sl_tuning> out;
+  std::vector<std::vector<int>> seen;
+  for (const auto &s : shape) {
+    const sl_tuning t{s[0], s[1], S->small_class, s[2], S->overlap};
+    sl_system D = *S;
+    D.prof = false;
+    apply_tuning(&D, t);
+    const std::vector<int> v = launch_shape(&D);
+    if (std::find(seen.begin(), seen.end(), v) != seen.end()) continue;
+    seen.push_back(v);
+    out.push_back(t);
+  }
+  return out;
+}
+
 // Slots per row of the exchange cache: spin-segment entries only, so the segment's
 // capacity (a caller's list may hold more, up to the row's).
 inline int jcache_rows(const sl_system *S) { return S->user_list ? S->max_nbr : S->max_spin; }

@@ -1529,16 +1529,7 @@ int sl_set_tuning(sl_system *S, const sl_tuning *t) {
   if (t->jcache < -1 || t->jcache > 1) return fail(S, SL_E_ARG, "jcache must be -1, 0 or 1");
   if (t->overlap < -1 || t->overlap > 1) return fail(S, SL_E_ARG, "overlap must be -1, 0 or 1");
   CHK(sl_synchronize(S));
-  // (2, 1, 0) is what sl_get_tuning reports for the default of all three
-  const bool all = t->spin_lanes == 2 && t->force_lanes == 1 && t->jcache == 0;
-  S->spin_auto = all || t->spin_lanes == 0;
-  S->force_auto = all || t->force_lanes == 0;
-  S->jc_auto = t->jcache == 0;
-  S->spin_lanes = S->spin_auto ? 2 : t->spin_lanes;
-  S->force_lanes = S->force_auto ? 1 : t->force_lanes;
-  S->small_class = t->small_class == 0 ? kSmallClassDefault : t->small_class;
-  S->jcache = S->jc_auto ? (S->prec == SL_FP32 ? 1 : -1) : t->jcache;
-  S->overlap = t->overlap == 0 ? -1 : t->overlap;
+  apply_tuning(S, *t);
   return SL_OK;
 }
 

@@ -133,16 +133,9 @@ int sl_autotune(sl_system *S, int steps, double dt, sl_tuning *chosen) {
     // kernels (it shares the caches with them) are part of the comparison.
     // A window with a list rebuild in it is run again; four rounds over
     // all candidates, the best window of each counts.
-    // (8 lanes per atom pays on small lattices: every class is then many
-    // wavefronts instead of a few)
-    // The last candidate is the default, for the small systems whose spin
-    // half-steps it runs in one workgroup (no set shape does).
-    constexpr int kTrials = 11;
-    const int trial[kTrials][3] = {{2, 1, -1}, {1, 1, 1}, {2, 1, 1}, {1, 1, -1}, {4, 1, 1},
-                                   {4, 1, -1}, {2, 2, -1}, {1, 2, 1}, {8, 1, -1}, {8, 2, -1},
-                                   {0, 0, 0}};
-    double best[kTrials];
-    for (double &b : best) b = 1e300;
+    const std::vector<sl_tuning> trial = tune_candidates(S);
+    const int ntrial = (int)trial.size();
+    std::vector<double> best(ntrial, 1e300);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = SL_OK;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = SL_E_HIP;
@@ -152,11 +145,9 @@ int sl_autotune(sl_system *S, int steps, double dt, sl_tuning *chosen) {
     // the order of the candidates rotates from round to round, so no shape
     // always follows the same other one
     for (int pass = 0; pass < 4 && rc == SL_OK; ++pass)
-      for (int q = 0; q < kTrials && rc == SL_OK; ++q) {
-        const int t = (q + 3 * pass) % kTrials;
-        sl_tuning tt{trial[t][0], trial[t][1], S->small_class, trial[t][2], S->overlap};
-        if ((rc = sl_set_tuning(C, &tt))) break;
-        if (trial[t][0] == 0 && !spin_lds_on(C)) continue;
+      for (int q = 0; q < ntrial && rc == SL_OK; ++q) {
+        const int t = (q + 3 * pass) % ntrial;
+        if ((rc = sl_set_tuning(C, &trial[t]))) break;
         if ((rc = sl_step(C, 3, dt))) break;
         for (int attempt = 0; attempt < 3 && rc == SL_OK; ++attempt) {
           const int64_t rb0 = C->rebuilds;
@@ -179,12 +170,12 @@ int sl_autotune(sl_system *S, int steps, double dt, sl_tuning *chosen) {
     sl_destroy(C);
     if (rc) return fail(S, rc, "autotune trial: " + err);
     int bt = 0;
-    for (int t = 1; t < kTrials; ++t)
+    for (int t = 1; t < ntrial; ++t)
       if (best[t] < best[bt]) bt = t;
-    v[0] = trial[bt][0];
-    v[1] = S->prm.frozen && v[0] ? 1 : trial[bt][1];
+    v[0] = trial[bt].spin_lanes;
+    v[1] = trial[bt].force_lanes;
     v[2] = S->small_class;
-    v[3] = trial[bt][2];
+    v[3] = trial[bt].jcache;
     cache_store(key, v);
   }
   sl_tuning t{v[0], v[1], v[2], v[3], S->overlap};

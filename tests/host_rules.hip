@@ -21,7 +21,42 @@ static void variants(const char *tag) {
   std::printf("%s_spline_cache_at_first %d\n", tag, spin_variant(with, P, &without));
 }
 
+// Autotuner candidates of a system of K equal classes: their number, whether the first
+// is the default, and the number of distinct launch shapes among them.
+static void candidates(const char *tag, int prec, int n, int K, bool frozen, bool soc) {
+  sl_system S;
+  S.prec = prec;
+  S.n = n;
+  S.K = K;
+  S.jcache = prec == SL_FP32 ? 1 : -1;
+  S.prm.frozen = frozen;
+  S.pc.soc_on = soc;
+  S.prof = true;  // (timing the caller's launches does not narrow the choice)
+  for (int c = 0; c <= K; ++c) S.class_off.push_back((int)((long)n * c / K));
+  const std::vector<sl_tuning> t = tune_candidates(&S);
+  std::vector<std::vector<int>> shapes;
+  int distinct = 0, cached = 0;
+  for (const sl_tuning &x : t) {
+    sl_system D = S;
+    D.prof = false;
+    apply_tuning(&D, x);
+    const std::vector<int> v = launch_shape(&D);
+    distinct += std::find(shapes.begin(), shapes.end(), v) == shapes.end();
+    cached += v.back();
+    shapes.push_back(v);
+  }
+  std::printf("%s_count %d\n%s_distinct %d\n%s_cached %d\n", tag, (int)t.size(), tag, distinct, tag, cached);
+  std::printf("%s_default_first %d\n", tag, t[0].spin_lanes == 0 && t[0].force_lanes == 0 && t[0].jcache == 0);
+  std::printf("%s_default_one_workgroup %d\n", tag, shapes[0][0] == 0);
+}
+
 int main() {
+  candidates("small", SL_FP64, 1024, 4, false, false);
+  candidates("middle", SL_FP64, 24334, 10, false, false);
+  candidates("middle_fp32", SL_FP32, 24334, 10, false, false);
+  candidates("large", SL_FP64, 432000, 4, false, false);
+  candidates("frozen", SL_FP64, 65536, 4, true, false);
+  candidates("soc", SL_FP64, 27648, 10, false, true);
   variants<double>("fp64");
   variants<float>("fp32");
   for (long nbucket : {1L, 5L, 16384L, 1L << 26, 1L << 30})

@@ -53,3 +53,14 @@ def test_benchmark_reports_the_default_lanes(rules):
                 assert rules[f"spin_lanes_{prec}_{jc}_{m}"] == bench.default_spin_lanes(prec, m, jc > 0)
     for n in (1, 12000, 12001, 120000, 120001, 432000):
         assert rules[f"force_lanes_{n}"] == bench.default_force_lanes(n)
+
+
+@pytest.mark.parametrize("system", ["small", "middle", "middle_fp32", "large", "frozen", "soc"])
+def test_autotuner_tries_the_default_and_no_shape_twice(rules, system):
+    r = {k[len(system) + 1:]: v for k, v in rules.items() if k.startswith(system + "_")}
+    assert r["default_first"] == 1
+    assert r["default_one_workgroup"] == (1 if system == "small" else 0)
+    # every lane count, with the cache and without (with the spin-orbit terms none is
+    # read); the default may be one of them
+    assert r["distinct"] == r["count"] >= (4 if system == "soc" else 8)
+    assert r["cached"] == 0 if system == "soc" else r["cached"] >= 4
