@@ -68,6 +68,22 @@ int clone_system(sl_system *S, sl_system **out) {
   if ((rc = sl_set_ordering(C, S->ordering, S->sgrid))) return bail(rc);
   if ((rc = sl_set_row_order(C, S->row_q))) return bail(rc);
   if ((rc = sl_set_step(C, S->step))) return bail(rc);
+  // and the colour classes, as a repair at these positions leaves them: a run from a
+  // perfect lattice keeps few large classes, a fresh colouring of its displaced atoms
+  // has more and smaller ones, for which other shapes are the fastest (432 000 atoms
+  // after 60 steps: 4 classes and 11)
+  if (S->K > 0 && S->have_colour) {
+    if ((rc = ensure_ready(C))) return bail(rc);
+    const int n = S->n;
+    std::vector<int> cu(n), ci(n), id(n);
+    if ((rc = sl_get_coloring(S, cu.data(), nullptr))) return bail(rc);
+    Atoms &A = C->a[C->cur];
+    if (hipMemcpy(id.data(), A.id, sizeof(int) * n, hipMemcpyDeviceToHost) != hipSuccess) return bail(SL_E_HIP);
+    for (int i = 0; i < n; ++i) ci[i] = cu[id[i]];
+    if (hipMemcpy(A.colour, ci.data(), sizeof(int) * n, hipMemcpyHostToDevice) != hipSuccess) return bail(SL_E_HIP);
+    C->Kbase = S->Kbase;
+    if ((rc = rebuild(C))) return bail(rc);
+  }
   *out = C;
   return SL_OK;
 }
