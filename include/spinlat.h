@@ -294,9 +294,8 @@ int sl_synchronize(sl_system *sys);
 /* Launch shape of the per-step kernels. Changes speed only: the results
  * differ at most by summation-order roundoff. lanes = 1, 2, 4 or 8 lanes
  * cooperate on one atom. 0 = default: in the spin phase chosen per class from
- * its size, in the force launch from the number of atoms (a value set there is
- * the least number taken; a system too small to fill the device takes more),
- * and the spin half-steps of a system of a few thousand atoms in one workgroup
+ * its size, in the force launch from the number of atoms (8, 4 and 1 in rising
+ * size), and the spin half-steps of a system of a few thousand atoms in one workgroup
  * (spin_lanes and jcache both 0). sl_get_tuning reports a field at its default
  * as 0, and all three of spin_lanes, force_lanes and jcache at their defaults as
  * 2, 1 and 0, which sl_set_tuning takes for the default too: setting what is

@@ -246,13 +246,13 @@ inline bool spin_lds_on(const sl_system *S) {
 }
 // Force launch: wavefronts per 64 atoms. 1 / 4 / 8 wavefronts: 8192 atoms 23 /
 // 12.1 / 11.9, 27 648 atoms 23.5 / 15.0 / 15.9, 65 536 atoms 24.3 / 20.7 / 25.2,
-// 128 000 atoms 35.4 / 34.4 / 43.8, 432 000 atoms 85 / 94 / 129. A tuned shape
-// (1 or 2 lanes, or what the caller sets) is the least that the launch takes.
-// The split force takes 1 or 2.
+// 128 000 atoms 35.4 / 34.4 / 43.8, 432 000 atoms 85 / 94 / 129. The split force takes
+// 1 or 2: 1 by default. A count that the caller sets is the one that runs.
 constexpr int kForceSpread = 12000, kForceFull = 120000;
 inline int force_lanes_for(const sl_system *S) {
-  if (S->overlap > 0) return S->force_lanes;
-  return std::max(S->force_lanes, S->n <= kForceSpread ? 8 : (S->n <= kForceFull ? 4 : 1));
+  if (!S->force_auto) return S->force_lanes;
+  if (S->overlap > 0) return 1;
+  return S->n <= kForceSpread ? 8 : (S->n <= kForceFull ? 4 : 1);
 }
 // Exchange cache: on for FP32; in FP64 where what it takes off the spin launches
 // (0.4 us each, 0.7 us with the bath; 4K - 4 launches a step) outweighs its own

@@ -134,8 +134,10 @@ extern "C" {
 int sl_autotune(sl_system *S, int steps, double dt, sl_tuning *chosen) {
   if (!S || steps < 1 || !std::isfinite(dt) || dt == 0.0) return fail(S, SL_E_ARG, "bad autotune arguments");
   CHK(ensure_ready(S));
+  // ("lanes=set": lines from when a force-lane count was only the least that ran lack it
+  // and are not found)
   const std::string key = tune_key(
-      "system n=" + std::to_string(S->n) + " prec=" + std::to_string(S->prec) +
+      "system lanes=set n=" + std::to_string(S->n) + " prec=" + std::to_string(S->prec) +
       " frozen=" + std::to_string(S->prm.frozen) + " langevin=" + std::to_string(S->pc.langevin) +
       " aniso=" + std::to_string(S->pc.aniso_on) + " mlp=" + std::to_string(S->mlp ? 1 : 0) +
       " K=" + std::to_string(S->K));

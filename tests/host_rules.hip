@@ -79,6 +79,13 @@ int main() {
     sl_system S;
     S.n = n;
     std::printf("force_lanes_%d %d\n", n, force_lanes_for(&S));
+    for (int lanes : {1, 2, 4, 8})
+      for (int overlap : {-1, 1}) {
+        apply_tuning(&S, {0, lanes, 0, 0, overlap});
+        std::printf("force_lanes_%d_set_%d_%d %d\n", n, lanes, overlap, force_lanes_for(&S));
+      }
+    apply_tuning(&S, {0, 0, 0, 0, 1});
+    std::printf("force_lanes_%d_split %d\n", n, force_lanes_for(&S));
   }
   return 0;
 }

@@ -64,3 +64,11 @@ def test_autotuner_tries_the_default_and_no_shape_twice(rules, system):
     # read); the default may be one of them
     assert r["distinct"] == r["count"] >= (4 if system == "soc" else 8)
     assert r["cached"] == 0 if system == "soc" else r["cached"] >= 4
+
+
+@pytest.mark.parametrize("n", [1, 12000, 12001, 120000, 120001, 432000])
+def test_force_lanes_that_are_set_are_those_that_run(rules, n):
+    for lanes in (1, 2, 4, 8):
+        for overlap in (-1, 1):
+            assert rules[f"force_lanes_{n}_set_{lanes}_{overlap}"] == lanes
+    assert rules[f"force_lanes_{n}_split"] == 1
