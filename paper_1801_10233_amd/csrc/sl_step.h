@@ -668,15 +668,12 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
   double rix = 0, riy = 0, riz = 0;
   real six = 0, siy = 0, siz = 0;
   // with several wavefronts per team the mass, velocity and build position of
-  // the closing part are loaded with the atom's other data, off the end of the
-  // chain
+  // the closing part are loaded before the barrier that joins the sums, off the end
+  // of the chain (loaded first of all, their addresses were held over the whole
+  // gather: 89 of the 238 forms with several wavefronts then reserved scratch, and
+  // the embedded-atom ones kept 3 instead of 4 wavefronts per SIMD; as fast)
   constexpr bool kEarly = WAVES > 1 && !kPairPass && (MODE & (kModeFinal | kModeNext)) != 0;
   double em = 0, evx = 0, evy = 0, evz = 0, ebx = 0, eby = 0, ebz = 0;
-  if (kEarly && valid && w == 0) {
-    em = A.mass[i];
-    evx = A.vx[i]; evy = A.vy[i]; evz = A.vz[i];
-    ebx = A.bx[i]; eby = A.by[i]; ebz = A.bz[i];
-  }
   if (valid) {
     rix = S.rx[i]; riy = S.ry[i]; riz = S.rz[i];
     const int is = i < S.held ? S.n + i : i;
@@ -807,6 +804,11 @@ __device__ __forceinline__ void force_atom(const SysView<real> &S, const PotCons
     segment(std::integral_constant<int, 0>{}, std::integral_constant<int, SL_FORCE_CHUNK0>{});
     if (!kSpinPass)
       segment(std::integral_constant<int, 1>{}, std::integral_constant<int, SL_FORCE_CHUNK1>{});
+  }
+  if (kEarly && valid && w == 0) {
+    em = A.mass[i];
+    evx = A.vx[i]; evy = A.vy[i]; evz = A.vz[i];
+    ebx = A.bx[i]; eby = A.by[i]; ebz = A.bz[i];
   }
   if constexpr (WAVES > 1) {
     const int lane = threadIdx.x & 63;
