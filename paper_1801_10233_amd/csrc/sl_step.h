@@ -428,7 +428,6 @@ struct SpinAhead {
   int i, ns;              // atom (-1: none), row length
   uint32_t aid;
   int j[kSlots];
-  float jt[MLP == 1 ? kSlots : 1];
   real J[kSlots];
   real g[3];              // noise of update LANES - 1 - w
 };
@@ -451,7 +450,7 @@ __device__ __forceinline__ void spin_ahead_load(const SysView<real> &S, const Se
     const int k = w + LANES * c;
     const bool in = k < S.kcap;
     a.j[c] = in ? S.nbr[(size_t)k * S.ld + i] : i;
-    if (MLP == 1) a.jt[c] = in ? tab[(size_t)k * S.ld + i].x : 0.f;
+    if (MLP == 1) a.J[c] = in ? (real)tab[(size_t)k * S.ld + i].x : (real)0;
     if (MLP == 3) a.J[c] = in ? jc[(size_t)k * S.ld + i] : (real)0;
   }
 }
@@ -491,7 +490,6 @@ __device__ __forceinline__ void spin_ahead_finish(const SysView<real> &S, const 
   }
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    if (MLP == 1) a.J[c] = (real)a.jt[c];
     if (w + LANES * c >= a.ns) a.J[c] = (real)0;
   }
 }
@@ -516,8 +514,9 @@ __device__ __forceinline__ void spin_sequence(Seq q, const SysView<real> &S, con
     const bool valid = i >= 0;
     real ax = 0, ay = 0, az = 0, x = 0, y = 0, z = 0;
     const int ns = a.ns;
-    // four slots at a time, the next piece's loads behind the last four
-    constexpr int G = CH < 4 ? CH : 4;
+    // four slots at a time, the next piece's loads behind the last four (two with the
+    // bath and the anisotropy on two wavefronts, where four spilled)
+    constexpr int G = LANES < 4 && LANGEVIN && ANISO ? 2 : (CH < 4 ? CH : 4);
     real qx[G], qy[G], qz[G], J[G];
 #pragma unroll
     for (int g = 0; g < CH; g += G) {

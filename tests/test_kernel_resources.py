@@ -44,7 +44,7 @@ RESERVED = {"void sl::k_force<float, 6, 1, 12>", "void sl::k_force<float, 7, 1, 
 
 
 @pytest.mark.parametrize("family,least", [("k_force<", 300), ("k_pair<", 16), ("k_eam_density<", 2),
-                                          ("k_spin_phase<", 200), ("k_spin_tail<", 20),
+                                          ("k_spin_phase<", 200), ("k_spin_tail<", 20), ("k_spin_lds<", 12),
                                           ("k_batch_force<", 50), ("k_batch_spin<", 10),
                                           ("k_batch_tail<", 4)])
 def test_step_kernels_use_no_scratch(kernels, family, least):
