@@ -65,8 +65,18 @@ __global__ __launch_bounds__((64 * TeamShape<LANES, LANGEVIN>::waves)) void k_sp
 // adds) in one workgroup: the items are applied in order with a workgroup
 // barrier between them, which keeps the class order of the sweep while
 // paying one launch for the whole run. Teams of kTailLanes wavefronts whatever
-// the launch shape of the large classes.
-constexpr int kTailLanes = 4;
+// the launch shape of the large classes. Classes of more than the 128 atoms that
+// such teams take in one pass (a set small_class) go on kTailWide wavefronts per 64
+// atoms, in FP32 with ready coefficients also with twice the threads (from positions that
+// is more than 128 registers), where fewer passes outweigh the longer ones (at most
+// kTailWide successive updates draw their noise there). Microseconds per
+// step with the bath, classes of 128 and up to 1024 atoms or so in one run: FP64
+// 3456 atoms 437 on four wavefronts, 360 on two; FP32 362 and 276.
+constexpr int kTailLanes = 4, kTailWide = 2;
+template <typename real, int LANES, int MLP>
+constexpr int kTailThreads =
+    sizeof(real) == 4 && LANES == kTailWide && (MLP == 1 || MLP == 3) ? 1024 : kTailBlock;
+template <int ATOMS>
 struct TailSeq {
   const TailArgs &T;
   int item, base;
@@ -79,7 +89,7 @@ struct TailSeq {
   template <typename real> __device__ const float4 *tab(const SysView<real> &S) const { return S.tab; }
   template <typename real> __device__ const real *jc(const SysView<real> &S) const { return S.jc; }
   __device__ void advance() {
-    base += kTailBlock / kTailLanes;
+    base += ATOMS;
     if (base >= T.item[item].end && ++item < T.nitems) base = T.item[item].begin;
   }
   __device__ explicit TailSeq(const TailArgs &t) : T(t), item(0), base(t.item[0].begin) {}
@@ -90,21 +100,21 @@ struct TailSeq {
     return *this;
   }
 };
-template <typename real, bool LANGEVIN, bool ANISO, int MLP>
-__global__ __launch_bounds__(kTailBlock) void k_spin_tail(SysView<real> S, PotConst P,
+template <typename real, bool LANGEVIN, bool ANISO, int LANES, int MLP>
+__global__ __launch_bounds__((kTailThreads<real, LANES, MLP>)) void k_spin_tail(SysView<real> S, PotConst P,
                                                           TailArgs T) {
-  constexpr int kTeams = kTailBlock / 64 / kTailLanes;
-  __shared__ SpinTeam<real, kTailLanes> team[kTeams];
+  constexpr int kTeams = kTailThreads<real, LANES, MLP> / 64 / LANES;
+  __shared__ SpinTeam<real, LANES> team[kTeams];
   if constexpr (MLP != 4) {
-    spin_sequence<real, LANGEVIN, ANISO, kTailLanes, kTeams, MLP>(TailSeq(T), S, P, S.sx, S.sy, S.sz, team, T.h,
+    spin_sequence<real, LANGEVIN, ANISO, LANES, kTeams, MLP>(TailSeq<64 * kTeams>(T), S, P, S.sx, S.sy, S.sz, team, T.h,
                                                                   T.amp, T.seed, T.replica, T.rs2);
   } else {
-    const int t = wave_id() / kTailLanes, w = wave_id() % kTailLanes;
+    const int t = wave_id() / LANES, w = wave_id() % LANES;
     for (int q = 0; q < T.nitems; ++q) {
       const TailItem &it = T.item[q];
       for (int base = it.begin; base < it.end; base += 64 * kTeams) {
         const int i = base + 64 * t + (int)(threadIdx.x & 63);
-        spin_update<real, LANGEVIN, ANISO, kTailLanes, MLP>(S, P, i, i < it.end, w, team + t, it.nrep,
+        spin_update<real, LANGEVIN, ANISO, LANES, MLP>(S, P, i, i < it.end, w, team + t, it.nrep,
                                                             it.step, it.sub, T.h, T.amp, T.seed,
                                                             T.replica, T.rs2);
         __syncthreads();
@@ -372,14 +382,26 @@ void launch_spin_phase(const SysView<real> &S, const PotConst &P, const SpinPhas
   }
 }
 
-template <typename real, int MLP>
+template <typename real, int LANES, int MLP>
 static void spin_tail_run(const SysView<real> &S, const PotConst &P, const TailArgs &T,
                           hipStream_t st) {
   const bool lg = P.langevin != 0, an = P.aniso_on != 0;
-  if (lg && an) hipLaunchKernelGGL((k_spin_tail<real, true, true, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
-  else if (lg) hipLaunchKernelGGL((k_spin_tail<real, true, false, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
-  else if (an) hipLaunchKernelGGL((k_spin_tail<real, false, true, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
-  else hipLaunchKernelGGL((k_spin_tail<real, false, false, MLP>), dim3(1), dim3(kTailBlock), 0, st, S, P, T);
+  if (lg && an) hipLaunchKernelGGL((k_spin_tail<real, true, true, LANES, MLP>), dim3(1), dim3((kTailThreads<real, LANES, MLP>)), 0, st, S, P, T);
+  else if (lg) hipLaunchKernelGGL((k_spin_tail<real, true, false, LANES, MLP>), dim3(1), dim3((kTailThreads<real, LANES, MLP>)), 0, st, S, P, T);
+  else if (an) hipLaunchKernelGGL((k_spin_tail<real, false, true, LANES, MLP>), dim3(1), dim3((kTailThreads<real, LANES, MLP>)), 0, st, S, P, T);
+  else hipLaunchKernelGGL((k_spin_tail<real, false, false, LANES, MLP>), dim3(1), dim3((kTailThreads<real, LANES, MLP>)), 0, st, S, P, T);
+}
+
+template <typename real, int MLP>
+static void spin_tail_lanes(const SysView<real> &S, const PotConst &P, const TailArgs &T, hipStream_t st) {
+  int m = 0, reps = 0;
+  for (int q = 0; q < T.nitems; ++q) {
+    m = std::max(m, T.item[q].end - T.item[q].begin);
+    reps = std::max(reps, T.item[q].nrep);
+  }
+  if constexpr (MLP != 4)
+    if (m > kTailBlock / kTailLanes && reps <= kTailWide) return spin_tail_run<real, kTailWide, MLP>(S, P, T, st);
+  spin_tail_run<real, kTailLanes, MLP>(S, P, T, st);
 }
 
 template <typename real>
@@ -387,11 +409,11 @@ void launch_spin_tail(const SysView<real> &S, const PotConst &P, const TailArgs 
   if (T.nitems <= 0) return;
   constexpr bool f32 = sizeof(real) == 4;
   switch (spin_variant<real>(S, P, nullptr)) {
-    case 4: spin_tail_run<real, 4>(S, P, T, st); break;
-    case 3: spin_tail_run<real, 3>(S, P, T, st); break;
-    case 2: spin_tail_run<real, (f32 ? 2 : 0)>(S, P, T, st); break;
-    case 1: spin_tail_run<real, (f32 ? 1 : 0)>(S, P, T, st); break;
-    default: spin_tail_run<real, 0>(S, P, T, st); break;
+    case 4: spin_tail_lanes<real, 4>(S, P, T, st); break;
+    case 3: spin_tail_lanes<real, 3>(S, P, T, st); break;
+    case 2: spin_tail_lanes<real, (f32 ? 2 : 0)>(S, P, T, st); break;
+    case 1: spin_tail_lanes<real, (f32 ? 1 : 0)>(S, P, T, st); break;
+    default: spin_tail_lanes<real, 0>(S, P, T, st); break;
   }
 }
 
