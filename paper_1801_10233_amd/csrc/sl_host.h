@@ -162,6 +162,7 @@ struct sl_system {
   double *eam = nullptr;  // embedded-atom F'(rho), F(rho) per atom [2][ld]
   bool jc_ok[2] = {false, false};
   int jc_rows[2] = {0, 0};  // slots per row that each cache was allocated for
+  bool jc_failed = false;   // no memory for a cache: positions are read until the next setting
 
   bool prof = false;
   int prof_every = 1;     // time the launches of every prof_every-th step
@@ -260,6 +261,7 @@ inline int force_lanes_for(const sl_system *S) {
 // (110 592 atoms: 6.9 -> 5.6 us; 432 000 atoms, one lane: 14.3 -> 9.1), and on a
 // frozen lattice, whose coefficients never change.
 inline bool jcache_on(const sl_system *S) {
+  if (S->jc_failed) return false;
   if (!S->jc_auto || S->prec == SL_FP32) return S->jcache > 0;
   return S->prm.frozen || spin_lds_on(S) || S->pc.langevin || S->K >= 7 || S->n > 4 * kSpinFull;
 }
@@ -271,6 +273,7 @@ inline void apply_tuning(sl_system *S, const sl_tuning &t) {
   S->spin_auto = all || t.spin_lanes == 0;
   S->force_auto = all || t.force_lanes == 0;
   S->jc_auto = t.jcache == 0;
+  S->jc_failed = false;
   S->spin_lanes = S->spin_auto ? 2 : t.spin_lanes;
   S->force_lanes = S->force_auto ? 1 : t.force_lanes;
   S->small_class = t.small_class == 0 ? kSmallClassDefault : t.small_class;

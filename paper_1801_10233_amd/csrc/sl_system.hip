@@ -236,7 +236,19 @@ int ensure_jcache(sl_system *S, int b) {
     S->jc[b] = nullptr;
     S->jc_rows[b] = 0;
     real *p = nullptr;
-    HIPCHK(S, dalloc(&p, (size_t)S->ld * rows));
+    if (dalloc(&p, (size_t)S->ld * rows) != hipSuccess) {
+      // the launches read positions instead; the other position's cache is of no
+      // use then, and asking again at every half-step would cost more than it could give
+      (void)hipGetLastError();
+      for (int q = 0; q < 2; ++q) {
+        dfree(S->jc[q]);
+        S->jc[q] = nullptr;
+        S->jc_rows[q] = 0;
+        S->jc_ok[q] = false;
+      }
+      S->jc_failed = true;
+      return SL_OK;
+    }
     S->jc[b] = p;
     S->jc_rows[b] = rows;
   }
@@ -1241,6 +1253,7 @@ int sl_set_neighbor(sl_system *S, double skin, int max_nbr) {
       S->jc_ok[b] = false;
     }
   }
+  S->jc_failed = false;
   S->user_list = false;
   S->have_list = false;
   S->have_D = false;

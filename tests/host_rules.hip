@@ -61,6 +61,16 @@ int main() {
   variants<float>("fp32");
   for (long nbucket : {1L, 5L, 16384L, 1L << 26, 1L << 30})
     std::printf("sort_threads_%ld %ld\n", nbucket, (long)bucket_sort_blocks((int)nbucket) * kBlock);
+  for (int prec : {SL_FP64, SL_FP32}) {
+    sl_system S;
+    S.prec = prec;
+    apply_tuning(&S, {0, 0, 0, 1, 0});
+    std::printf("cache_%d_on %d\n", prec, jcache_on(&S));
+    S.jc_failed = true;
+    std::printf("cache_%d_failed %d\n", prec, jcache_on(&S));
+    apply_tuning(&S, {0, 0, 0, 1, 0});
+    std::printf("cache_%d_set_again %d\n", prec, jcache_on(&S));
+  }
   for (int rows : {1, 5, 6, 63, 80, 640, 641, 400000}) {
     const int slots = slots_per_group(rows, 5);
     std::printf("slots_%d %d\n", rows, slots);

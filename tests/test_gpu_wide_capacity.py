@@ -1,6 +1,7 @@
-"""A list capacity far above the rows it holds (the caller's choice, which also
+"""List capacities. One far above the rows it holds (the caller's choice, which also
 bounds the launches over slots) changes nothing: the learned potential's pairs and
-the exchange cache of a caller's list, 128 atoms, bit for bit as with the default."""
+the exchange cache of a caller's list, 128 atoms, bit for bit as with the default. The
+cache is sized by the spin segment, down to fewer slots than a first round reads."""
 import ctypes
 import os
 
@@ -9,7 +10,7 @@ import pytest
 
 from paper_1801_10233_amd import spinlat as sl
 from paper_1801_10233_amd import workloads as W
-from tests.common import make_gpu
+from tests.common import make_gpu, make_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -98,3 +99,18 @@ def test_exchange_cache_follows_a_callers_longer_rows():
         runs.append(g)
     for x, y in zip(runs[0].get_state(), runs[1].get_state()):
         assert np.abs(x - y).max() < 1e-12 * max(1.0, np.abs(y).max())
+
+
+@pytest.mark.parametrize("shape", [(0, 0, 0, 0), (1, 1, -1, 1), (2, 2, 4096, 1), (4, 4, -1, 1), (8, 8, -1, 1)])
+@pytest.mark.parametrize("physics", ["nve", "langevin"])
+def test_fewer_slots_than_a_first_round(physics, shape):
+    # eight nearest neighbours, and room for no more
+    w = W.coupled_nve(n=6) if physics == "nve" else W.large_langevin(n=6)
+    w.pot = dict(w.pot, ex_rc=2.55)
+    w.skin = 0.2
+    o, g = make_oracle(w), make_gpu(w, max_spin_nbr=8)
+    g.set_tuning(*shape)
+    o.step(10, w.dt)
+    g.step(10, w.dt)
+    assert g.stats()["max_spin_nbr_seen"] == 8
+    assert np.abs(g.get_state()[2] - o.get_state()[2]).max() < 1e-12

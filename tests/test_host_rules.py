@@ -72,3 +72,8 @@ def test_force_lanes_that_are_set_are_those_that_run(rules, n):
         for overlap in (-1, 1):
             assert rules[f"force_lanes_{n}_set_{lanes}_{overlap}"] == lanes
     assert rules[f"force_lanes_{n}_split"] == 1
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_cache_without_memory_is_off_until_set_again(rules, precision):
+    assert [rules[f"cache_{precision}_{k}"] for k in ("on", "failed", "set_again")] == [1, 0, 1]
