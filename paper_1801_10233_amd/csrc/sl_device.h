@@ -483,8 +483,11 @@ __device__ __forceinline__ double fma_sc(double a, double b, double c) {
 //
 // -2 ln u: u = 2^k (1 + f) with sqrt(1/2) <= 1 + f < sqrt(2), s = f/(2 + f)
 // and ln(1 + f) = 2 atanh(s) = f - s (f - R), R = 2 (s^2/3 + s^4/5 + ...)
-// (2s = f - s f, so the rounding of s enters scaled by f). The series is cut
-// at s^20 (2e-17 relative).
+// (2s = f - s f, so the rounding of s enters scaled by f). This arrangement
+// and the two-part ln 2 below are those of the logarithm of fdlibm, Sun
+// Microsystems' freely distributable math library (1993); R is atanh's own
+// Taylor series in place of its minimax polynomial, cut at s^20 (2e-17
+// relative).
 __device__ __forceinline__ double neg2_log(double u) {
   double m = __builtin_amdgcn_frexp_mant(u);  // [1/2, 1)
   int k = __builtin_amdgcn_frexp_exp(u);

@@ -158,6 +158,7 @@ struct ColourArgs {
   double L[3], invL[3];
   double cr2;
   int *rows;       // [n][16] packed conflicting neighbours (k_colour_indeg)
+  int *any_long;   // 1: some atom has more of them than a packed row holds
   int mutual;      // 1: j in the row of i means i in the row of j
   const int *err;  // sticky error word
 };
