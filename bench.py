@@ -179,6 +179,17 @@ def default_force_lanes(n_atoms):
     return 8 if n_atoms <= 12000 else (4 if n_atoms <= 120000 else 1)
 
 
+def launch_shape(tuning, precision, n_atoms, colours, table_launches):
+    """Spin lanes, force lanes and whether the exchange cache was read, of an analytic run
+    of equal classes under `tuning` (its table launches are the cache's)."""
+    spin, force, jcache = tuning["spin_lanes"], tuning["force_lanes"], tuning["jcache"]
+    if (spin, force, jcache) == (2, 1, 0):      # the default as it is reported
+        spin = force = 0
+    on = jcache > 0 or (jcache == 0 and table_launches > 0)
+    return (spin or default_spin_lanes(precision, n_atoms / colours, on),
+            force or default_force_lanes(n_atoms), on)
+
+
 def timed_run(S, steps, dt, profile=False):
     S.synchronize()
     sync()
@@ -577,12 +588,7 @@ def main():
     launches, ms, work = kinds[dom]
     n_prof = kinds[sl.PROF_FORCE][0]          # one force launch per timed step
     tun = S.tuning()
-    # (the table launches of an analytic run are the exchange cache's)
-    jc_on = tun["jcache"] > 0 or (tun["jcache"] == 0 and sl.PROF_TABLE in kinds)
-    if (tun["spin_lanes"], tun["force_lanes"], tun["jcache"]) == (2, 1, 0):  # the default
-        tun = dict(tun, spin_lanes=0, force_lanes=0)
-    spin_lanes = tun["spin_lanes"] or default_spin_lanes(prec, w.N / st["n_colours"], jc_on)
-    force_lanes = tun["force_lanes"] or default_force_lanes(w.N)
+    spin_lanes, force_lanes, jc_on = launch_shape(tun, prec, w.N, st["n_colours"], prof[sl.PROF_TABLE][0])
     # the method's bytes per update; the cached form reads its 14 coefficients
     # in place of the own position (moved_bytes_per_unit), which makes the
     # launch faster but is not counted as more work done

@@ -77,3 +77,16 @@ def test_force_lanes_that_are_set_are_those_that_run(rules, n):
 @pytest.mark.parametrize("precision", [0, 1])
 def test_cache_without_memory_is_off_until_set_again(rules, precision):
     assert [rules[f"cache_{precision}_{k}"] for k in ("on", "failed", "set_again")] == [1, 0, 1]
+
+
+def test_benchmark_names_the_launches_that_ran():
+    import sys
+    sys.path.insert(0, os.path.dirname(HERE))
+    import bench
+    f64, f32 = bench.sl.SL_FP64, bench.sl.SL_FP32
+    default = dict(spin_lanes=2, force_lanes=1, jcache=0)
+    assert bench.launch_shape(default, f64, 432000, 4, 10) == (1, 1, True)
+    assert bench.launch_shape(default, f32, 432000, 4, 10) == (4, 1, True)
+    assert bench.launch_shape(default, f64, 16000, 4, 0) == (4, 4, False)
+    assert bench.launch_shape(dict(spin_lanes=8, force_lanes=0, jcache=-1), f64, 16000, 4, 0) == (8, 4, False)
+    assert bench.launch_shape(dict(spin_lanes=2, force_lanes=1, jcache=1), f64, 432000, 4, 10) == (2, 1, True)
