@@ -104,7 +104,7 @@ ColourArgs colour_args(sl_system *S) {
 // largest colour.
 constexpr int kFinishMax = 4096, kFinishRounds = 4096;
 int jp_rounds(sl_system *S, const ColourArgs &C, int *mc) {
-  HIPCHK(S, hipMemsetAsync(S->jpcnt, 0, 7 * sizeof(int), S->st));
+  HIPCHK(S, hipMemsetAsync(S->jpcnt, 0, 8 * sizeof(int), S->st));
   launch_colour_indeg(C, S->ctmp, S->jpmask[0], S->jpmask[1], S->jplist[0], &S->jpcnt[0], S->st);
   int r = 0;
   for (;;) {

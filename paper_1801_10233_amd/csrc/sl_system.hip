@@ -1019,7 +1019,7 @@ int sl_create(const sl_params *p, sl_system **out) {
   A_(dalloc(&S->stage, 3 * (size_t)n));
   A_(dalloc(&S->err, 1));
   A_(dalloc(&S->seen, 2));
-  A_(dalloc(&S->jpcnt, 7));
+  A_(dalloc(&S->jpcnt, 8));  // (whole 16-byte words: one fill launch clears them)
   A_(dalloc(&S->jplist[0], (size_t)n));
   A_(dalloc(&S->jplist[1], (size_t)n));
   A_(dalloc(&S->jpmask[0], (size_t)n));
